@@ -718,8 +718,9 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
             plan.add(reinterpret_cast<void **>(&h->d_skw1), sizeof(double) * 2 * off);
         }
     }
-    h->fin_len = 4 * static_cast<size_t>(h->nmax) + 2 * static_cast<size_t>(h->nmax) * h->nmax + 8 +
-                 static_cast<size_t>(h->tc_lags) * h->nmax;
+    // fin1d_at, then the lag products of she_stats
+    h->fin_len = 4 * static_cast<size_t>(h->nmax) + 8 + static_cast<size_t>(h->tc_lags) * h->nmax;
+    if (corr) h->fin_len += 2 * static_cast<size_t>(h->nmax) * h->nmax;
     return SHE_OK;
 }
 
@@ -832,7 +833,7 @@ static she_status plan_nd(she_handle *h, const she_config *cfg, Plan &plan)
     plan.add(reinterpret_cast<void **>(&h->d_part), 2 * sizeof(double) * h->nparts * h->n_inst);
     plan.add(reinterpret_cast<void **>(&h->d_step), sizeof(int64_t));
     h->graph_steps = cfg->graph_steps;
-    h->fin_len = 8;
+    h->fin_len = 4 + kFinParts;
     if (h->mask & SHE_STAT_SK) {
         // shells round(|k|), signed k in [-N/2, N/2); mode counts per shell
         const double kmax = std::sqrt(0.25 * nx * nx + 0.25 * p.ny * p.ny);
@@ -860,7 +861,7 @@ static she_status plan_nd(she_handle *h, const she_config *cfg, Plan &plan)
             plan.add(reinterpret_cast<void **>(&h->d_skwm), nb);
             plan.add(reinterpret_cast<void **>(&h->d_skwm2), nb);
         }
-        h->fin_len = 3 + h->nbins;
+        h->fin_len = 4 + h->nbins + kFinParts;
     }
     return SHE_OK;
 }
@@ -1406,6 +1407,15 @@ static she_status copy_out(she_handle *h, double *dst, int64_t cap, const double
     return SHE_OK;
 }
 
+// Finalisation results of one 1D instance in d_fin: mean[N], var[N], sum, S_k
+// [N], covariance [N^2] (this much is copied to the host, up to what the
+// caller asked for), then the scratch: circulant sums [N], second moments [N^2].
+static Fin1D fin1d_at(double *fin, int64_t n)
+{
+    double *sk = fin + 2 * n + 1, *cov = sk + n, *circ = cov + n * n;
+    return Fin1D{fin, fin + n, fin + 2 * n, cov, sk, circ + n, circ};
+}
+
 extern "C" she_status she_stats(she_handle *h, int32_t instance, she_stats_out *out)
 {
     if (!h || !out) return fail(h, SHE_EINVAL, "NULL argument");
@@ -1471,24 +1481,26 @@ extern "C" she_status she_stats(she_handle *h, int32_t instance, she_stats_out *
         const int N = h->tab[instance].n;
         const bool corr = h->tab[instance].x_off >= 0;
         const int rows = static_cast<int>(acc.n_samples % kCorrBlock);
-        SHE_HIP(h, launch_fin1d(h->prec, s, h->d_tab, instance, N, h->d_pool, h->d_s1, h->d_s2,
+        // the covariance and S_k are formed and copied only when asked for
+        const bool want = corr && (out->corr || out->sk);
+        const Fin1D fin = fin1d_at(h->d_fin, N);
+        SHE_HIP(h, launch_fin1d(h->prec, s, h->d_tab, instance, N, h->d_pool, h->d_s1, h->d_s2, h->tab[instance].off,
                                 corr ? static_cast<char *>(h->d_x) + h->esz * h->tab[instance].x_off : nullptr,
-                                corr ? h->d_c + h->tab[instance].c_off : nullptr, acc.n_samples, rows, corr,
-                                h->d_fin));
-        const size_t len = 4 * static_cast<size_t>(N) + 2 * static_cast<size_t>(N) * N + 1;
+                                corr ? h->d_c + h->tab[instance].c_off : nullptr, acc.n_samples, rows, want, fin));
+        const int64_t nn = static_cast<int64_t>(N) * N;
+        const size_t len = 3 * static_cast<size_t>(N) + 1 + (want && out->corr ? static_cast<size_t>(nn) : 0);
         std::vector<double> host(len);
         SHE_HIP(h, hipMemcpyAsync(host.data(), h->d_fin, sizeof(double) * len, hipMemcpyDeviceToHost, s));
         SHE_HIP(h, hipStreamSynchronize(s));
-        const int64_t nn = static_cast<int64_t>(N) * N;
         she_status st;
         if (h->d_s1 == nullptr && (out->mean || out->var))
             return fail(h, SHE_EINVAL, "per-cell mean/var need SHE_STAT_MOMENTS");
         if ((st = copy_out(h, out->mean, out->mean_cap, host.data(), N, "mean")) != SHE_OK) return st;
         if ((st = copy_out(h, out->var, out->var_cap, host.data() + N, N, "var")) != SHE_OK) return st;
         if ((out->corr || out->sk) && !corr) return fail(h, SHE_EINVAL, "corr / sk need SHE_STAT_CORR");
-        if ((st = copy_out(h, out->corr, out->corr_cap, host.data() + 2 * N, nn, "corr")) != SHE_OK) return st;
-        if ((st = copy_out(h, out->sk, out->sk_cap, host.data() + 2 * N + nn, N, "sk")) != SHE_OK) return st;
-        out->sum_u = host[3 * N + 2 * nn];
+        if ((st = copy_out(h, out->corr, out->corr_cap, host.data() + 3 * N + 1, nn, "corr")) != SHE_OK) return st;
+        if ((st = copy_out(h, out->sk, out->sk_cap, host.data() + 2 * N + 1, N, "sk")) != SHE_OK) return st;
+        out->sum_u = host[2 * N];
         if (out->tcorr) {
             if (!h->d_tc) return fail(h, SHE_EINVAL, "tcorr needs SHE_STAT_TCORR");
             const int64_t ln = static_cast<int64_t>(h->tc_lags) * N;
