@@ -179,9 +179,12 @@ typedef struct {
                                      64, 256 or 512, or 1024 for an FP32
                                      batch of FE/PC heat instances with
                                      instantaneous noise, uniform material
-                                     and stats_mask 0; an instance
-                                     takes whole waves of a workgroup, small
-                                     instances share one                    */
+                                     and stats_mask 0.  An explicit instance
+                                     of up to 256 cells has a workgroup of its
+                                     own (with 64: one wave); a longer one
+                                     takes as many whole waves as it needs,
+                                     which may be more than this; results are
+                                     identical                                 */
     int32_t rows_per_block;       /* tuning: 2D/3D march length (0 auto)      */
     int32_t rows_per_group;       /* tuning: 3D rows per workgroup (0 auto)   */
     int32_t tuning_flags;         /* SHE_TUNE_* bits (0 = defaults)           */

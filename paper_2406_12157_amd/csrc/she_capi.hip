@@ -6,12 +6,15 @@
 #include "she_internal.hpp"
 
 #include <algorithm>
+#include <array>
 #include <cmath>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <cstdio>
 #include <cstring>
 #include <numeric>
+#include <queue>
 #include <string>
 #include <vector>
 
@@ -68,6 +71,10 @@ struct she_handle {
     std::vector<double> pcr_host;     // implicit schemes: FP64 reduction factors
     double *d_pcr = nullptr;
     size_t smem1d = 0;
+    // explicit batches: the wave kernels' shape (Launch1D)
+    bool rods = false;
+    int rod_block = 64, rod_cpl = 4;
+    int32_t rod_ahead = 0, rod_zrow = 0, rod_slots = 0;
 
     // batch means: samples per batch (0: none) and their arrays
     int32_t batch_len = 0;
@@ -440,19 +447,21 @@ she_status validate(const she_config *cfg, she_handle *h)
 // Instances take whole waves (as many as they have Philox blocks, up to the
 // workgroup) and are packed first-fit, largest first, into workgroups of
 // block / 64 waves and at most 64 KB of LDS.  Returns an error text, or null.
-static const char *pack_1d(const std::vector<Inst1D> &tab, int block, int32_t es, int mode,
-                           std::vector<Seg1D> &segs, int &n_blocks, size_t &smem, int cus)
+static constexpr int kLdsCap1D = 64 * 1024;
+static const char *const kLdsWhy1D = "1D instance too large for LDS (64 KB per workgroup)";
+
+static const char *pack_1d(const std::vector<Inst1D> &tab, int block, int32_t es, std::vector<Seg1D> &segs,
+                           int &n_blocks, size_t &smem, int cus)
 {
     const int W = block / 64;
-    constexpr int kLdsCap = 64 * 1024;
     const int n_inst = static_cast<int>(tab.size());
     std::vector<int> nw(n_inst), bytes(n_inst), idx(n_inst);
     for (int i = 0; i < n_inst; ++i) {
         const int n = tab[i].n, nf = tab[i].bc == SHE_DIRICHLET ? n + 1 : n;
         const int nfg = (nf + 3) / 4;
         nw[i] = std::min(W, (nfg + 63) / 64);
-        bytes[i] = seg_lds(n, nf, es, mode).total;
-        if (bytes[i] > kLdsCap) return "1D instance too large for LDS (64 KB per workgroup)";
+        bytes[i] = seg_lds(n, nf, es, 2).total;
+        if (bytes[i] > kLdsCap1D) return kLdsWhy1D;
         idx[i] = i;
     }
     std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) {
@@ -465,13 +474,13 @@ static const char *pack_1d(const std::vector<Inst1D> &tab, int block, int32_t es
     segs.clear();
     for (int i : idx) {
         size_t bin = 0;
-        while (bin < used_w.size() && (used_w[bin] + nw[i] > W || used_b[bin] + bytes[i] > kLdsCap)) ++bin;
+        while (bin < used_w.size() && (used_w[bin] + nw[i] > W || used_b[bin] + bytes[i] > kLdsCap1D)) ++bin;
         if (bin == used_w.size()) {
             used_w.push_back(0);
             used_b.push_back(0);
-            segs.resize(segs.size() + W, Seg1D{-1, 0, 0, 0});
+            segs.resize(segs.size() + W, Seg1D{-1, 0, 0, 0, 4, 0});
         }
-        for (int w = 0; w < nw[i]; ++w) segs[bin * W + used_w[bin] + w] = Seg1D{i, used_w[bin], nw[i], used_b[bin]};
+        for (int w = 0; w < nw[i]; ++w) segs[bin * W + used_w[bin] + w] = Seg1D{i, used_w[bin], nw[i], used_b[bin], 4, 0};
         used_w[bin] += nw[i];
         used_b[bin] += bytes[i];
     }
@@ -480,9 +489,7 @@ static const char *pack_1d(const std::vector<Inst1D> &tab, int block, int32_t es
     // Between one and two workgroups per CU: workgroup p and p + C (C CUs)
     // are dispatched to the same CU, so the order pairs loads.  The heaviest
     // workgroups (work ~ cells x stages per step) run alone, and the others
-    // go in pairs of a heavier with a lighter one.  Measured on the
-    // 1000-rod batch of log-uniform lengths (64..4096, FE and PC): 2.03-2.10
-    // against 2.16-2.17 us per step in packing order.
+    // go in pairs of a heavier with a lighter one.
     if (n_blocks > cus && n_blocks <= 2 * cus) {
         std::vector<int64_t> wt(n_blocks, 0);
         for (int b = 0; b < n_blocks; ++b)
@@ -518,6 +525,155 @@ static int device_cus()
         return 256;
     }
     return cus;
+}
+
+// Shape of an explicit batch on the wave kernels (she_step_1d.hpp).
+//
+// Instances of up to 256 cells: one workgroup each, wave 0 advancing the state
+// with 1, 2 or 4 cells per lane and the others drawing the numbers ahead.
+//
+// Longer ones (or block_threads = 64): whole waves with 4 cells per lane, 62
+// units beside the two halo lanes (one more at a Dirichlet wall; one less on a
+// periodic rod whose last unit is not full).  Where 16 waves would not hold the
+// instance, some of its middle waves take 8 cells per lane, and where that does
+// not either, all take 16.
+static void plan_rods(she_handle *h, int block_threads)
+{
+    const int cus = device_cus();
+    const int32_t es = static_cast<int32_t>(h->esz);
+    h->rods = true;
+    if (h->nmax <= 256 && block_threads != 64) {
+        h->rod_cpl = h->nmax <= 64 ? 1 : (h->nmax <= 128 ? 2 : 4);
+        int nf = 0;
+        for (const Inst1D &t : h->tab) nf = std::max(nf, t.bc == SHE_DIRICHLET ? t.n + 1 : t.n);
+        h->rod_zrow = (nf + 3) & ~3;
+        int waves = block_threads > 0 ? std::min(8, block_threads / 64) : (h->prec == SHE_F32 ? 4 : 8);
+        if (block_threads == 0 && h->n_inst > 2 * cus) waves = 4;
+        h->rod_block = 64 * waves;
+        // chunk length: as many steps as the LDS allows beside the batch's other
+        // workgroups of the CU
+        const size_t cap = h->n_inst > cus ? 36 * 1024 : 60 * 1024;
+        for (int K = 32;; K /= 2) {
+            const int slots = h->mask ? (K + h->every - 1) / h->every : 0;
+            const size_t b = 16 + static_cast<size_t>(es) * (2 * static_cast<size_t>(K) * h->rod_zrow + 64 * h->rod_cpl + 4 +
+                                                             2 * static_cast<size_t>(slots) * 64 * h->rod_cpl);
+            if (b <= cap || K == 2) {
+                h->rod_ahead = K;
+                h->rod_slots = slots;
+                h->smem1d = b;
+                break;
+            }
+        }
+        h->blocks1d = h->n_inst;
+        h->segs_host.assign(1, Seg1D{0, 0, 1, 0, h->rod_cpl, 0});
+        return;
+    }
+    const int n_inst = h->n_inst;
+    std::vector<int> nw(n_inst), nbig(n_inst, 0), idx(n_inst);
+    auto waves_of = [&](const Inst1D &t, int c) {
+        const bool dirichlet = t.bc == SHE_DIRICHLET;
+        const int units = ((dirichlet ? t.n + 1 : t.n) + c - 1) / c;
+        if (units <= 64) return 1;
+        const int cap = !dirichlet && t.n % c != 0 ? 61 : 62;
+        return ((dirichlet ? units - 2 : units) + cap - 1) / cap;
+    };
+    int cmax = 4, wmax = 1;
+    for (int i = 0; i < n_inst; ++i) {
+        nw[i] = waves_of(h->tab[i], 4);
+        if (nw[i] > 16) {
+            const int blocks = ((h->tab[i].bc == SHE_DIRICHLET ? h->tab[i].n + 1 : h->tab[i].n) + 3) / 4;
+            nw[i] = 16;
+            nbig[i] = 1;
+            while (nbig[i] < 14 && blocks - 124 * nbig[i] > 60 * (16 - nbig[i])) ++nbig[i];
+            if (blocks - 124 * nbig[i] > 60 * (16 - nbig[i])) cmax = 16;
+            cmax = std::max(cmax, 8);
+        }
+    }
+    int64_t total = 0;
+    for (int i = 0; i < n_inst; ++i) {
+        if (cmax == 16) {
+            nw[i] = waves_of(h->tab[i], 16);
+            nbig[i] = 0;
+        }
+        wmax = std::max(wmax, nw[i]);
+        total += nw[i];
+        idx[i] = i;
+    }
+    int W = std::max(1, block_threads / 64);
+    if (block_threads == 0) W = 4;
+    while (W < wmax) W *= 2;
+    // work of a wave per step: a PC step takes 4/3 of an FE step (the numbers are
+    // drawn once; 640 against 480 cycles of a SIMD with 4 cells per lane)
+    auto cost = [&](int i) { return static_cast<int64_t>(h->tab[i].scheme == SHE_HEUN ? 4 : 3); };
+    auto all = [&](int i) { return cost(i) * (nw[i] + nbig[i]); };
+    std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return all(a) > all(b); });
+    // Workgroups are dealt to the CUs in turn (workgroup p and p + CUs share
+    // one), the waves of a workgroup to the SIMDs in turn, the next workgroup of
+    // the CU starting one SIMD further.  Largest instance first, each goes to
+    // the CU with the least work that has a workgroup with room, its waves to
+    // the free places on the SIMDs with the least.
+    struct Bin {
+        int used = 0;
+        int32_t lds = 0;
+        std::vector<Seg1D> seg;
+    };
+    std::vector<Bin> bins;
+    const int rounds0 = static_cast<int>((total + static_cast<int64_t>(W) * cus - 1) / (static_cast<int64_t>(W) * cus));
+    for (int rounds = std::max(1, rounds0);; ++rounds) {
+        const int ncu = std::min(cus, n_inst), nb = ncu * rounds;
+        bins.assign(nb, Bin{});
+        for (Bin &b : bins) b.seg.assign(W, Seg1D{-1, 0, 0, 0, 4, 0});
+        std::vector<std::array<int64_t, 4>> simd(ncu, std::array<int64_t, 4>{});
+        // CUs by load, a heap of (load, CU); a CU without room is set aside
+        std::priority_queue<std::pair<int64_t, int>, std::vector<std::pair<int64_t, int>>, std::greater<>> order;
+        for (int c = 0; c < ncu; ++c) order.push({0, c});
+        bool ok = true;
+        std::vector<std::pair<int64_t, int>> aside;
+        for (int i : idx) {
+            int best = -1, cu = -1;
+            int64_t load = 0;
+            while (best < 0 && !order.empty()) {
+                load = order.top().first;
+                cu = order.top().second;
+                order.pop();
+                for (int q = 0; q < rounds && best < 0; ++q)
+                    if (bins[cu + q * ncu].used + nw[i] <= W) best = cu + q * ncu;
+                if (best < 0) aside.push_back({load, cu});
+            }
+            if (best < 0) {
+                ok = false;
+                break;
+            }
+            Bin &b = bins[best];
+            const int small = nw[i] - nbig[i], lo = small / 2;
+            for (int w = 0; w < nw[i]; ++w) {
+                const bool big = nbig[i] > 0 && w >= lo && w < lo + nbig[i];
+                int pos = -1;
+                for (int p = 0; p < W; ++p)
+                    if (b.seg[p].inst < 0 && (pos < 0 || simd[cu][(p + best / ncu) & 3] < simd[cu][(pos + best / ncu) & 3]))
+                        pos = p;
+                b.seg[pos] = Seg1D{i, pos - w, nw[i], b.lds, cmax == 16 ? 16 : (big ? 8 : 4), nbig[i]};
+                simd[cu][(pos + best / ncu) & 3] += cost(i) * (big ? 2 : 1);
+            }
+            b.used += nw[i];
+            b.lds += (rod_lds(nw[i], cmax, es) + 15) & ~15;
+            order.push({load + all(i), cu});
+            for (auto &x : aside) order.push(x);
+            aside.clear();
+        }
+        if (ok) break;
+    }
+    h->segs_host.clear();
+    size_t smem = 0;
+    for (const Bin &b : bins) {
+        h->segs_host.insert(h->segs_host.end(), b.seg.begin(), b.seg.end());
+        smem = std::max(smem, static_cast<size_t>(b.lds));
+    }
+    h->rod_block = 64 * W;
+    h->rod_cpl = cmax;
+    h->rod_ahead = 0;
+    h->blocks1d = static_cast<int>(bins.size());
+    h->smem1d = smem;
 }
 
 static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
@@ -644,19 +800,20 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
     h->c_elems = co;
     h->hist_elems = ho;
     h->tc_elems = to;
-    // Launch shape: threads per workgroup and Philox blocks per thread.  Auto:
-    // the smallest shape whose workgroup holds the largest instance with at
-    // most one block per thread up to 512 threads (64 x 1, 64 x 2, 256 x 1,
-    // 512 x 1), then 512 threads with 2 or 4 blocks each.
-    bool heat_only = true;
+    // Launch shape of the barrier kernel (implicit batches; its limits hold for
+    // all): threads per workgroup and Philox blocks per thread.  Auto: the
+    // smallest shape whose workgroup holds the largest instance with at most one
+    // block per thread up to 512 threads (64 x 1, 64 x 2, 256 x 1, 512 x 1), then
+    // 512 threads with 2 or 4 blocks each.
+    // instantaneous noise and one equation throughout: a kernel for that face
+    // path alone (mode 3, 4 or 5)
+    bool one_kind = true;
     for (int i = 0; i < h->n_inst; ++i)
-        heat_only = heat_only && h->tab[i].eq == SHE_HEAT && h->tab[i].noise == SHE_NOISE_INSTANT;
-    const int mode = !h->pcr_host.empty() ? 2 : (h->varc ? 1 : (heat_only ? 3 : 0));
+        one_kind = one_kind && h->tab[i].eq == h->tab[0].eq && h->tab[i].noise == SHE_NOISE_INSTANT;
+    const int mode = !h->pcr_host.empty() ? 2 : (h->varc ? 1 : (one_kind ? 3 + h->tab[0].eq : 0));
     h->mode1d = mode;
-    // A uniform explicit FP32 batch of heat instances with instantaneous noise
-    // and no statistics whose largest instance has 513..1024 blocks may take
-    // 1024 threads with one block each (a kernel compiled for that face path
-    // only, 38 VGPRs, two workgroups per CU).
+    // 1024 threads are accepted for explicit FP32 batches of heat instances with
+    // instantaneous noise and no statistics
     const bool wide_ok = h->prec == SHE_F32 && mode == 3 && h->mask == 0;
     int block = cfg->block_threads, maxg = 1;
     if (block == 0) {
@@ -665,17 +822,6 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
         else if (nfg_max <= 256) block = 256;
         else if (nfg_max <= 512) block = 512;
         else block = 512, maxg = nfg_max <= 1024 ? 2 : 4;
-        if (wide_ok && nfg_max > 512 && nfg_max <= 1024) {
-            // 1024 x 1 halves the largest instances' chain, but its workgroups
-            // are resident together only up to one per CU (measured: a c4-like
-            // batch of 282 such workgroups ran slower than 471 of 512 x 2)
-            std::vector<Seg1D> sg;
-            int nb = 0;
-            size_t sm = 0;
-            const int cus = device_cus();
-            if (!pack_1d(h->tab, 1024, static_cast<int32_t>(es), mode, sg, nb, sm, cus) && nb <= cus)
-                block = 1024, maxg = 1;
-        }
     } else {
         if (block != 64 && block != 256 && block != 512 && !(block == 1024 && wide_ok))
             return fail(nullptr, SHE_EINVAL,
@@ -688,10 +834,15 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
         return fail(nullptr, SHE_EUNSUPPORTED, "1D instance too large for the resident kernel at this block size");
     h->block1d = block;
     h->maxg = maxg;
-    {
+    if (mode == 2) {
         const char *why =
-            pack_1d(h->tab, block, static_cast<int32_t>(es), mode, h->segs_host, h->blocks1d, h->smem1d, device_cus());
+            pack_1d(h->tab, block, static_cast<int32_t>(es), h->segs_host, h->blocks1d, h->smem1d, device_cus());
         if (why) return fail(nullptr, SHE_EUNSUPPORTED, why);
+    } else {
+        for (const Inst1D &t : h->tab)
+            if (seg_lds(t.n, t.bc == SHE_DIRICHLET ? t.n + 1 : t.n, static_cast<int32_t>(es), mode).total > kLdsCap1D)
+                return fail(nullptr, SHE_EUNSUPPORTED, kLdsWhy1D);
+        plan_rods(h, cfg->block_threads);
     }
 
     plan.add(reinterpret_cast<void **>(&h->d_tab), sizeof(Inst1D) * h->n_inst);
@@ -1314,10 +1465,15 @@ static she_status advance(she_handle *h, int64_t nsteps, bool sampling)
                     fold = true;
                 }
             }
-            SHE_HIP(h, launch_step1d(h->prec, h->block1d, h->maxg, stats, h->mode1d, h->blocks1d, h->smem1d, s,
-                                     h->d_tab, h->d_segs, h->d_pool, h->d_coef, h->d_pcr, h->steps,
-                                     static_cast<int32_t>(k),
-                                     h->burn_in, h->every, h->mask, st));
+            if (h->rods)
+                SHE_HIP(h, launch_rods(Launch1D{h->prec, h->mode1d, stats, h->blocks1d, h->rod_block, h->smem1d, s,
+                                                h->d_tab, h->d_segs, h->d_pool, h->d_coef, h->steps,
+                                                static_cast<int32_t>(k), h->burn_in, h->every, h->mask, st, h->rod_cpl,
+                                                h->rod_ahead, h->rod_zrow, h->rod_slots}));
+            else
+                SHE_HIP(h, launch_step1d(h->prec, h->block1d, h->maxg, stats, h->blocks1d, h->smem1d, s, h->d_tab,
+                                         h->d_segs, h->d_pool, h->d_coef, h->d_pcr, h->steps,
+                                         static_cast<int32_t>(k), h->burn_in, h->every, h->mask, st));
             const int64_t cnt = stats ? sampled_by(h->steps + k) - sampled_by(h->steps) : 0;
             if (tc && cnt > 0)
                 SHE_HIP(h, launch_tcorr1d(h->prec, h->n_inst, h->nmax, h->tc_lags, s, h->d_tab, h->d_hist,

@@ -191,7 +191,18 @@ struct Seg1D {
     int32_t w0;
     int32_t nw;
     int32_t lds;
+    int32_t cpl;        // explicit batches: cells per lane of this wave (4, 8 or 16)
+    int32_t nbig;       // explicit batches: waves of the instance with 8 cells per lane
+                        // beside others with 4 (0: all alike)
 };
+
+// LDS bytes of one instance of an explicit batch served by nw waves: meeting
+// flags, the wave sums of a sample and the edge exchange (rod_waves).
+constexpr int rod_edge(int cpl) { return cpl > 8 ? 2 * cpl : 8; }  // two units of a wave at the ends
+inline int32_t rod_lds(int32_t nw, int32_t cpl, int32_t es)
+{
+    return nw == 1 ? 128 : 128 + 2 * 3 * 16 * 8 + 2 * nw * 2 * rod_edge(cpl) * es;
+}
 
 // LDS region of one 1D instance (byte offsets, 16-byte aligned parts):
 // exchange arrays [2 buffers][first value, last value, face-0 number][nfg
@@ -286,16 +297,39 @@ __device__ __forceinline__ void resolve_step(const StepArg &a, int64_t &step, in
 namespace she {
 
 // ---- launchers (defined next to their kernels) ----
-// mode 0: uniform explicit batch; 3: the same with every instance a heat
-// equation with instantaneous noise (only that face path compiled);
-// 1: some instance has material coefficients
-// (k_off >= 0 in `coef`; r_f, s_f, w_i of every instance staged in LDS);
-// 2: some instance is implicit (reduction factors in `pcr`; mode 1 included).
-// segs: n_blocks * block / 64 wave entries.
-hipError_t launch_step1d(int prec, int block, int maxg, bool stats, int mode, int n_blocks, size_t smem,
-                         hipStream_t s, const Inst1D *tab, const Seg1D *segs, void *pool,
-                         const void *coef, const double *pcr, int64_t step0, int32_t nsteps, int64_t burn_in,
-                         int32_t every, uint32_t mask, Stats1D st);
+// One launch of an explicit 1D batch.  mode 0: uniform; 3, 4, 5: uniform with
+// instantaneous noise and of one equation; 1: some instance has material
+// coefficients (k_off >= 0 in `coef`).
+// ahead = 0: k_rods, segs holding n_blocks * block / 64 wave entries, cpl the
+// largest cells per lane (4, 8 or 16); ahead > 0: k_rods_ahead, one block per
+// instance with cpl (1, 2 or 4) cells per lane, chunks of `ahead` steps, rows of
+// zrow numbers and `slots` sampled states per chunk in LDS.
+struct Launch1D {
+    int prec;
+    int mode;
+    bool stats;
+    int n_blocks, block;
+    size_t smem;
+    hipStream_t s;
+    const Inst1D *tab;
+    const Seg1D *segs;
+    void *pool;
+    const void *coef;
+    int64_t step0;
+    int32_t nsteps;
+    int64_t burn_in;
+    int32_t every;
+    uint32_t mask;
+    Stats1D st;
+    int cpl;
+    int32_t ahead, zrow, slots;
+};
+hipError_t launch_rods(const Launch1D &a);
+// Batches with an implicit instance: reduction factors in `pcr`; r_f, s_f, w_i
+// of every instance staged in LDS.  segs: n_blocks * block / 64 wave entries.
+hipError_t launch_step1d(int prec, int block, int maxg, bool stats, int n_blocks, size_t smem, hipStream_t s,
+                         const Inst1D *tab, const Seg1D *segs, void *pool, const void *coef, const double *pcr,
+                         int64_t step0, int32_t nsteps, int64_t burn_in, int32_t every, uint32_t mask, Stats1D st);
 // Initial state of 1D instances: steady profile + init_sd * N(tag 1, step 0, face = cell).
 hipError_t launch_init1d(int prec, int n_inst, int nmax, hipStream_t s, const Inst1D *tab,
                          const double *init_sd, void *pool);

@@ -1,11 +1,7 @@
-// 1D step kernel: one workgroup owns one instance of a (possibly ragged) batch
-// and keeps its whole state in LDS for a chunk of steps.
-//
-// Scheme (Garcia et al., Sec. 3): face flux F_f = r (U_f - U_{f-1}) + w sigma A N_f
-// through the low face f of cell f, update U_i += F_{i+1} - F_i (FE), or the
-// predictor-corrector U = (U + U* + Delta(U*; same N)) / 2 (PC).  Dirichlet
-// walls: F_0 = 2 r (U_0 - U_L) + sqrt(2) sigma A(U_L) N_0 and mirrored at the
-// right wall (ghost stencil U_1 - 3U_0 + 2U_L of the Dirichlet paragraph).
+// 1D batches: the step kernel of batches with implicit instances, the time
+// correlation, initial state, finalisation, batch means and the verification
+// kernels.  Explicit batches step in she_step_1d.hpp, whose comment states the
+// scheme.
 //
 // Implicit schemes (backward Euler theta = 1, Crank-Nicolson theta = 1/2;
 // the implicit-scheme exercise, Sec. 6): the flux pass weights the
@@ -14,56 +10,20 @@
 // host precomputes in FP64 the factors of parallel cyclic reduction (log2 N
 // levels of d_i -= k1 d_(i-s) + k2 d_(i+s), then d_i / b_i) and, for periodic
 // rods, the Sherman-Morrison vector of the cyclic part.  The reduction runs in
-// FP64 for either state type (an FP64 array over the flux and scratch LDS),
-// so only the final state is rounded: rounded factors would bias the
-// conserved sum a little every step.
-//
-// Material varying along the rod (composite-rod exercise, Sec. 6; VARC): the
-// conservative form with a conductance r_f and noise factor s_f per face and
-// a factor w_i = (rho c_V)_ref / (rho c_V)_i per cell, U_i += w_i (F_(i+1) -
-// F_i), staged in LDS next to the state.  Uniform instances of such a batch
-// get uniform arrays (bit-identical to the uniform kernel).
-//
-// Work split: an instance is served by a run of whole waves of a workgroup
-// (small instances share a workgroup, each with its own waves and LDS
-// region); its thread t owns Philox blocks g = t, t + TS, ... (TS threads);
-// block g holds faces 4g..4g+3, which are the low faces of cells 4g..4g+3,
-// so one Philox call and two Box-Muller pairs serve four cells and PC re-uses
-// the numbers from registers.  The state stays in registers for the whole
-// launch; one LDS exchange and one barrier per FE step, two per PC step.
+// FP64 for either state type (an FP64 array in LDS), so only the final state
+// is rounded: rounded factors would bias the conserved sum a little every step.
 //
 // Statistics on sample steps: per-cell FP64 sums of dU and dU^2 kept in
-// registers for the whole launch, spatial sums reduced over the workgroup,
-// and (optionally) the shifted state written as one row of a 256-row X block;
+// registers for the whole launch, spatial sums reduced over the instance, and
+// (optionally) the shifted state written as one row of a 256-row X block;
 // a full block is contracted on the matrix cores, C += X^T X, with
 // v_mfma_f32_16x16x4f32 (FP32 state) or v_mfma_f64_16x16x4f64 (FP64 state),
 // and added to the FP64 N x N sum.  For the time correlation each sample row
 // also goes to a per-instance history ring; after the launch, k_tcorr adds the
 // lag products of the new rows (one thread per cell and lag, FP64).
-#include <type_traits>
-
-#include "she_internal.hpp"
-#include "she_rng.hpp"
-#include "she_wave.hpp"
+#include "she_step_1d.hpp"
 
 namespace she {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-// Noise amplitude of a face with value v: v (SHE), sqrt(v) (DK),
-// sqrt(v (1 - v)) (Burgers); a negative radicand is clamped and counted.
-template <typename T>
-__device__ __forceinline__ T face_amp(int eq, T v, uint32_t &clamps)
-{
-    if (eq == 0) return v;
-    const T q = eq == 2 ? v * (T(1) - v) : v;
-    if (q < T(0)) {
-        ++clamps;
-        return T(0);
-    }
-    return amp_sqrt(q);
-}
 
 // Value of the last of the first `m` (1..4) entries, chosen among values
 // (a select of array elements as lvalues would become an address select and
@@ -74,73 +34,8 @@ __device__ __forceinline__ T last_of(int m, T a0, T a1, T a2, T a3)
     return m >= 4 ? a3 : (m == 3 ? a2 : (m == 2 ? a1 : a0));
 }
 
-__device__ __forceinline__ f32x4 mfma16x16x4(float a, float b, f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ f64x4 mfma16x16x4(double a, double b, f64x4 c)
-{
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
-// C[N x N] += X^T X for a full block X[256 x N] (row = snapshot).  Tiles of
-// 16 x 16 over the upper triangle are spread over the instance's waves
-// (wave = 0 .. nwave-1); each lane accumulates four outputs of its tile over
-// K = 256 in the matrix-core accumulator type and adds them to the FP64 sum
-// (both triangles).
-// Operand layout of the 16x16x4 instructions: lane l supplies A[l%16][l/16]
-// and B[l/16][l%16]; output element v of lane l is D[4(l/16)+v][l%16] for
-// the FP32 form and D[(l/16)+4v][l%16] for the FP64 form.
-template <typename T>
-__device__ void xtx_block(const T *__restrict__ X, double *__restrict__ Cm, int N, int wave, int nwave)
-{
-    using acc_t = typename std::conditional<std::is_same<T, float>::value, f32x4, f64x4>::type;
-    const int lane = threadIdx.x & 63;
-    const int nt = (N + 15) >> 4;
-    const int ntiles = nt * (nt + 1) / 2;
-    for (int t = wave; t < ntiles; t += nwave) {
-        int ti = 0, rem = t;
-        while (rem >= nt - ti) {
-            rem -= nt - ti;
-            ++ti;
-        }
-        const int tj = ti + rem;
-        const int i = 16 * ti + (lane & 15), j = 16 * tj + (lane & 15);
-        acc_t acc = {0, 0, 0, 0};
-        // eight K-steps of operands are loaded before their eight products, so
-        // the loads overlap instead of each product waiting for its own
-        constexpr int kB = 8;
-        for (int k0 = 0; k0 < kCorrBlock; k0 += 4 * kB) {
-            T a[kB], b[kB];
-#pragma unroll
-            for (int q = 0; q < kB; ++q) {
-                const int k = k0 + 4 * q + (lane >> 4);
-                a[q] = i < N ? X[(int64_t)k * N + i] : T(0);
-                b[q] = j < N ? X[(int64_t)k * N + j] : T(0);
-            }
-#pragma unroll
-            for (int q = 0; q < kB; ++q) acc = mfma16x16x4(a[q], b[q], acc);
-        }
-        const int col = 16 * tj + (lane & 15);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            // output rows: FP32 form 4(l/16)+v, FP64 form (l/16)+4v (measured on gfx950)
-            const int row = 16 * ti + (std::is_same<T, float>::value ? 4 * (lane >> 4) + v : (lane >> 4) + 4 * v);
-            if (row < N && col < N) {
-                const double val = static_cast<double>(acc[v]);
-                Cm[(int64_t)row * N + col] += val;
-                if (ti != tj) Cm[(int64_t)col * N + row] += val;
-            }
-        }
-    }
-}
-
-// MODE 0: uniform explicit batch; 3: the same with every instance a heat
-// equation with instantaneous noise (only that face path is compiled: fewer
-// registers and a shorter loop); 1: material coefficients (VARC); 2: some
-// instance is implicit (material arrays available as well).  Each mode is
-// compiled separately so that a batch pays only for the paths it uses.
+// Batches with an implicit instance (explicit and composite ones may be among
+// them; explicit batches run the wave kernels of she_step_1d.hpp).
 //
 // Thread t of an instance's waves owns Philox blocks g = t + s TS (s < MAXG,
 // TS the instance's thread count): the faces 4g..4g+3 and the cells 4g..4g+3,
@@ -152,14 +47,12 @@ __device__ void xtx_block(const T *__restrict__ X, double *__restrict__ Cm, int 
 // as well (same inputs, same code, so the two agree bit for bit and the sum
 // is conserved).  The exchange arrays alternate between two buffers, so one
 // barrier per stage suffices.
-template <typename T, int BLOCK, int MAXG, bool STATS, int MODE>
+template <typename T, int BLOCK, int MAXG, bool STATS>
 __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, const Seg1D *__restrict__ segs,
                                             T *__restrict__ pool, const T *__restrict__ coef,
                                             const double *__restrict__ pcr, int64_t step0, int32_t nsteps,
                                             int64_t burn_in, int32_t every, uint32_t mask, Stats1D st)
 {
-    constexpr bool VARC = MODE == 1 || MODE == 2;
-    constexpr bool HEAT_ONLY = MODE == 3;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const Seg1D seg = segs[static_cast<int64_t>(blockIdx.x) * (BLOCK / 64) + wave];
@@ -177,7 +70,7 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
     const int TS = 64 * seg.nw;
     const int t = static_cast<int>(threadIdx.x) - 64 * seg.w0;
     const int lw = wave - seg.w0;
-    const SegLds lay = seg_lds(N, nf, static_cast<int32_t>(sizeof(T)), MODE);
+    const SegLds lay = seg_lds(N, nf, static_cast<int32_t>(sizeof(T)), 2);
     unsigned char *base = smem_raw + seg.lds;
     T *xch = reinterpret_cast<T *>(base + lay.xch);
     double *red = reinterpret_cast<double *>(base + lay.red);  // [3][16] wave sums of a sample
@@ -203,28 +96,26 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
             const int i = 4 * (t + s * TS) + l;
             u[s][l] = i < N ? gU[i] : T(0);
         }
-    if constexpr (VARC) {
-        if (d.k_off >= 0) {
-            const T *k = coef + d.k_off;
-            for (int f = t; f < nf; f += TS) {
-                Rf[f] = k[f];
-                Sf[f] = k[nf + f];
-            }
-            for (int i = t; i < N; i += TS) Wc[i] = k[2 * nf + i];
-            if (!dir && t == 0) {
-                Rf[N] = k[0];
-                Sf[N] = k[nf];
-            }
-        } else {
-            for (int f = t; f < nf; f += TS) {
-                Rf[f] = r;
-                Sf[f] = (dir && (f == 0 || f == N)) ? sgw : sg;
-            }
-            for (int i = t; i < N; i += TS) Wc[i] = T(1);
-            if (!dir && t == 0) {
-                Rf[N] = r;
-                Sf[N] = sg;
-            }
+    if (d.k_off >= 0) {
+        const T *k = coef + d.k_off;
+        for (int f = t; f < nf; f += TS) {
+            Rf[f] = k[f];
+            Sf[f] = k[nf + f];
+        }
+        for (int i = t; i < N; i += TS) Wc[i] = k[2 * nf + i];
+        if (!dir && t == 0) {
+            Rf[N] = k[0];
+            Sf[N] = k[nf];
+        }
+    } else {
+        for (int f = t; f < nf; f += TS) {
+            Rf[f] = r;
+            Sf[f] = (dir && (f == 0 || f == N)) ? sgw : sg;
+        }
+        for (int i = t; i < N; i += TS) Wc[i] = T(1);
+        if (!dir && t == 0) {
+            Rf[N] = r;
+            Sf[N] = sg;
         }
     }
 
@@ -268,9 +159,8 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
     __syncthreads();
 
     // implicit schemes: weight of the state-dependent deterministic flux
-    const bool impl = MODE == 2 && d.scheme >= 2;
+    const bool impl = d.scheme >= 2;
     const T ex = static_cast<T>(impl ? 1.0 - d.theta : 1.0);
-    const T rex = r * ex;
     // face kinds: 0 heat with instantaneous noise; 1 deterministic or no
     // noise (any equation); 2 Dean-Kawasaki; 3 Burgers (both instantaneous)
     const int kind = noise != 0 ? 1 : (eq == 0 ? 0 : eq + 1);
@@ -333,8 +223,8 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
 #pragma unroll
                 for (int l = 0; l < 5; ++l) {
                     const int f = 4 * g + l;
-                    const T rf = VARC ? Rf[f] * ex : rex;
-                    const T sf = VARC ? Sf[f] : sg;
+                    const T rf = Rf[f] * ex;
+                    const T sf = Sf[f];
                     const T df = hi[l] - lo[l];
                     const T cf = T(0.5) * (lo[l] + hi[l]);
                     // clamps are counted on the faces this block owns
@@ -367,16 +257,16 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
                     // walls: F_0 = 2 r (U_0 - U_L) + sqrt 2 sigma A(U_L) N_0, mirrored at
                     // face N (the state term weighted by 1 - theta in implicit schemes)
                     if (g == 0) {
-                        const T rw = VARC ? Rf[0] : r;
-                        const T sw = VARC ? Sf[0] : sgw;
+                        const T rw = Rf[0];
+                        const T sw = Sf[0];
                         const T dwl = fma(-nu * uL, T(1) - uL, T(2) * rw * (ex * V[s][0] - uL));
                         F[0] = noise != 2 ? fma(sw * amp_uL, zz[0], dwl) : dwl;
                     }
                     if (!inner) {
                         const int m = nc < 4 ? nc : 4;
                         const T vl = last_of<T>(m, V[s][0], V[s][1], V[s][2], V[s][3]);
-                        const T rw = VARC ? Rf[N] : r;
-                        const T sw = VARC ? Sf[N] : sgw;
+                        const T rw = Rf[N];
+                        const T sw = Sf[N];
                         const T dwr = fma(-nu * uR, T(1) - uR, T(2) * rw * (uR - ex * vl));
                         const T w = noise != 2 ? fma(sw * amp_uR, rnz[s], dwr) : dwr;
 #pragma unroll
@@ -385,18 +275,14 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
                     }
                 }
 #pragma unroll
-                for (int l = 0; l < 4; ++l) dv[s][l] = VARC ? Wc[4 * g + l] * (F[l + 1] - F[l]) : F[l + 1] - F[l];
+                for (int l = 0; l < 4; ++l) dv[s][l] = Wc[4 * g + l] * (F[l + 1] - F[l]);
             }
         };
-        if constexpr (HEAT_ONLY) {
-            faces(std::integral_constant<int, 0>{});
-        } else {
-            switch (kind) {
-            case 0: faces(std::integral_constant<int, 0>{}); break;
-            case 1: faces(std::integral_constant<int, 1>{}); break;
-            case 2: faces(std::integral_constant<int, 2>{}); break;
-            default: faces(std::integral_constant<int, 3>{}); break;
-            }
+        switch (kind) {
+        case 0: faces(std::integral_constant<int, 0>{}); break;
+        case 1: faces(std::integral_constant<int, 1>{}); break;
+        case 2: faces(std::integral_constant<int, 2>{}); break;
+        default: faces(std::integral_constant<int, 3>{}); break;
         }
     };
 
@@ -420,7 +306,7 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
 #pragma unroll
         for (int s = 0; s < MAXG; ++s) rnz[s] = T(0);
         stage(u, z, rnz, dv, true);
-        if (MODE == 2 && impl) {
+        if (impl) {
             // right-hand side in FP64, then M U' = rhs by parallel cyclic
             // reduction in the FP64 LDS array (same cells per thread)
             double x[MAXG][4];
@@ -654,27 +540,13 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
     }
 }
 
-template <typename T, int BLOCK, int MAXG, bool STATS, int MODE>
+template <typename T, int BLOCK, int MAXG, bool STATS>
 __global__ void __launch_bounds__(BLOCK)
     k_step1d(const Inst1D *__restrict__ tab, const Seg1D *__restrict__ segs, T *__restrict__ pool,
              const T *__restrict__ coef, const double *__restrict__ pcr, int64_t step0, int32_t nsteps,
              int64_t burn_in, int32_t every, uint32_t mask, Stats1D st)
 {
-    step1d_body<T, BLOCK, MAXG, STATS, MODE>(tab, segs, pool, coef, pcr, step0, nsteps, burn_in, every, mask, st);
-}
-
-// 1024 threads with one Philox block each, for a uniform explicit FP32 batch
-// of heat instances with instantaneous noise and no statistics (only that
-// face path is compiled), held to 64 VGPRs so that two workgroups (32 waves) fit on a
-// CU: a packed batch of instances up to 4096 Philox blocks stays resident in
-// one round while its largest instances keep one block per thread.
-template <typename T>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8)))
-    k_step1d_wide(const Inst1D *__restrict__ tab, const Seg1D *__restrict__ segs, T *__restrict__ pool,
-                  const T *__restrict__ coef, const double *__restrict__ pcr, int64_t step0, int32_t nsteps,
-                  int64_t burn_in, int32_t every, uint32_t mask, Stats1D st)
-{
-    step1d_body<T, 1024, 1, false, 3>(tab, segs, pool, coef, pcr, step0, nsteps, burn_in, every, mask, st);
+    step1d_body<T, BLOCK, MAXG, STATS>(tab, segs, pool, coef, pcr, step0, nsteps, burn_in, every, mask, st);
 }
 
 // ------------------------------------------------------------------ time correlation
@@ -1019,66 +891,81 @@ struct Step1DLaunch {
     Stats1D st;
 };
 
-template <typename T, int BLOCK, int MAXG, bool STATS, int MODE>
+template <typename T, int BLOCK, int MAXG, bool STATS>
 static hipError_t step1d_k(const Step1DLaunch &a)
 {
-    hipLaunchKernelGGL((k_step1d<T, BLOCK, MAXG, STATS, MODE>), dim3(a.n_blocks), dim3(BLOCK), a.smem, a.s, a.tab,
-                       a.segs, static_cast<T *>(a.pool), static_cast<const T *>(a.coef), a.pcr, a.step0, a.nsteps,
-                       a.burn_in, a.every, a.mask, a.st);
+    hipLaunchKernelGGL((k_step1d<T, BLOCK, MAXG, STATS>), dim3(a.n_blocks), dim3(BLOCK), a.smem, a.s, a.tab, a.segs,
+                       static_cast<T *>(a.pool), static_cast<const T *>(a.coef), a.pcr, a.step0, a.nsteps, a.burn_in,
+                       a.every, a.mask, a.st);
     return hipGetLastError();
 }
 
-template <typename T, int BLOCK, int MAXG, bool STATS>
-static hipError_t step1d_m(int mode, const Step1DLaunch &a)
+template <typename T, int BLOCK, int MAXG>
+static hipError_t step1d_t(bool stats, const Step1DLaunch &a)
 {
-    switch (mode) {
-    case 0: return step1d_k<T, BLOCK, MAXG, STATS, 0>(a);
-    case 1: return step1d_k<T, BLOCK, MAXG, STATS, 1>(a);
-    case 2: return step1d_k<T, BLOCK, MAXG, STATS, 2>(a);
-    case 3: return step1d_k<T, BLOCK, MAXG, STATS, 3>(a);
+    return stats ? step1d_k<T, BLOCK, MAXG, true>(a) : step1d_k<T, BLOCK, MAXG, false>(a);
+}
+
+// Launch shapes (threads per workgroup, Philox blocks per thread) the
+// planner chooses: 64 x {1, 2}, 256 x {1, 2}, 512 x {1, 2, 4}.
+template <typename T>
+static hipError_t step1d_p(int block, int maxg, bool stats, const Step1DLaunch &a)
+{
+    if (block == 64 && maxg == 1) return step1d_t<T, 64, 1>(stats, a);
+    if (block == 64 && maxg == 2) return step1d_t<T, 64, 2>(stats, a);
+    if (block == 256 && maxg == 1) return step1d_t<T, 256, 1>(stats, a);
+    if (block == 256 && maxg == 2) return step1d_t<T, 256, 2>(stats, a);
+    if (block == 512 && maxg == 1) return step1d_t<T, 512, 1>(stats, a);
+    if (block == 512 && maxg == 2) return step1d_t<T, 512, 2>(stats, a);
+    if (block == 512 && maxg == 4) return step1d_t<T, 512, 4>(stats, a);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_step1d(int prec, int block, int maxg, bool stats, int n_blocks, size_t smem, hipStream_t s,
+                         const Inst1D *tab, const Seg1D *segs, void *pool, const void *coef, const double *pcr,
+                         int64_t step0, int32_t nsteps, int64_t burn_in, int32_t every, uint32_t mask, Stats1D st)
+{
+    const Step1DLaunch a{n_blocks, smem, s, tab, segs, pool, coef, pcr, step0, nsteps, burn_in, every, mask, st};
+    return prec == 0 ? step1d_p<float>(block, maxg, stats, a) : step1d_p<double>(block, maxg, stats, a);
+}
+
+// Typed launchers of the explicit batches, instantiated in she_k1d_f*.hip.
+extern template hipError_t rods_t<float, 0, false>(const Launch1D &);
+extern template hipError_t rods_t<float, 0, true>(const Launch1D &);
+extern template hipError_t rods_t<float, 1, false>(const Launch1D &);
+extern template hipError_t rods_t<float, 1, true>(const Launch1D &);
+extern template hipError_t rods_t<float, 3, false>(const Launch1D &);
+extern template hipError_t rods_t<float, 3, true>(const Launch1D &);
+extern template hipError_t rods_t<double, 0, false>(const Launch1D &);
+extern template hipError_t rods_t<double, 0, true>(const Launch1D &);
+extern template hipError_t rods_t<double, 1, false>(const Launch1D &);
+extern template hipError_t rods_t<double, 1, true>(const Launch1D &);
+extern template hipError_t rods_t<double, 3, false>(const Launch1D &);
+extern template hipError_t rods_t<double, 3, true>(const Launch1D &);
+extern template hipError_t rods_t<float, 4, false>(const Launch1D &);
+extern template hipError_t rods_t<float, 4, true>(const Launch1D &);
+extern template hipError_t rods_t<float, 5, false>(const Launch1D &);
+extern template hipError_t rods_t<float, 5, true>(const Launch1D &);
+extern template hipError_t rods_t<double, 4, false>(const Launch1D &);
+extern template hipError_t rods_t<double, 4, true>(const Launch1D &);
+extern template hipError_t rods_t<double, 5, false>(const Launch1D &);
+extern template hipError_t rods_t<double, 5, true>(const Launch1D &);
+
+template <typename T>
+static hipError_t rods_p(const Launch1D &a)
+{
+    const bool ahead = a.ahead > 0;
+    switch (a.mode) {
+    case 0: return ahead ? rods_t<T, 0, true>(a) : rods_t<T, 0, false>(a);
+    case 1: return ahead ? rods_t<T, 1, true>(a) : rods_t<T, 1, false>(a);
+    case 3: return ahead ? rods_t<T, 3, true>(a) : rods_t<T, 3, false>(a);
+    case 4: return ahead ? rods_t<T, 4, true>(a) : rods_t<T, 4, false>(a);
+    case 5: return ahead ? rods_t<T, 5, true>(a) : rods_t<T, 5, false>(a);
     default: return hipErrorInvalidValue;
     }
 }
 
-template <typename T, int BLOCK, int MAXG>
-static hipError_t step1d_t(bool stats, int mode, const Step1DLaunch &a)
-{
-    return stats ? step1d_m<T, BLOCK, MAXG, true>(mode, a) : step1d_m<T, BLOCK, MAXG, false>(mode, a);
-}
-
-// Launch shapes (threads per workgroup, Philox blocks per thread) the
-// planner chooses: 64 x {1, 2}, 256 x {1, 2}, 512 x {1, 2, 4}, and 1024 x 1
-// for uniform explicit batches without statistics.
-template <typename T>
-static hipError_t step1d_p(int block, int maxg, bool stats, int mode, const Step1DLaunch &a)
-{
-    if (block == 64 && maxg == 1) return step1d_t<T, 64, 1>(stats, mode, a);
-    if (block == 64 && maxg == 2) return step1d_t<T, 64, 2>(stats, mode, a);
-    if (block == 256 && maxg == 1) return step1d_t<T, 256, 1>(stats, mode, a);
-    if (block == 256 && maxg == 2) return step1d_t<T, 256, 2>(stats, mode, a);
-    if (block == 512 && maxg == 1) return step1d_t<T, 512, 1>(stats, mode, a);
-    if (block == 512 && maxg == 2) return step1d_t<T, 512, 2>(stats, mode, a);
-    if (block == 512 && maxg == 4) return step1d_t<T, 512, 4>(stats, mode, a);
-    if constexpr (std::is_same<T, float>::value) {
-        if (block == 1024 && maxg == 1 && !stats && mode == 3) {
-            hipLaunchKernelGGL((k_step1d_wide<T>), dim3(a.n_blocks), dim3(1024), a.smem, a.s, a.tab, a.segs,
-                               static_cast<T *>(a.pool), static_cast<const T *>(a.coef), a.pcr, a.step0,
-                               a.nsteps, a.burn_in, a.every, a.mask, a.st);
-            return hipGetLastError();
-        }
-    }
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_step1d(int prec, int block, int maxg, bool stats, int mode, int n_blocks, size_t smem,
-                         hipStream_t s, const Inst1D *tab, const Seg1D *segs, void *pool, const void *coef,
-                         const double *pcr, int64_t step0, int32_t nsteps, int64_t burn_in, int32_t every,
-                         uint32_t mask, Stats1D st)
-{
-    const Step1DLaunch a{n_blocks, smem, s, tab, segs, pool, coef, pcr, step0, nsteps, burn_in, every, mask, st};
-    if (prec == 0) return step1d_p<float>(block, maxg, stats, mode, a);
-    return step1d_p<double>(block, maxg, stats, mode, a);
-}
+hipError_t launch_rods(const Launch1D &a) { return a.prec == 0 ? rods_p<float>(a) : rods_p<double>(a); }
 
 hipError_t launch_init1d(int prec, int n_inst, int nmax, hipStream_t s, const Inst1D *tab, const double *init_sd,
                          void *pool)

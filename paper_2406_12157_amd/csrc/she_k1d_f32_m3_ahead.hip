@@ -1,0 +1,6 @@
+// Explicit 1D step kernels: state type float, mode 3, numbers drawn ahead.
+#include "she_step_1d.hpp"
+
+namespace she {
+template hipError_t rods_t<float, 3, true>(const Launch1D &);
+}  // namespace she

@@ -1,0 +1,94 @@
+"""Explicit 1D step kernels at the edges of their work split: cells per lane,
+lanes per wave, waves per instance, halo exchanges, launch chunks and samples."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import gpu_instance, max_rel, oracle_desc
+from paper_2406_12157_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# bars of the state parity tests: FP32 1e-5, FP64 1e-12, relative
+TOL = {0: 1e-5, 1: 1e-12}
+
+
+@pytest.fixture(scope="module")
+def she():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2406_12157_amd import she as mod
+    mod.load()
+    return mod
+
+
+def batch(n, eq=W.HEAT, noise=0):
+    u0, eps, gap, sd = {W.HEAT: (1.0, 1e-2, 0.1, 0.1), W.SPECIES: (100.0, 1.0, 20.0, 10.0),
+                        W.BURGERS: (0.3, 1e-4, 0.0, 4e-3)}[eq]
+    return [W.instance((n,), eq=eq, bc=bc, scheme=scheme, noise=noise, r=0.1, eps=eps, u0=u0, u_left=u0 + gap * bc,
+                       u_right=u0 - gap * bc, init_sd=sd, seed=9, realisation=2 * bc + scheme,
+                       nu=0.3 if eq == W.BURGERS else 0.0)
+            for bc in (0, 1) for scheme in (0, 1) if n > 1 or bc]
+
+
+def check(she, insts, precision, steps, **kw):
+    with she.Handle([gpu_instance(she, i) for i in insts], precision=precision, **kw) as h:
+        init = [h.read_field(q) for q in range(len(insts))]
+        h.step(steps)
+        got = [h.read_field(q) for q in range(len(insts))]
+    for q, inst in enumerate(insts):
+        want = init[q].copy()
+        oracle.advance(oracle_desc(inst, precision), want, 0, steps)
+        err = max_rel(got[q], want)
+        assert err <= TOL[precision], (inst["n"], inst["bc"], inst["scheme"], err)
+    return got
+
+
+# one wave with 1, 2, 4 cells per lane, full and not; two waves from 257 cells
+# on; full waves of 62 units; 16 waves; 8 cells per lane in the middle waves
+# (and FP32: 16 in all)
+SIZES = [1, 2, 3, 63, 64, 65, 127, 128, 129, 253, 255, 256, 257, 495, 497, 503, 505, 992, 993, 2001, 3903, 3904, 3968,
+         3969, 3975, 3976, 4005, 4096, 4223, 4473, 5400]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n", SIZES)
+def test_rod_sizes(she, n, precision):
+    insts = batch(n)
+    got = check(she, insts, precision, 23)
+    if n <= 512:  # every wave its own numbers: the same bits
+        with she.Handle([gpu_instance(she, i) for i in insts], precision=precision, block_threads=64) as h:
+            h.step(23)
+            for q in range(len(insts)):
+                np.testing.assert_array_equal(h.read_field(q), got[q])
+
+
+@pytest.mark.parametrize("n", [7800, 8001, 8191])
+def test_rod_sizes_16_cells_per_lane(she, n):
+    check(she, batch(n), 0, 19)
+
+
+@pytest.mark.parametrize("eq,noise", [(W.SPECIES, 0), (W.BURGERS, 0), (W.HEAT, 1), (W.HEAT, 2)])
+@pytest.mark.parametrize("n", [62, 128, 251, 500, 4100])
+def test_rod_face_kinds(she, n, eq, noise):
+    check(she, batch(n, eq, noise), 0, 21)
+
+
+@pytest.mark.parametrize("n", [61, 128, 254, 700])
+def test_samples_do_not_depend_on_the_launches(she, n):
+    """Samples on every third step, over calls of all lengths (chunk ends,
+    X blocks completed inside a call), against one call; FP64 sums of the same
+    values in the same order per cell."""
+    insts = batch(n)
+    kw = dict(precision=0, sample_every=3, burn_in=4, stats=she.STAT_MOMENTS | she.STAT_CORR)
+    with she.Handle([gpu_instance(she, i) for i in insts], **kw) as a, \
+            she.Handle([gpu_instance(she, i) for i in insts], **kw) as b:
+        a.run(900)
+        for k in (1, 2, 31, 32, 33, 64, 1, 300, 436):
+            b.run(k)
+        for q in range(len(insts)):
+            np.testing.assert_array_equal(a.read_field(q), b.read_field(q))
+            x, y = a.stats(q, corr=True), b.stats(q, corr=True)
+            assert x["n_samples"] == y["n_samples"] == 898 // 3
+            for key in ("mean", "var", "corr"):
+                np.testing.assert_array_equal(x[key], y[key])
