@@ -966,7 +966,20 @@ static she_status plan_nd(she_handle *h, const she_config *cfg, Plan &plan)
         if (ty < 1 || p.ny % ty != 0 || LX * ty > 256)
             return fail(nullptr, SHE_EINVAL, "rows_per_group must divide n[1] with (n[0]/cx)*rows <= 256");
         h->ty = ty;
-        int chunk = cfg->rows_per_block > 0 ? cfg->rows_per_block : 8;
+        // Planes per march: a chunk recomputes the z-faces below its first plane
+        // (about 0.4 plane), so long chunks are cheaper once the chip is full,
+        // and a small grid needs short ones to fill it at all.  Measured, us per
+        // step with chunks of 1, 2, 4, 8: 64^3 FE (256 tile planes) 4.7, 5.6, 7.4,
+        // 11.3; four 64^3 PC (1024) 16.7, 15.9, 17.1, 23.8; 128^3 FE (2048) 11.9,
+        // 9.6, 9.7, 12.3; ten 128x32x156 DK PC (6240) 60.9, 50.1, 46.4, 49.7; four
+        // 128^3 DK (8192) 37.5, 29.0, 25.7, 24.9; 256^3 DK (16384) 60.6, 46.8,
+        // 41.9, 40.7 (12: 43.9).
+        int chunk = cfg->rows_per_block;
+        if (chunk <= 0) {
+            const int64_t planes = static_cast<int64_t>(h->n_inst) * (p.ny / ty) * p.nz;
+            chunk = static_cast<int>(std::max<int64_t>(
+                1, std::min<int64_t>(8, std::max(std::min<int64_t>(4, planes / 512), planes / 1536))));
+        }
         chunk = std::min(chunk, p.nz);
         p.chunk = chunk;
         const int nzc = (p.nz + chunk - 1) / chunk;
