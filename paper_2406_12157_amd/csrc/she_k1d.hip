@@ -632,8 +632,7 @@ __global__ void __launch_bounds__(256)
     double v = ref;
     const double sd = init_sd[inst];
     if (sd > 0.0) {
-        const Normals4<double> nz = block_normals<double>(static_cast<uint32_t>(i >> 2), 0u, ctr_word2(0, 1u),
-                                                          d.realisation, make_key(d.seed));
+        const Normals4<double> nz = init_normals(static_cast<uint32_t>(i >> 2), d.realisation, make_key(d.seed));
         v = ref + sd * nz.z[i & 3];
     }
     pool[d.off + i] = static_cast<T>(v);

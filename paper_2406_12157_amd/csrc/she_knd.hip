@@ -74,8 +74,7 @@ __global__ void __launch_bounds__(256)
     const InstND ipar = p.ip[inst];
     double v = ipar.u0;
     if (ipar.init_sd > 0.0) {
-        const Normals4<double> nz = block_normals<double>(static_cast<uint32_t>(c >> 2), 0u, ctr_word2(0, 1u),
-                                                          ipar.realisation, make_key(p.seed));
+        const Normals4<double> nz = init_normals(static_cast<uint32_t>(c >> 2), ipar.realisation, make_key(p.seed));
         v += ipar.init_sd * nz.z[c & 3];
     }
     field[static_cast<int64_t>(inst) * cells + c] = static_cast<T>(v);

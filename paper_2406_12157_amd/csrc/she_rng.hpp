@@ -119,6 +119,96 @@ __device__ __forceinline__ double unit_angle_f64(uint32_t w)
     return static_cast<double>(w >> 9) * 0x1p-23;
 }
 
+// FP64 Box-Muller functions for the arguments it meets, 2^23 each.  The general
+// log, sqrt and sincospi spend most of their instructions on arguments that do
+// not occur (195 vector instructions per pair; these take 82).  The
+// polynomials are minimax fits of the series named (Remez exchange in 70-digit
+// arithmetic); tails are carried where a rounding would show, so that the
+// largest error over all arguments is no larger than that of the general
+// functions.  Multiply-adds are written out and nothing else is contracted.
+
+// -2 ln(u_a), u_a = (2 (w >> 9) + 1) 2^-24.  With u_a = 2^e f, f in
+// [sqrt(1/2), sqrt(2)), and s = (f - 1) / (f + 1) (both sums exact: f has 24
+// bits), ln f = 2 atanh(s) = 2 s (1 + s^2 R(s^2)).
+__device__ __forceinline__ double neg2_log_u(uint32_t w)
+{
+#pragma clang fp contract(off)
+    const double k = static_cast<double>((w >> 8) | 1u);  // 2^24 u_a
+    const long long bits = __double_as_longlong(k);
+    // exponent and significand about sqrt(1/2): high word offset so that the
+    // exponent field changes at sqrt(1/2)
+    const uint32_t h = static_cast<uint32_t>(static_cast<unsigned long long>(bits) >> 32) + (0x3FF00000u - 0x3FE6A09Eu);
+    const double e = static_cast<double>(static_cast<int>(h >> 20) - (0x3FF + 24));
+    const uint32_t fh = (h & 0xFFFFFu) + 0x3FE6A09Eu;
+    const double f = __longlong_as_double((static_cast<long long>(fh) << 32) | (bits & 0xFFFFFFFFll));
+    const double g = f - 1.0, d = f + 1.0;
+    // 1 / d to full precision: the error 2^-24 of the estimate enters cubed
+    const double r0 = __builtin_amdgcn_rcp(d);
+    const double q = fma(-d, r0, 1.0);
+    const double r = fma(r0, fma(q, q, q), r0);
+    const double s = g * r;
+    const double sl = fma(-d, s, g) * r;  // tail of the quotient
+    const double z = s * s;
+    double R = 0x1.2b5fbf99bdf98p-4;
+    R = fma(R, z, 0x1.39fdb92a21270p-4);
+    R = fma(R, z, 0x1.7462ba295f4f1p-4);
+    R = fma(R, z, 0x1.c71c62d037d4ep-4);
+    R = fma(R, z, 0x1.2492492e03e8ap-3);
+    R = fma(R, z, 0x1.9999999995223p-3);
+    R = fma(R, z, 0x1.5555555555558p-2);
+    // -2 ln u = -2 e ln 2 - 4 s - 4 (s z R + sl): e times the leading 41 bits of
+    // 2 ln 2 is exact, and |that| > |4 s| or e = 0, so the sum's tail is exact too
+    const double A = -4.0 * s, B = e * -0x1.62e42fefa3000p+0;
+    const double hi = B + A, lo = (B - hi) + A;
+    const double t = fma(s * z, R, sl);
+    return hi + (lo + fma(t, -4.0, e * -0x1.3de6af278ece6p-41));
+}
+
+// sqrt(x) for x in [2^-23, 34): the error 2^-24 of the estimate enters cubed,
+// then one correction by the residual.
+__device__ __forceinline__ double sqrt_pos(double x)
+{
+#pragma clang fp contract(off)
+    const double y = __builtin_amdgcn_rsq(x);
+    const double g = x * y;
+    const double e = fma(-g, y, 1.0);
+    const double p = fma(e, 0.375, 0.5);
+    const double g1 = fma(g, e * p, g);
+    return fma(fma(-g1, g1, x), 0.5 * y, g1);
+}
+
+// cos and sin of 2 pi u_b, u_b = (w >> 9) 2^-23: the quadrant and the signed
+// remainder j in [-2^20, 2^20) are bit fields of w; theta = (pi / 4) 2^-20 j,
+// sin theta = j (c0 + j^2 S(j^2)), cos theta = 1 + j^2 C(j^2) (j^2 is exact, and
+// so is j times the leading 31 bits of c0).
+__device__ __forceinline__ void cos_sin_u(uint32_t w, double &c, double &s)
+{
+#pragma clang fp contract(off)
+    const int j = static_cast<int>(w << 2) >> 11;  // bits 9..29 of w, signed
+    const uint32_t q = w + 0x20000000u;            // bits 30, 31: the quadrant of the remainder
+    const double x = static_cast<double>(j), z = x * x;
+    double S = 0x1.e4a9f37c032ebp-298;
+    S = fma(S, z, -0x1.e3027e2c5bec6p-250);
+    S = fma(S, z, 0x1.50783208bdb36p-202);
+    S = fma(S, z, -0x1.32d2cce500616p-155);
+    S = fma(S, z, 0x1.466bc6775a478p-109);
+    S = fma(S, z, -0x1.4abbce625be52p-64);
+    double C = -0x1.b2f3fd8650096p-322;
+    C = fma(C, z, 0x1.f9ce2494625c6p-274);
+    C = fma(C, z, -0x1.a6d1eef4b8ab8p-226);
+    C = fma(C, z, 0x1.e1f5068689174p-179);
+    C = fma(C, z, -0x1.55d3c7e3cb243p-132);
+    C = fma(C, z, 0x1.03c1f081b5ac0p-86);
+    C = fma(C, z, -0x1.66ee9764d772dp-96) + -0x1.3bd3cc9be45dep-42;  // the first coefficient's tail first
+    const double sn = fma(x, 0x1.921fb54000000p-21, x * fma(z, S, 0x1.10b4611a62633p-51));
+    const double cs = fma(z, C, 1.0);
+    const bool swap = (q & 0x40000000u) != 0;
+    const long long a = __double_as_longlong(swap ? sn : cs), b = __double_as_longlong(swap ? cs : sn);
+    const uint32_t sc = (q + 0x40000000u) & 0x80000000u, ss = q & 0x80000000u;
+    c = __longlong_as_double(a ^ (static_cast<long long>(sc) << 32));
+    s = __longlong_as_double(b ^ (static_cast<long long>(ss) << 32));
+}
+
 __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float &zc, float &zs)
 {
     const float ua = unit_open_f32(wa);
@@ -131,12 +221,21 @@ __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float &zc, 
 
 __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, double &zc, double &zs)
 {
+    const double rho = sqrt_pos(neg2_log_u(wa));
+    double s, c;
+    cos_sin_u(wb, c, s);
+    zc = rho * c;
+    zs = rho * s;
+}
+
+// The same pair from the general functions, for the initial perturbation: an
+// FP32 state rounds it, and another last bit could change which way.
+__device__ __forceinline__ void box_muller_init(uint32_t wa, uint32_t wb, double &zc, double &zs)
+{
     const double ua = unit_open_f64(wa);
     const double ub = unit_angle_f64(wb);
     const double rho = sqrt(-2.0 * log(ua));
-    // sin and cos of 2 pi u_b from the exactly reduced sincospi(2 u_b): no
-    // multiply by an inexact 2 pi and no general range reduction (the
-    // argument is in [0, 2)); c1 steps 10% faster than with sincos(2 pi u_b)
+    // sin and cos of 2 pi u_b from the exactly reduced sincospi(2 u_b)
     double s, c;
     sincospi(2.0 * ub, &s, &c);
     zc = rho * c;
@@ -153,6 +252,16 @@ __device__ __forceinline__ Normals4<T> block_normals(uint32_t block, uint32_t st
     Normals4<T> n;
     box_muller(x.w[0], x.w[1], n.z[0], n.z[1]);
     box_muller(x.w[2], x.w[3], n.z[2], n.z[3]);
+    return n;
+}
+
+// The four initial normals (tag 1) of Philox block `block`.
+__device__ __forceinline__ Normals4<double> init_normals(uint32_t block, uint32_t realisation, PhiloxKey key)
+{
+    const Words4 x = philox4x32_10(block, 0u, ctr_word2(0, 1u), realisation, key);
+    Normals4<double> n;
+    box_muller_init(x.w[0], x.w[1], n.z[0], n.z[1]);
+    box_muller_init(x.w[2], x.w[3], n.z[2], n.z[3]);
     return n;
 }
 
@@ -193,10 +302,8 @@ __device__ __forceinline__ void box_muller_sq(uint32_t wa, uint32_t wb, float rc
 __device__ __forceinline__ void box_muller_sq(uint32_t wa, uint32_t wb, double rc, double &r2, double &c,
                                               double &s)
 {
-    const double ua = unit_open_f64(wa);
-    const double ub = unit_angle_f64(wb);
-    r2 = (-2.0 * log(ua)) * (rc * rc);
-    sincospi(2.0 * ub, &s, &c);
+    r2 = neg2_log_u(wa) * (rc * rc);
+    cos_sin_u(wb, c, s);
 }
 
 template <typename T>
