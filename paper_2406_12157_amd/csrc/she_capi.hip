@@ -875,6 +875,33 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
     return SHE_OK;
 }
 
+// March length of the 2D kernels that recompute two rows per chunk (PC, and FE
+// two steps per launch), lx lanes per row.  A wave's time is its rows + 2; w
+// waves on a SIMD take about `share` w of that together (one alone leaves part
+// of the issue slots idle: FP32 0.8, FP64 1.0), and the fullest SIMD decides.
+// The shortest march within `slack` of the best.  Measured, us per step:
+// 512 x 512 x 8 PC with 2, 4, 8 rows (2048, 1024, 512 waves) 10.8, 9.5, 12.9,
+// FP64 26.2, 18.9, 26.3, FE 6.4, 5.8, 8.4; 256 x 130 x 16 FP64 PC 1, 2, 3, 4, 8
+// rows 13.8, 11.5, 9.4, 10.3, 14.8; 64 x 64 x 512 PC 1, 2, 4, 8, 16 rows 16.1,
+// 11.6, 10.2, 11.4, 18.1; 512 x 512 x 64 PC 8, 12, 16, 32 rows 35.0, 33.3, 31.1,
+// 36.3.
+static int march_rows(int n_inst, int ny, int lx, int cap, bool f64, double slack)
+{
+    const int64_t simds = 4 * static_cast<int64_t>(device_cus());
+    const double share = f64 ? 1.0 : 0.8;
+    double t[65], best = 1e300;
+    cap = std::min(cap, ny);
+    for (int c = 1; c <= cap; ++c) {
+        const int64_t waves = (static_cast<int64_t>(n_inst) * ((ny + c - 1) / c) * lx + 63) / 64;
+        const int64_t w = (waves + simds - 1) / simds;
+        t[c] = (c + 2) * std::max(1.0, share * static_cast<double>(w));
+        best = std::min(best, t[c]);
+    }
+    int c = 1;
+    while (t[c] > best * slack) ++c;
+    return c;
+}
+
 static she_status plan_nd(she_handle *h, const she_config *cfg, Plan &plan)
 {
     const she_instance_desc &d0 = h->inst[0];
@@ -931,23 +958,17 @@ static she_status plan_nd(she_handle *h, const she_config *cfg, Plan &plan)
     }
     h->cells = static_cast<int64_t>(p.nx) * p.ny * p.nz;
     if (d0.dim == 2) {
-        // Default march length.  FE: about 16384 row groups in flight, 1..8 rows
-        // each (short marches keep more loads in flight; the halo row a chunk
-        // re-reads mostly hits the cache).  PC recomputes three rows per chunk
-        // and its kernel holds three waves per SIMD, so it takes as few groups
-        // as fill that once, 12 per CU, of up to 64 rows.  Measured at
-        // 512 x 512 x 256 (ms per step without statistics): 43 rows (3072
-        // groups, one round) 0.1222; 32 rows (4096) 0.1263; 64 rows 0.1238;
-        // 40 rows (3328, a short second round) 0.1422.
+        // Default march length.  One FE step per launch: about 16384 row groups in
+        // flight, 1..8 rows each (short marches keep more loads in flight; the
+        // halo row a chunk re-reads mostly hits the cache).  PC: march_rows, up to
+        // 64 rows; at 512 x 512 x 256 (ms per step without statistics) 43 rows
+        // (3072 groups, one round of three waves per SIMD) 0.1222, 32 rows 0.1263,
+        // 64 rows 0.1238, 40 rows (3328, a short second round) 0.1422.
         int chunk = cfg->rows_per_block;
         const int64_t rows_all = static_cast<int64_t>(h->n_inst) * p.ny;
-        if (chunk <= 0) {
-            const int64_t pc_groups = 12 * static_cast<int64_t>(device_cus());
-            chunk = d0.scheme == SHE_EM
-                        ? static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(8, rows_all / 16384)))
-                        : static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(64, (rows_all + pc_groups - 1) /
-                                                                                             pc_groups)));
-        }
+        if (chunk <= 0)
+            chunk = d0.scheme == SHE_EM ? static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(8, rows_all / 16384)))
+                                        : march_rows(h->n_inst, p.ny, LX, 64, h->prec == SHE_F64, 1.03);
         chunk = std::min(chunk, p.ny);
         p.chunk = chunk;
         const int nchunks = (p.ny + chunk - 1) / chunk;
@@ -1049,14 +1070,13 @@ static she_status build_plan(she_handle *h, const she_config *cfg, Plan &plan)
     if (h->dim == 2 && h->pnd.scheme == SHE_EM && h->pnd.ny >= 3 && !(cfg->tuning_flags & SHE_TUNE_SINGLE_STEP)) {
         // Two FE steps per launch (n[1] >= 3: the march reads two rows beyond
         // its chunk).  Each march chunk recomputes the intermediate rows on
-        // both sides of it, so the chunks are longer: about 2048 of up to 32
-        // rows.  Measured on 512 x 512 fields, ms per step, one step per launch
+        // both sides of it, so the chunks are longer: march_rows, up to 32 rows.
+        // Measured on 512 x 512 fields, ms per step, one step per launch
         // vs two: 256 realisations 0.1113 vs 0.0855, 64: 0.0326 vs 0.0232,
         // 16: 0.0131 vs 0.0090, 1: 0.0041 vs 0.0033.  Never shorter than
         // the one-step chunks, whose partials buffer this reuses.
         const ParamsND &p = h->pnd;
-        const int64_t rows_all = static_cast<int64_t>(h->n_inst) * p.ny;
-        const int c2 = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(32, rows_all / 2048)));
+        const int c2 = march_rows(h->n_inst, p.ny, p.nx / h->cx, 32, h->prec == SHE_F64, 1.0);
         h->chunk2 = std::min(std::max(c2, p.chunk), p.ny);
         h->nparts2 = (p.ny + h->chunk2 - 1) / h->chunk2;
         const int gpb = 256 / (p.nx / h->cx);
