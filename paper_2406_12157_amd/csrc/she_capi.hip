@@ -238,6 +238,93 @@ std::vector<double> thomas_solve(const std::vector<double> &a, const std::vector
     return d;
 }
 
+// Factors of the one-wave solve (LaneSolve) of the rows a x_(i-1) + b x_i + c
+// x_(i+1) = d, C cells per lane, a_0 = c_(N-1) = 0; cells beyond N are identity
+// rows.  z, sq, sc: the Sherman-Morrison vector and scalars (z empty: none).
+// Appends [6 C + 16][64] doubles: per cell of the lane the forward factor m, the
+// backward factor n, 1 / diagonal, the couplings p to the left lane's last cell
+// and q to the lane's own, z; then g, 1/b, k1[6], k2[6], sq, sc.  Returns the
+// levels of the reduction over the lanes that matter.
+int lane_factors(const std::vector<double> &a, const std::vector<double> &b, const std::vector<double> &c,
+                 const std::vector<double> &z, double sq, double sc, int C, std::vector<double> &out)
+{
+    const int N = static_cast<int>(b.size());
+    std::vector<double> f(static_cast<size_t>(6 * C + 16) * 64, 0.0);
+    auto at = [&](int field, int lane) -> double & { return f[static_cast<size_t>(field) * 64 + lane]; };
+    // rows of each lane after the elimination: A x_0 + B x_l + Cc x_last = d
+    std::vector<double> A(64 * C), B(64 * C), U(64 * C);
+    for (int lane = 0; lane < 64; ++lane) {
+        double *la = &A[lane * C], *lb = &B[lane * C], *lu = &U[lane * C];
+        for (int l = 0; l < C; ++l) {
+            const int i = lane * C + l;
+            la[l] = i < N ? a[i] : 0.0;
+            lb[l] = i < N ? b[i] : 1.0;
+            lu[l] = i < N ? c[i] : 0.0;
+            at(5 * C + l, lane) = i < N && !z.empty() ? z[i] : 0.0;
+        }
+        for (int l = 1; l < C; ++l) {
+            const double m = la[l] / lb[l - 1];
+            at(l, lane) = m;
+            la[l] = -m * la[l - 1];
+            lb[l] -= m * lu[l - 1];
+        }
+        for (int l = C - 3; l >= 0; --l) {
+            const double n = lu[l] / lb[l + 1];
+            at(C + l, lane) = n;
+            la[l] -= n * la[l + 1];
+            lu[l] = -n * lu[l + 1];
+        }
+        for (int l = 0; l + 1 < C; ++l) {
+            at(2 * C + l, lane) = 1.0 / lb[l];
+            at(3 * C + l, lane) = la[l] / lb[l];
+            at(4 * C + l, lane) = lu[l] / lb[l];
+        }
+    }
+    // one row per lane for its last cell
+    std::vector<double> ra(64), rb(64), rc(64);
+    for (int lane = 0; lane < 64; ++lane) {
+        const int e = lane * C + C - 1;
+        ra[lane] = A[e];
+        rb[lane] = B[e];
+        rc[lane] = U[e];
+        if (C > 1) {
+            rc[lane] = 0.0;
+            if (lane < 63) {
+                const double g = U[e] / B[e + 1];
+                at(6 * C, lane) = g;
+                rb[lane] -= g * A[e + 1];
+                rc[lane] = -g * U[e + 1];
+            }
+        }
+    }
+    int L = 0;
+    for (; L < 6; ++L) {
+        const int s = 1 << L;
+        double largest = 0.0;
+        std::vector<double> na(64, 0.0), nb(64), nc(64, 0.0);
+        for (int l = 0; l < 64; ++l) {
+            const double f1 = l >= s ? ra[l] / rb[l - s] : 0.0, f2 = l + s < 64 ? rc[l] / rb[l + s] : 0.0;
+            nb[l] = rb[l] - (l >= s ? f1 * rc[l - s] : 0.0) - (l + s < 64 ? f2 * ra[l + s] : 0.0);
+            if (l >= s) na[l] = -f1 * ra[l - s];
+            if (l + s < 64) nc[l] = -f2 * rc[l + s];
+            at(6 * C + 2 + L, l) = f1;
+            at(6 * C + 8 + L, l) = f2;
+            largest = std::max(largest, std::max(std::fabs(f1), std::fabs(f2)));
+        }
+        if (largest < 0x1p-64) break;
+        ra.swap(na);
+        rb.swap(nb);
+        rc.swap(nc);
+    }
+    for (int l = 0; l < 64; ++l) {
+        at(6 * C + 1, l) = 1.0 / rb[l];
+        at(6 * C + 14, l) = sq;
+        at(6 * C + 15, l) = sc;
+    }
+    out.insert(out.end(), f.begin(), f.end());
+    return L;
+}
+
 // Largest modulus over wavenumbers theta of the one-step factor of the
 // linearised Burgers scheme at the steepest slope |1 - 2c| = 1:
 // L = -4 r sin^2(theta/2) - i nu sin(theta), G = 1 + L (FE), 1 + L + L^2/2 (PC).
@@ -527,10 +614,14 @@ static int device_cus()
     return cus;
 }
 
-// Shape of an explicit batch on the wave kernels (she_step_1d.hpp).
+// Cells per lane of a rod whose state one wave holds.
+static int rod_cells_per_lane(int n) { return n <= 64 ? 1 : (n <= 128 ? 2 : (n <= 256 ? 4 : 8)); }
+
+// Shape of a batch on the wave kernels (she_step_1d.hpp).
 //
-// Instances of up to 256 cells: one workgroup each, wave 0 advancing the state
-// with 1, 2 or 4 cells per lane and the others drawing the numbers ahead.
+// Instances of up to 256 cells (512 in a batch with implicit ones): one
+// workgroup each, wave 0 advancing the state with 1, 2, 4 or 8 cells per lane and
+// the others drawing the numbers ahead.
 //
 // Longer ones (or block_threads = 64): whole waves with 4 cells per lane, 62
 // units beside the two halo lanes (one more at a Dirichlet wall; one less on a
@@ -542,8 +633,8 @@ static void plan_rods(she_handle *h, int block_threads)
     const int cus = device_cus();
     const int32_t es = static_cast<int32_t>(h->esz);
     h->rods = true;
-    if (h->nmax <= 256 && block_threads != 64) {
-        h->rod_cpl = h->nmax <= 64 ? 1 : (h->nmax <= 128 ? 2 : 4);
+    if (h->mode1d == 2 || (h->nmax <= 256 && block_threads != 64)) {
+        h->rod_cpl = rod_cells_per_lane(h->nmax);
         int nf = 0;
         for (const Inst1D &t : h->tab) nf = std::max(nf, t.bc == SHE_DIRICHLET ? t.n + 1 : t.n);
         h->rod_zrow = (nf + 3) & ~3;
@@ -693,6 +784,11 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
         const int64_t per = std::max<int64_t>(64, std::min<int64_t>(4096, (int64_t(1) << 22) / std::max<int64_t>(1, cells)));
         h->hist_rows = static_cast<int32_t>(per + h->tc_lags);
     }
+    // a batch with implicit rods of at most 512 cells has one wave solve each of
+    // them (lane_cells cells per lane; 0: the barrier kernel)
+    int longest = 0;
+    for (int i = 0; i < h->n_inst; ++i) longest = std::max(longest, h->inst[i].n[0]);
+    const int lane_cells = longest <= 512 && cfg->block_threads != 64 ? rod_cells_per_lane(longest) : 0;
     int64_t ho = 0, to = 0;
     std::map<std::vector<double>, std::pair<int64_t, int32_t>> pcr_shared;  // matrix rows -> factor block
     for (int i = 0; i < h->n_inst; ++i) {
@@ -767,16 +863,25 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
                     up[N - 1] = 0.0;
                 }
                 t.p_off = static_cast<int64_t>(h->pcr_host.size());
-                t.pcr_levels = pcr_factors(lo, di, up, h->pcr_host);
+                std::vector<double> z;
+                double q = 0.0, sc = 0.0;
                 if (per) {
                     std::vector<double> u(N, 0.0);
                     u[0] = g;
                     u[N - 1] = alpha;
-                    const std::vector<double> z = thomas_solve(lo, di, up, u);
-                    h->pcr_host.insert(h->pcr_host.end(), z.begin(), z.end());
-                    const double q = beta / g;
-                    h->pcr_host.push_back(q);
-                    h->pcr_host.push_back(1.0 / (1.0 + z[0] + q * z[N - 1]));
+                    z = thomas_solve(lo, di, up, u);
+                    q = beta / g;
+                    sc = 1.0 / (1.0 + z[0] + q * z[N - 1]);
+                }
+                if (lane_cells) {
+                    t.pcr_levels = lane_factors(lo, di, up, z, q, sc, lane_cells, h->pcr_host);
+                } else {
+                    t.pcr_levels = pcr_factors(lo, di, up, h->pcr_host);
+                    if (per) {
+                        h->pcr_host.insert(h->pcr_host.end(), z.begin(), z.end());
+                        h->pcr_host.push_back(q);
+                        h->pcr_host.push_back(sc);
+                    }
                 }
                 pcr_shared.emplace(std::move(key), std::make_pair(t.p_off, t.pcr_levels));
             }
@@ -844,6 +949,7 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
                 return fail(nullptr, SHE_EUNSUPPORTED, kLdsWhy1D);
         plan_rods(h, cfg->block_threads);
     }
+    if (mode == 2 && lane_cells) plan_rods(h, cfg->block_threads);
 
     plan.add(reinterpret_cast<void **>(&h->d_tab), sizeof(Inst1D) * h->n_inst);
     plan.add(reinterpret_cast<void **>(&h->d_segs), sizeof(Seg1D) * h->segs_host.size());
@@ -1500,7 +1606,7 @@ static she_status advance(she_handle *h, int64_t nsteps, bool sampling)
             }
             if (h->rods)
                 SHE_HIP(h, launch_rods(Launch1D{h->prec, h->mode1d, stats, h->blocks1d, h->rod_block, h->smem1d, s,
-                                                h->d_tab, h->d_segs, h->d_pool, h->d_coef, h->steps,
+                                                h->d_tab, h->d_segs, h->d_pool, h->d_coef, h->d_pcr, h->steps,
                                                 static_cast<int32_t>(k), h->burn_in, h->every, h->mask, st, h->rod_cpl,
                                                 h->rod_ahead, h->rod_zrow, h->rod_slots}));
             else

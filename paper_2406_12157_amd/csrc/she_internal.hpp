@@ -26,9 +26,11 @@ struct Inst1D {
     uint64_t seed;
     double r, sigma, u0, uL, uR;
     double nu;          // Burgers: Courant number
-    // implicit schemes: FP64 parallel-cyclic-reduction factors of M = I - theta W A
-    // at p_off of the reduction buffer: k1[L][N], k2[L][N], 1/b[N], then (periodic)
-    // the Sherman-Morrison vector z[N] and the scalars q, 1/(1 + z_0 + q z_(N-1))
+    // implicit schemes: FP64 factors of M = I - theta W A at p_off of the reduction
+    // buffer.  Rods on one wave: per lane, see lane_factors.  Batches with longer
+    // ones: parallel cyclic reduction over all cells, k1[L][N], k2[L][N], 1/b[N], then
+    // (periodic) the Sherman-Morrison vector z[N] and the scalars q, 1/(1 + z_0 + q
+    // z_(N-1))
     int64_t p_off;
     int32_t pcr_levels;
     int32_t pad_;
@@ -299,10 +301,11 @@ namespace she {
 // ---- launchers (defined next to their kernels) ----
 // One launch of an explicit 1D batch.  mode 0: uniform; 3, 4, 5: uniform with
 // instantaneous noise and of one equation; 1: some instance has material
-// coefficients (k_off >= 0 in `coef`).
+// coefficients (k_off >= 0 in `coef`); 2 (ahead only): some instance is implicit
+// (factors in `pcr`, lane_factors).
 // ahead = 0: k_rods, segs holding n_blocks * block / 64 wave entries, cpl the
 // largest cells per lane (4, 8 or 16); ahead > 0: k_rods_ahead, one block per
-// instance with cpl (1, 2 or 4) cells per lane, chunks of `ahead` steps, rows of
+// instance with cpl (1, 2, 4, or in mode 2 also 8) cells per lane, chunks of `ahead` steps, rows of
 // zrow numbers and `slots` sampled states per chunk in LDS.
 struct Launch1D {
     int prec;
@@ -315,6 +318,7 @@ struct Launch1D {
     const Seg1D *segs;
     void *pool;
     const void *coef;
+    const double *pcr;
     int64_t step0;
     int32_t nsteps;
     int64_t burn_in;

@@ -933,6 +933,8 @@ extern template hipError_t rods_t<float, 0, false>(const Launch1D &);
 extern template hipError_t rods_t<float, 0, true>(const Launch1D &);
 extern template hipError_t rods_t<float, 1, false>(const Launch1D &);
 extern template hipError_t rods_t<float, 1, true>(const Launch1D &);
+extern template hipError_t rods_t<float, 2, true>(const Launch1D &);
+extern template hipError_t rods_t<double, 2, true>(const Launch1D &);
 extern template hipError_t rods_t<float, 3, false>(const Launch1D &);
 extern template hipError_t rods_t<float, 3, true>(const Launch1D &);
 extern template hipError_t rods_t<double, 0, false>(const Launch1D &);
@@ -957,6 +959,7 @@ static hipError_t rods_p(const Launch1D &a)
     switch (a.mode) {
     case 0: return ahead ? rods_t<T, 0, true>(a) : rods_t<T, 0, false>(a);
     case 1: return ahead ? rods_t<T, 1, true>(a) : rods_t<T, 1, false>(a);
+    case 2: return ahead ? rods_t<T, 2, true>(a) : hipErrorInvalidValue;
     case 3: return ahead ? rods_t<T, 3, true>(a) : rods_t<T, 3, false>(a);
     case 4: return ahead ? rods_t<T, 4, true>(a) : rods_t<T, 4, false>(a);
     case 5: return ahead ? rods_t<T, 5, true>(a) : rods_t<T, 5, false>(a);

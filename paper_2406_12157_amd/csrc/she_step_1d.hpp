@@ -192,13 +192,21 @@ enum Ends {
     kRing = 3       // periodic rod held by the wave alone, last unit full
 };
 
+// The solve of an explicit step.
+struct NoSolve {
+    template <int C>
+    __device__ __forceinline__ void operator()(double (&)[C]) const {}
+};
+
 // What one wave knows of its instance: the uniform parameters, the unit of
 // each lane and where the ends of the rod lie.  MODE 0: any uniform rod (the
 // face kind is looked up in each stage); 3, 4, 5: every rod uniform, with
 // instantaneous noise and of one equation, heat, Dean-Kawasaki or Burgers (one
-// face path: fewer registers, no branches); 1: material coefficients.
+// face path: fewer registers, no branches); 1: material coefficients; 2: as 1,
+// with implicit rods among them.
 template <typename T, int CPL, int MODE>
 struct Rod {
+    static constexpr bool VARC = MODE == 1 || MODE == 2;
     int N;
     bool dir;
     int eq, noise, kind;
@@ -213,7 +221,8 @@ struct Rod {
     bool left_wall;  // Dirichlet and lane 0 holds cell 0
     int lg, m;       // lane of the unit of the last cell (-1: not here), its cells
     bool partial;    // that unit is here and not full
-    T Rf[MODE == 1 ? CPL : 1], Sf[MODE == 1 ? CPL : 1], Wc[MODE == 1 ? CPL : 1];
+    T ex;            // MODE 2: weight 1 - theta of the state-dependent deterministic flux
+    T Rf[VARC ? CPL : 1], Sf[VARC ? CPL : 1], Wc[VARC ? CPL : 1];
 
     // Lane l holds unit first + l (wrapped on a periodic rod); lanes
     // [own0, own1) hold units of the wave's own; lanes up to last hold a unit.
@@ -253,14 +262,15 @@ struct Rod {
         }
         partial = lg >= 0 && m < CPL;
         T sw = static_cast<T>(d.sigma * 1.41421356237309504880), swR = sw, rl = r, rr = r;
-        if constexpr (MODE == 1) {
+        ex = static_cast<T>(MODE == 2 && d.scheme >= 2 ? 1.0 - d.theta : 1.0);
+        if constexpr (VARC) {
             const int nf = dir ? N + 1 : N;
             const T *k = d.k_off >= 0 ? coef + d.k_off : nullptr;
 #pragma unroll
             for (int l = 0; l < CPL; ++l) {
                 const int f = CPL * unit + l;
                 const bool wall = dir && (f == 0 || f == N);
-                Rf[l] = (k && f >= 0 && f < nf) ? k[f] : r;
+                Rf[l] = ex * ((k && f >= 0 && f < nf) ? k[f] : r);
                 Sf[l] = (k && f >= 0 && f < nf) ? k[nf + f] : (wall ? sw : sg);
                 Wc[l] = (k && f >= 0 && f < N) ? k[2 * nf + f] : T(1);
             }
@@ -290,14 +300,14 @@ struct Rod {
     template <int K>
     __device__ __forceinline__ T face(T lo, T hi, T z, int l, uint32_t &clamps) const
     {
-        const T rf = MODE == 1 ? Rf[MODE == 1 ? l : 0] : r;
-        const T sf = MODE == 1 ? Sf[MODE == 1 ? l : 0] : sg;
+        const T rf = VARC ? Rf[VARC ? l : 0] : r;
+        const T sf = VARC ? Sf[VARC ? l : 0] : sg;
         const T df = hi - lo;
         if constexpr (K == 0) {
             // sf (lo + hi) / 2 z + r (hi - lo): the half goes into the factor
             // (exact), and the multiply-add is written out so that every copy
             // of this code rounds alike
-            return fma((MODE == 1 ? T(0.5) * sf : hs) * (lo + hi), z, rf * df);
+            return fma((VARC ? T(0.5) * sf : hs) * (lo + hi), z, rf * df);
         } else {
             const T cf = T(0.5) * (lo + hi);
             const int f = CPL * unit + l;
@@ -342,14 +352,14 @@ struct Rod {
         T F[CPL + 1];
         // walls: F_0 = 2 r (U_0 - U_L) + sqrt 2 sigma A(U_L) N_0, mirrored at face N
         const bool wall0 = WALLS && left_wall && lane == 0;
-        if constexpr (WALLS && K == 0 && MODE != 1) {
+        if constexpr (WALLS && K == 0 && !VARC) {
             // the left wall is a face like any other but for its factors
             const T w = sel(wall0, ampL, hs * (left + V[0]));
             F[0] = fma(w, z[0], r0 * (V[0] - left));
         } else {
             F[0] = face<K>(left, V[0], z[0], 0, clamps);
             if (WALLS && left_wall) {
-                T w = rwL * (V[0] - uL);
+                T w = rwL * ((MODE == 2 ? ex * V[0] : V[0]) - uL);
                 if constexpr (K != 0 && K != 2) w = fma(-nu * uL, T(1) - uL, w);
                 w = fma(ampL, z[0], w);
                 F[0] = sel(wall0, w, F[0]);
@@ -359,7 +369,7 @@ struct Rod {
         for (int l = 1; l < CPL; ++l) F[l] = face<K>(V[l - 1], V[l], z[l], l, clamps);
         T Fr = F[0];
         if (E == kWalls || (E == kAny && dir)) {
-            T w = rwR * (uR - lastv);
+            T w = rwR * (uR - (MODE == 2 ? ex * lastv : lastv));
             if constexpr (K != 0 && K != 2) w = fma(-nu * uR, T(1) - uR, w);
             w = fma(ampR, zN, w);
             Fr = sel(lane == lg, w, from_right(w, F[0]));
@@ -373,7 +383,7 @@ struct Rod {
             for (int l = 1; l < CPL; ++l) F[l] = sel(lane == lg && l == m, Fr, F[l]);
         }
 #pragma unroll
-        for (int l = 0; l < CPL; ++l) dv[l] = MODE == 1 ? Wc[MODE == 1 ? l : 0] * (F[l + 1] - F[l]) : F[l + 1] - F[l];
+        for (int l = 0; l < CPL; ++l) dv[l] = VARC ? Wc[VARC ? l : 0] * (F[l + 1] - F[l]) : F[l + 1] - F[l];
     }
 
     template <int E>
@@ -392,13 +402,20 @@ struct Rod {
         }
     }
 
-    // One step (FE, or PC) with the numbers z.
-    template <int E, bool PC>
-    __device__ __forceinline__ void step(T (&u)[CPL], const T (&z)[CPL], T zN, uint32_t &clamps) const
+    // One step (SCHEME 0 FE, 1 PC, 2 implicit: solve) with the numbers z.
+    template <int E, int SCHEME, typename Solve>
+    __device__ __forceinline__ void step(T (&u)[CPL], const T (&z)[CPL], T zN, uint32_t &clamps, const Solve &solve) const
     {
         T dv[CPL];
         stage<E>(u, z, zN, dv, clamps);
-        if constexpr (!PC) {
+        if constexpr (SCHEME == 2) {
+            double x[CPL];
+#pragma unroll
+            for (int l = 0; l < CPL; ++l) x[l] = l < nc ? static_cast<double>(u[l] + dv[l]) : 0.0;
+            solve(x);
+#pragma unroll
+            for (int l = 0; l < CPL; ++l) u[l] = static_cast<T>(x[l]);
+        } else if constexpr (SCHEME == 0) {
 #pragma unroll
             for (int l = 0; l < CPL; ++l) u[l] = u[l] + dv[l];
         } else {
@@ -414,11 +431,12 @@ struct Rod {
     // f(ends, scheme) for this wave's kind of ends and the instance's scheme, as
     // compile-time constants.
     template <typename Fn>
-    __device__ __forceinline__ void by_kind(bool pc, Fn &&f) const
+    __device__ __forceinline__ void by_kind(int scheme, Fn &&f) const
     {
         auto g = [&](auto e) __attribute__((always_inline)) {
-            if (pc) f(e, std::true_type{});
-            else f(e, std::false_type{});
+            if (scheme == 0) f(e, std::integral_constant<int, 0>{});
+            else if (MODE != 2 || scheme == 1) f(e, std::integral_constant<int, 1>{});
+            else if constexpr (MODE == 2) f(e, std::integral_constant<int, 2>{});
         };
         const int e = ends();
         if (e == kInterior) {
@@ -588,9 +606,9 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
     for (int k = 0; k < nsteps;) {
         // the steps up to the next sample (or the end of the launch)
         const int k_end = min(nsteps, k_next);
-        rod.by_kind(pc, [&](auto ec, auto pcc) __attribute__((always_inline)) {
+        rod.by_kind(d.scheme, [&](auto ec, auto sc) __attribute__((always_inline)) {
             constexpr int E = decltype(ec)::value;
-            constexpr bool PC = decltype(pcc)::value;
+            constexpr bool PC = decltype(sc)::value == 1;
             constexpr int per = PC ? kStages / 2 : kStages;
             for (; k < k_end; ++k) {
                 const bool fresh = nw > 1 && left == 0;
@@ -619,7 +637,7 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
                 if (E == kWalls) zN = from_right(T(0), z[0]);
                 else if (E == kAny && dir) zN = rod.partial ? pick<T, CPL>(z, rod.m) : from_right(T(0), z[0]);
                 if (fresh) collect();
-                rod.template step<E, PC>(u, z, zN, clamps);
+                rod.template step<E, PC>(u, z, zN, clamps, NoSolve{});
             }
         });
 
@@ -776,9 +794,110 @@ __global__ void __launch_bounds__(1024, (rods_occupancy<T, CMAX, STATS, MODE>())
                                                    lds);
 }
 
+// ------------------------------------------------------------------ implicit solve
+
+// v of lane - S or lane + S (any value where that is no lane: its factor is 0).
+template <int S>
+__device__ __forceinline__ double lane_below(double v)
+{
+    if constexpr (S == 1) return from_left(v, v);
+    else return __shfl_up(v, S, 64);
+}
+
+template <int S>
+__device__ __forceinline__ double lane_above(double v)
+{
+    if constexpr (S == 1) return from_right(v, v);
+    else return __shfl_down(v, S, 64);
+}
+
+// M x = d for the constant tridiagonal M = I - theta W A of an implicit rod, C
+// consecutive cells per lane, in FP64.  Within a lane the rows are eliminated
+// until cells 1 .. C-1 depend only on the left lane's last cell x_0 and the
+// lane's own last one; the last cells then form a tridiagonal system of one row
+// per lane, solved by cyclic reduction over the lanes (r -= k1 r(l - s) + k2 r(l
+// + s), s = 1, 2, 4, ..), and the others follow.  The host forms all factors
+// once (lane_factors); M is diagonally dominant, so k1 and k2 fall quadratically
+// from level to level, and levels whose factors are below 2^-64 are left out.
+// A periodic rod takes the Sherman-Morrison correction x -= f z of its cyclic
+// part.  The factors stay in registers: a reduction through LDS over all cells,
+// its factors read from L2 and two barriers per level, took 8.4 us per step of
+// 1024 Crank-Nicolson rods of 256 cells at r = 2; this takes 0.90 (64 cells: 5.5,
+// 0.75).  Bound by the chain of lane exchanges, one LDS-pipe permute pair each.
+template <int C>
+struct LaneSolve {
+    double m[C], n[C], ib[C], p[C], q[C], z[C];  // in-lane elimination and substitution, cyclic vector
+    double g, k1[6], k2[6], invb;
+    double sq, sc;  // cyclic part: f = (x_0 + sq x_(N-1)) sc
+    int levels, lg, ml;
+    bool ring;
+
+    __device__ __forceinline__ void load(const double *__restrict__ f, int nlev, bool periodic, int last_lane, int last)
+    {
+        const int lane = threadIdx.x & 63;
+        levels = nlev;
+        ring = periodic;
+        lg = last_lane;
+        ml = last;
+        f += lane;
+#pragma unroll
+        for (int l = 0; l < C; ++l) {
+            m[l] = f[64 * (0 * C + l)];
+            n[l] = f[64 * (1 * C + l)];
+            ib[l] = f[64 * (2 * C + l)];
+            p[l] = f[64 * (3 * C + l)];
+            q[l] = f[64 * (4 * C + l)];
+            z[l] = f[64 * (5 * C + l)];
+        }
+        f += 64 * 6 * C;
+        g = f[0];
+        invb = f[64];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            k1[k] = f[64 * (2 + k)];
+            k2[k] = f[64 * (8 + k)];
+        }
+        sq = f[64 * 14];
+        sc = f[64 * 15];
+    }
+
+    template <int K>
+    __device__ __forceinline__ void level(double &r) const
+    {
+        if (levels > K) r = fma(-k2[K], lane_above<(1 << K)>(r), fma(-k1[K], lane_below<(1 << K)>(r), r));
+    }
+
+    __device__ __forceinline__ void operator()(double (&x)[C]) const
+    {
+#pragma unroll
+        for (int l = 1; l < C; ++l) x[l] = fma(-m[l], x[l - 1], x[l]);
+#pragma unroll
+        for (int l = C - 3; l >= 0; --l) x[l] = fma(-n[l], x[l + 1], x[l]);
+        double r = x[C - 1];
+        if constexpr (C > 1) r = fma(-g, from_right(x[0], x[0]), r);
+        level<0>(r);
+        level<1>(r);
+        level<2>(r);
+        level<3>(r);
+        level<4>(r);
+        level<5>(r);
+        r *= invb;
+        const double x0 = from_left(r, r);
+#pragma unroll
+        for (int l = 0; l < C - 1; ++l) x[l] = fma(-q[l], r, fma(-p[l], x0, x[l] * ib[l]));
+        x[C - 1] = r;
+        if (ring) {
+            const double f = (of_lane(x[0], 0) + sq * of_lane(pick<double, C>(x, ml - 1), lg)) * sc;
+#pragma unroll
+            for (int l = 0; l < C; ++l) x[l] = fma(-f, z[l], x[l]);
+        }
+    }
+};
+
 // ------------------------------------------------------------------ numbers drawn ahead
 
-// One instance per workgroup, CPL cells per lane of wave 0 (N <= 64 CPL).  The
+// One instance per workgroup, CPL cells per lane of wave 0 (N <= 64 CPL; CPL 8
+// for batches with implicit rods only).  The
 // steps go in chunks of up to K.  While wave 0 advances chunk c with the
 // numbers in one LDS buffer and leaves the sampled states in LDS, the other
 // waves draw the numbers of chunk c + 1 into the other buffer, and wave 1 first
@@ -790,8 +909,9 @@ __global__ void __launch_bounds__(1024, (rods_occupancy<T, CMAX, STATS, MODE>())
 // workgroups per CU on, VALU issue.  Four waves in FP32 draw faster than wave 0
 // steps; FP64 numbers take about four times as long, so it has eight.
 template <typename T, int CPL, bool STATS, int MODE>
-__global__ void __launch_bounds__(512, 4)
-    k_rods_ahead(const Inst1D *__restrict__ tab, T *__restrict__ pool, const T *__restrict__ coef, int64_t step0,
+__global__ void __launch_bounds__(512, CPL == 8 ? 2 : 4)
+    k_rods_ahead(const Inst1D *__restrict__ tab, T *__restrict__ pool, const T *__restrict__ coef,
+                 const double *__restrict__ pcr, int64_t step0,
                  int32_t nsteps, int64_t burn_in, int32_t every, uint32_t mask, Stats1D st, int32_t K, int32_t zrow,
                  int32_t slots)
 {
@@ -899,6 +1019,10 @@ __global__ void __launch_bounds__(512, 4)
         Rod<T, CPL, MODE> rod;
         const int units = (N + CPL - 1) / CPL;
         rod.init(d, coef, 0, 0, units, units - 1, true);
+        typename std::conditional<MODE == 2, LaneSolve<CPL>, NoSolve>::type solve;
+        if constexpr (MODE == 2) {
+            if (d.scheme >= 2) solve.load(pcr + d.p_off, d.pcr_levels, !dir, rod.lg, rod.m);
+        }
         uint32_t clamps = 0;
         T u[CPL];
 #pragma unroll
@@ -906,9 +1030,9 @@ __global__ void __launch_bounds__(512, 4)
         // the steps of a chunk; sampled states go to out.  The next step's
         // numbers are read a step ahead of their use (past the chunk's last row
         // what is read is not used; the buffers are padded).
-        auto advance = [&](auto ec, auto pcc, const T *buf, T *out, const Chunk &q) __attribute__((always_inline)) {
+        auto advance = [&](auto ec, auto sc, const T *buf, T *out, const Chunk &q) __attribute__((always_inline)) {
             constexpr int E = decltype(ec)::value;
-            constexpr bool PC = decltype(pcc)::value;
+            constexpr int SCHEME = decltype(sc)::value;
             constexpr bool WN = E == kWalls || E == kAny;
             T za[CPL], zz[CPL], wa = T(0), wz = T(0);
             const T *p = buf + cell0, *pn = buf + N;
@@ -925,13 +1049,13 @@ __global__ void __launch_bounds__(512, 4)
                 const int ke = min(q.len, ks);
                 for (; kk + 2 <= ke; kk += 2) {
                     load(zz, wz);
-                    rod.template step<E, PC>(u, za, wa, clamps);
+                    rod.template step<E, SCHEME>(u, za, wa, clamps, solve);
                     load(za, wa);
-                    rod.template step<E, PC>(u, zz, wz, clamps);
+                    rod.template step<E, SCHEME>(u, zz, wz, clamps, solve);
                 }
                 if (kk < ke) {
                     load(zz, wz);
-                    rod.template step<E, PC>(u, za, wa, clamps);
+                    rod.template step<E, SCHEME>(u, za, wa, clamps, solve);
                     ++kk;
 #pragma unroll
                     for (int l = 0; l < CPL; ++l) za[l] = zz[l];
@@ -945,9 +1069,8 @@ __global__ void __launch_bounds__(512, 4)
                 }
             }
         };
-        const bool pc = d.scheme == 1;
         const bool gone = chunks([&](int c, const Chunk &q, const Chunk &) __attribute__((always_inline)) {
-            rod.by_kind(pc, [&](auto ec, auto pcc) __attribute__((always_inline)) { advance(ec, pcc, zb(c), sb(c), q); });
+            rod.by_kind(d.scheme, [&](auto ec, auto sc) __attribute__((always_inline)) { advance(ec, sc, zb(c), sb(c), q); });
         });
         if (gone) return;
 #pragma unroll
@@ -1073,12 +1196,18 @@ static hipError_t ahead_m(const Launch1D &a)
 {
 #define SHE_AHEAD(C)                                                                                          \
     hipLaunchKernelGGL((k_rods_ahead<T, C, STATS, MODE>), dim3(a.n_blocks), dim3(a.block), a.smem, a.s, a.tab, \
-                       static_cast<T *>(a.pool), static_cast<const T *>(a.coef), a.step0, a.nsteps, a.burn_in, \
-                       a.every, a.mask, a.st, a.ahead, a.zrow, a.slots)
+                       static_cast<T *>(a.pool), static_cast<const T *>(a.coef), a.pcr, a.step0, a.nsteps,     \
+                       a.burn_in, a.every, a.mask, a.st, a.ahead, a.zrow, a.slots)
     switch (a.cpl) {
     case 1: SHE_AHEAD(1); break;
     case 2: SHE_AHEAD(2); break;
     case 4: SHE_AHEAD(4); break;
+    case 8:
+        if constexpr (MODE == 2) {
+            SHE_AHEAD(8);
+            break;
+        }
+        return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
 #undef SHE_AHEAD

@@ -92,3 +92,17 @@ def test_samples_do_not_depend_on_the_launches(she, n):
             assert x["n_samples"] == y["n_samples"] == 898 // 3
             for key in ("mean", "var", "corr"):
                 np.testing.assert_array_equal(x[key], y[key])
+
+
+# one wave per rod up to 512 cells (1, 2, 4, 8 cells per lane, full and not);
+# 513: the kernel of longer implicit rods.  r = 0.01: two levels of the
+# reduction matter, r = 300: all of them
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n", [1, 3, 4, 63, 64, 65, 127, 128, 130, 255, 256, 257, 500, 512, 513])
+def test_implicit_rod_sizes(she, n, precision):
+    insts = [W.instance((n,), bc=bc, scheme=scheme, r=r, eps=1e-3, u0=1.0, u_left=1.0 + 0.1 * bc,
+                        u_right=1.0 - 0.1 * bc, init_sd=0.05, seed=4, realisation=3 * bc + scheme)
+             for bc in (0, 1) for scheme, r in ((W.BE, 0.01), (W.CN, 2.0), (W.BE, 300.0)) if bc or n >= 3]
+    insts.append(W.instance((min(n, 40),), bc=1, scheme=W.HEUN, r=0.05, eps=1e-3, u0=1.0, u_left=1.1, u_right=0.9,
+                            init_sd=0.05, seed=4, realisation=9))
+    check(she, insts, precision, 25)
