@@ -35,6 +35,7 @@ struct she_handle {
 
     // device memory
     bool own = false;
+    bool counted = false;         // Stage knows of this handle
     char *base = nullptr;
     size_t bytes = 0;
 
@@ -135,6 +136,67 @@ she_status hipfail(she_handle *h, hipError_t e, const char *what)
 {
     return fail(h, SHE_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
+
+// Host memory that kernels write results into: a small result then costs one
+// launch and one wait, where a copy to pageable memory adds a staging copy and a
+// second wait (52 us for the statistics of one rod with two such copies, 24 us
+// for its field).  At most kMost buffers are kept for the next calls of any
+// thread, and none once the last handle is gone; a call that gets none copies.
+class Stage {
+public:
+    static constexpr size_t kDoubles = 32768;
+    Stage()
+    {
+        std::lock_guard<std::mutex> lk(mu());
+        if (!spare().empty()) {
+            p_ = spare().back();
+            spare().pop_back();
+            return;
+        }
+        void *v = nullptr;
+        if (hipHostMalloc(&v, kDoubles * sizeof(double), hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+            p_ = static_cast<double *>(v);
+        else
+            (void)hipGetLastError();
+    }
+    ~Stage()
+    {
+        if (!p_) return;
+        std::lock_guard<std::mutex> lk(mu());
+        if (handles() > 0 && spare().size() < kMost) spare().push_back(p_);
+        else (void)hipHostFree(p_);
+    }
+    Stage(const Stage &) = delete;
+    Stage &operator=(const Stage &) = delete;
+    double *get() const { return p_; }
+    static void add_handle(int k)
+    {
+        std::lock_guard<std::mutex> lk(mu());
+        handles() += k;
+        if (handles() > 0) return;
+        for (double *p : spare()) (void)hipHostFree(p);
+        spare().clear();
+    }
+
+private:
+    static constexpr size_t kMost = 4;
+    static std::mutex &mu()
+    {
+        static std::mutex m;
+        return m;
+    }
+    static std::vector<double *> &spare()
+    {
+        static std::vector<double *> v;
+        return v;
+    }
+    static int &handles()
+    {
+        static int n = 0;
+        return n;
+    }
+    double *p_ = nullptr;
+};
 
 #define SHE_HIP(h, call)                                   \
     do {                                                   \
@@ -975,8 +1037,8 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
             plan.add(reinterpret_cast<void **>(&h->d_skw1), sizeof(double) * 2 * off);
         }
     }
-    // fin1d_at, then the lag products of she_stats
-    h->fin_len = 4 * static_cast<size_t>(h->nmax) + 8 + static_cast<size_t>(h->tc_lags) * h->nmax;
+    // fin1d_at and its scratch, or the lag products of she_stats
+    h->fin_len = kFinAcc + 4 * static_cast<size_t>(h->nmax) + 8 + static_cast<size_t>(h->tc_lags) * h->nmax;
     if (corr) h->fin_len += 2 * static_cast<size_t>(h->nmax) * h->nmax;
     return SHE_OK;
 }
@@ -1124,7 +1186,7 @@ static she_status plan_nd(she_handle *h, const she_config *cfg, Plan &plan)
     plan.add(reinterpret_cast<void **>(&h->d_part), 2 * sizeof(double) * h->nparts * h->n_inst);
     plan.add(reinterpret_cast<void **>(&h->d_step), sizeof(int64_t));
     h->graph_steps = cfg->graph_steps;
-    h->fin_len = 4 + kFinParts;
+    h->fin_len = kFinAcc + 4 + kFinParts;
     if (h->mask & SHE_STAT_SK) {
         // shells round(|k|), signed k in [-N/2, N/2); mode counts per shell
         const double kmax = std::sqrt(0.25 * nx * nx + 0.25 * p.ny * p.ny);
@@ -1152,7 +1214,7 @@ static she_status plan_nd(she_handle *h, const she_config *cfg, Plan &plan)
             plan.add(reinterpret_cast<void **>(&h->d_skwm), nb);
             plan.add(reinterpret_cast<void **>(&h->d_skwm2), nb);
         }
-        h->fin_len = 4 + h->nbins + kFinParts;
+        h->fin_len = kFinAcc + 4 + ((h->nbins + 1) & ~1) + kFinParts;  // the partials 16-byte aligned
     }
     return SHE_OK;
 }
@@ -1377,6 +1439,8 @@ extern "C" she_status she_create(const she_config *cfg, she_handle **out)
     }
     h->bytes = plan.total;
     plan.carve(h->base);
+    h->counted = true;
+    Stage::add_handle(1);
 
     hipStream_t s = h->stream;
     // host sources of the asynchronous copies below; they live until the
@@ -1445,6 +1509,7 @@ extern "C" void she_destroy(she_handle *h)
         if (g) (void)hipGraphExecDestroy(g);
     if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
     if (h->own && h->base) (void)hipFree(h->base);
+    if (h->counted) Stage::add_handle(-1);
     delete h;
 }
 
@@ -1702,13 +1767,13 @@ static she_status copy_out(she_handle *h, double *dst, int64_t cap, const double
     return SHE_OK;
 }
 
-// Finalisation results of one 1D instance in d_fin: mean[N], var[N], sum, S_k
-// [N], covariance [N^2] (this much is copied to the host, up to what the
-// caller asked for), then the scratch: circulant sums [N], second moments [N^2].
-static Fin1D fin1d_at(double *fin, int64_t n)
+// Finalisation results of one 1D instance at out: accumulators, mean[N], var[N],
+// sum, S_k [N], covariance [N^2] (as much of it as the caller asked for);
+// scratch for the circulant sums [N] and second moments [N^2].
+static Fin1D fin1d_at(double *out, double *scratch, int64_t n)
 {
-    double *sk = fin + 2 * n + 1, *cov = sk + n, *circ = cov + n * n;
-    return Fin1D{fin, fin + n, fin + 2 * n, cov, sk, circ + n, circ};
+    double *mean = out + kFinAcc, *sk = mean + 2 * n + 1;
+    return Fin1D{reinterpret_cast<InstAcc *>(out), mean, mean + n, mean + 2 * n, sk + n, sk, scratch + n, scratch};
 }
 
 extern "C" she_status she_stats(she_handle *h, int32_t instance, she_stats_out *out)
@@ -1716,9 +1781,38 @@ extern "C" she_status she_stats(she_handle *h, int32_t instance, she_stats_out *
     if (!h || !out) return fail(h, SHE_EINVAL, "NULL argument");
     if (instance < 0 || instance >= h->n_inst) return fail(h, SHE_EINVAL, "instance out of range");
     hipStream_t s = h->stream;
-    InstAcc acc;
-    SHE_HIP(h, hipMemcpyAsync(&acc, h->d_acc + instance, sizeof(InstAcc), hipMemcpyDeviceToHost, s));
+    // Finalise into host memory the device writes, or where the results do not
+    // fit there into d_fin and copy; one wait either way.
+    const bool d1 = h->dim == 1;
+    const int N = d1 ? h->tab[instance].n : 0;
+    const int64_t nn = static_cast<int64_t>(N) * N;
+    const bool corr = d1 && h->tab[instance].x_off >= 0;
+    // the covariance and S_k are formed and copied only when asked for
+    const bool want = corr && (out->corr || out->sk);
+    const size_t len = kFinAcc + (d1 ? 3 * static_cast<size_t>(N) + 1 + (want ? static_cast<size_t>(nn) : 0)
+                                     : 3 + static_cast<size_t>(h->nbins));
+    const Stage stage;
+    double *const to = stage.get() && len <= Stage::kDoubles ? stage.get() : h->d_fin;
+    if (d1) {
+        // the scratch behind the results' place in d_fin
+        double *scratch = h->d_fin + kFinAcc + 3 * static_cast<size_t>(N) + 1 + (want ? nn : 0);
+        SHE_HIP(h, launch_fin1d(h->prec, s, h->d_tab, instance, N, h->d_pool, h->d_s1, h->d_s2, h->tab[instance].off,
+                                corr ? static_cast<char *>(h->d_x) + h->esz * h->tab[instance].x_off : nullptr,
+                                corr ? h->d_c + h->tab[instance].c_off : nullptr, h->d_acc + instance, want,
+                                fin1d_at(to, scratch, N)));
+    } else {
+        SHE_HIP(h, launch_finnd(h->prec, s, h->pnd, instance, h->cells, h->field(), h->d_acc, h->d_sksum,
+                                h->d_skmodes, h->nbins, h->d_fin + h->fin_len - kFinParts, to));
+    }
+    std::vector<double> copied;
+    if (to == h->d_fin) {
+        copied.resize(len);
+        SHE_HIP(h, hipMemcpyAsync(copied.data(), to, sizeof(double) * len, hipMemcpyDeviceToHost, s));
+    }
     SHE_HIP(h, hipStreamSynchronize(s));
+    const double *const host = to == h->d_fin ? copied.data() : to;
+    InstAcc acc;
+    std::memcpy(&acc, host, sizeof acc);
     out->n_samples = acc.n_samples;
     out->steps = h->steps;
     out->nonfinite = acc.nonfinite;
@@ -1772,30 +1866,17 @@ extern "C" she_status she_stats(she_handle *h, int32_t instance, she_stats_out *
                 return st;
         }
     }
+    const double *const res = host + kFinAcc;
     if (h->dim == 1) {
-        const int N = h->tab[instance].n;
-        const bool corr = h->tab[instance].x_off >= 0;
-        const int rows = static_cast<int>(acc.n_samples % kCorrBlock);
-        // the covariance and S_k are formed and copied only when asked for
-        const bool want = corr && (out->corr || out->sk);
-        const Fin1D fin = fin1d_at(h->d_fin, N);
-        SHE_HIP(h, launch_fin1d(h->prec, s, h->d_tab, instance, N, h->d_pool, h->d_s1, h->d_s2, h->tab[instance].off,
-                                corr ? static_cast<char *>(h->d_x) + h->esz * h->tab[instance].x_off : nullptr,
-                                corr ? h->d_c + h->tab[instance].c_off : nullptr, acc.n_samples, rows, want, fin));
-        const int64_t nn = static_cast<int64_t>(N) * N;
-        const size_t len = 3 * static_cast<size_t>(N) + 1 + (want && out->corr ? static_cast<size_t>(nn) : 0);
-        std::vector<double> host(len);
-        SHE_HIP(h, hipMemcpyAsync(host.data(), h->d_fin, sizeof(double) * len, hipMemcpyDeviceToHost, s));
-        SHE_HIP(h, hipStreamSynchronize(s));
         she_status st;
         if (h->d_s1 == nullptr && (out->mean || out->var))
             return fail(h, SHE_EINVAL, "per-cell mean/var need SHE_STAT_MOMENTS");
-        if ((st = copy_out(h, out->mean, out->mean_cap, host.data(), N, "mean")) != SHE_OK) return st;
-        if ((st = copy_out(h, out->var, out->var_cap, host.data() + N, N, "var")) != SHE_OK) return st;
+        if ((st = copy_out(h, out->mean, out->mean_cap, res, N, "mean")) != SHE_OK) return st;
+        if ((st = copy_out(h, out->var, out->var_cap, res + N, N, "var")) != SHE_OK) return st;
         if ((out->corr || out->sk) && !corr) return fail(h, SHE_EINVAL, "corr / sk need SHE_STAT_CORR");
-        if ((st = copy_out(h, out->corr, out->corr_cap, host.data() + 3 * N + 1, nn, "corr")) != SHE_OK) return st;
-        if ((st = copy_out(h, out->sk, out->sk_cap, host.data() + 2 * N + 1, N, "sk")) != SHE_OK) return st;
-        out->sum_u = host[2 * N];
+        if ((st = copy_out(h, out->corr, out->corr_cap, res + 3 * N + 1, nn, "corr")) != SHE_OK) return st;
+        if ((st = copy_out(h, out->sk, out->sk_cap, res + 2 * N + 1, N, "sk")) != SHE_OK) return st;
+        out->sum_u = res[2 * N];
         if (out->tcorr) {
             if (!h->d_tc) return fail(h, SHE_EINVAL, "tcorr needs SHE_STAT_TCORR");
             const int64_t ln = static_cast<int64_t>(h->tc_lags) * N;
@@ -1806,20 +1887,15 @@ extern "C" she_status she_stats(she_handle *h, int32_t instance, she_stats_out *
             SHE_HIP(h, hipStreamSynchronize(s));
         }
     } else {
-        SHE_HIP(h, launch_finnd(h->prec, s, h->pnd, instance, h->cells, h->field(), h->d_acc, h->d_sksum,
-                                h->d_skmodes, h->nbins, h->d_fin));
-        std::vector<double> host(3 + h->nbins);
-        SHE_HIP(h, hipMemcpyAsync(host.data(), h->d_fin, sizeof(double) * host.size(), hipMemcpyDeviceToHost, s));
-        SHE_HIP(h, hipStreamSynchronize(s));
         she_status st;
-        if ((st = copy_out(h, out->mean, out->mean_cap, host.data(), 1, "mean")) != SHE_OK) return st;
-        if ((st = copy_out(h, out->var, out->var_cap, host.data() + 1, 1, "var")) != SHE_OK) return st;
+        if ((st = copy_out(h, out->mean, out->mean_cap, res, 1, "mean")) != SHE_OK) return st;
+        if ((st = copy_out(h, out->var, out->var_cap, res + 1, 1, "var")) != SHE_OK) return st;
         if (out->corr || out->tcorr) return fail(h, SHE_EINVAL, "corr / tcorr are 1D only");
         if ((out->sk || out->sk_modes) && h->nbins == 0) return fail(h, SHE_EINVAL, "sk needs SHE_STAT_SK (2D)");
-        if ((st = copy_out(h, out->sk, out->sk_cap, host.data() + 3, h->nbins, "sk")) != SHE_OK) return st;
+        if ((st = copy_out(h, out->sk, out->sk_cap, res + 3, h->nbins, "sk")) != SHE_OK) return st;
         if ((st = copy_out(h, out->sk_modes, out->sk_modes_cap, h->skmodes.data(), h->nbins, "sk_modes")) != SHE_OK)
             return st;
-        out->sum_u = host[2];
+        out->sum_u = res[2];
     }
     if (acc.nonfinite) return fail(h, SHE_ENONFINITE, "a sample met a non-finite value; state frozen");
     return SHE_OK;
@@ -1842,6 +1918,15 @@ extern "C" she_status she_read_field(she_handle *h, int32_t instance, double *ho
     if (instance < 0 || instance >= h->n_inst) return fail(h, SHE_EINVAL, "instance out of range");
     const int64_t nc = inst_cells(h, instance);
     if (n != nc) return fail(h, SHE_EINVAL, "n must equal the instance's cell count");
+    if (static_cast<size_t>(nc) <= Stage::kDoubles) {
+        const Stage stage;
+        if (stage.get()) {
+            SHE_HIP(h, launch_widen(h->prec, h->stream, inst_field(h, instance), nc, stage.get()));
+            SHE_HIP(h, hipStreamSynchronize(h->stream));
+            std::memcpy(host, stage.get(), sizeof(double) * nc);
+            return SHE_OK;
+        }
+    }
     std::vector<char> buf(h->esz * nc);
     SHE_HIP(h, hipMemcpyAsync(buf.data(), inst_field(h, instance), buf.size(), hipMemcpyDeviceToHost, h->stream));
     SHE_HIP(h, hipStreamSynchronize(h->stream));

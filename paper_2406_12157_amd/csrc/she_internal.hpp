@@ -337,16 +337,20 @@ hipError_t launch_step1d(int prec, int block, int maxg, bool stats, int n_blocks
 // Initial state of 1D instances: steady profile + init_sd * N(tag 1, step 0, face = cell).
 hipError_t launch_init1d(int prec, int n_inst, int nmax, hipStream_t s, const Inst1D *tab,
                          const double *init_sd, void *pool);
-// 1D finalisation of one instance (FP64, device): mean[N], var[N] and sum(U)
-// always; with corr the covariance cov[N^2] and S_k sk[N] too (m2[N^2] and
-// circ[N] are scratch).  s1, s2: the batch's per-cell sums (null: not kept), the
-// instance's at off.
+// 1D finalisation of one instance (FP64): its accumulators acc, mean[N], var[N]
+// and sum(U) always; with corr the covariance cov[N^2] and S_k sk[N] too (m2[N^2]
+// and circ[N] are device scratch; the others may be host memory the device
+// writes).  s1, s2: the batch's per-cell sums (null: not kept), the instance's at
+// off.
 struct Fin1D {
+    InstAcc *acc;
     double *mean, *var, *sum, *cov, *sk, *m2, *circ;
 };
 hipError_t launch_fin1d(int prec, hipStream_t s, const Inst1D *tab, int inst, int n, const void *pool,
                         const double *s1, const double *s2, int64_t off, const void *xblk, const double *c,
-                        int64_t n_samples, int partial_rows, bool corr, const Fin1D &out);
+                        const InstAcc *acc, bool corr, const Fin1D &out);
+// out[i] = field[i], i < n, in FP64 (out may be host memory).
+hipError_t launch_widen(int prec, hipStream_t s, const void *field, int64_t n, double *out);
 
 // Where a sample launch of the two-step 2D FE march puts the row transforms
 // of the rows it writes (the first stage of the structure factor).
@@ -383,13 +387,15 @@ hipError_t launch_set_step(hipStream_t s, int64_t *ctr, int64_t value);
 hipError_t launch_add_step(hipStream_t s, int64_t *ctr, int64_t k);
 // nD initial state: u0 + init_sd * N(tag 1, step 0, face = cell) per instance.
 hipError_t launch_initnd(int prec, hipStream_t s, const ParamsND &p, int64_t cells, void *field);
-// nD finalisation of one instance: out[0] spatial mean, out[1] spatial variance,
-// out[2] sum(U), then (nbins > 0) out[3 + b] the shell average of <|U_k|^2>;
-// kFinParts more entries of out are scratch for the sum's partials.
-constexpr int kFinParts = 1024;
+// nD finalisation of one instance: its accumulators at out, then out[kFinAcc]
+// spatial mean, [+1] spatial variance, [+2] sum(U) and (nbins > 0) [+3 + b] the
+// shell average of <|U_k|^2>; out may be host memory.  part: kFinParts doubles of
+// device scratch for the sum's partials.
+constexpr int kFinAcc = 16, kFinParts = 1024;
+static_assert(sizeof(InstAcc) <= kFinAcc * sizeof(double) && sizeof(InstAcc) % sizeof(double) == 0, "");
 hipError_t launch_finnd(int prec, hipStream_t s, const ParamsND &p, int inst, int64_t cells,
                         const void *field, const InstAcc *acc, const double *sk_sums,
-                        const double *sk_modes, int nbins, double *out);
+                        const double *sk_modes, int nbins, double *part, double *out);
 
 // 1D time correlation: lag sums tc[m][i] += sum over the samples n in
 // [n0, min(n0 + count, n_samples)) with n >= m of h[n][i] h[n-m][i] (FP64),

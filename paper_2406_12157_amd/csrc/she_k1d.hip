@@ -646,9 +646,11 @@ __global__ void __launch_bounds__(256)
 // their own loads.
 template <typename T>
 __global__ void __launch_bounds__(256)
-    k_fin_m2(const T *__restrict__ X, int rows, const double *__restrict__ C, const double *__restrict__ s1, int N,
-             int64_t M, double *__restrict__ m2, double *__restrict__ cov)
+    k_fin_m2(const T *__restrict__ X, const double *__restrict__ C, const double *__restrict__ s1, int N,
+             const InstAcc *__restrict__ q, double *__restrict__ m2, double *__restrict__ cov)
 {
+    const int64_t M = max(q->n_samples, static_cast<int64_t>(1));
+    const int rows = static_cast<int>(q->n_samples % kCorrBlock);  // open rows of the X block
     const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (e >= static_cast<int64_t>(N) * N) return;
     const int i = static_cast<int>(e / N), j = static_cast<int>(e - static_cast<int64_t>(i) * N);
@@ -657,12 +659,12 @@ __global__ void __launch_bounds__(256)
     for (; b + 8 <= rows; b += 8) {
         T x[8], y[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            x[q] = X[static_cast<int64_t>(b + q) * N + i];
-            y[q] = X[static_cast<int64_t>(b + q) * N + j];
+        for (int k = 0; k < 8; ++k) {
+            x[k] = X[static_cast<int64_t>(b + k) * N + i];
+            y[k] = X[static_cast<int64_t>(b + k) * N + j];
         }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) acc += static_cast<double>(x[q]) * static_cast<double>(y[q]);
+        for (int k = 0; k < 8; ++k) acc += static_cast<double>(x[k]) * static_cast<double>(y[k]);
     }
     for (; b < rows; ++b)
         acc += static_cast<double>(X[static_cast<int64_t>(b) * N + i]) * static_cast<double>(X[static_cast<int64_t>(b) * N + j]);
@@ -675,11 +677,13 @@ __global__ void __launch_bounds__(256)
 template <typename T>
 __global__ void __launch_bounds__(256)
     k_fin_cells(const Inst1D *__restrict__ tab, int inst, const T *__restrict__ pool,
-                const double *__restrict__ s1, const double *__restrict__ s2, int64_t M, Fin1D out)
+                const double *__restrict__ s1, const double *__restrict__ s2, const InstAcc *__restrict__ acc, Fin1D out)
 {
     const Inst1D d = tab[inst];
     const int N = d.n;
-    const double inv = M > 0 ? 1.0 / static_cast<double>(M) : 0.0;
+    const double inv = 1.0 / static_cast<double>(max(acc->n_samples, static_cast<int64_t>(1)));
+    if (threadIdx.x < sizeof(InstAcc) / 8)
+        reinterpret_cast<uint64_t *>(out.acc)[threadIdx.x] = reinterpret_cast<const uint64_t *>(acc)[threadIdx.x];
     double a = 0.0;
     for (int i = threadIdx.x; i < N; i += 256) {
         const double ref = d.bc == 1 ? d.uL + (d.uR - d.uL) * (i + 0.5) / N : d.u0;
@@ -721,8 +725,9 @@ __global__ void __launch_bounds__(256) k_fin_circ(int N, const double *__restric
 // One wave per k: lane l takes j = l, l + 64, ... of the three sums.
 __global__ void __launch_bounds__(256)
     k_fin_sk(const Inst1D *__restrict__ tab, int inst, const double *__restrict__ s1, const double *__restrict__ circ,
-             int64_t M, double *__restrict__ sk)
+             const InstAcc *__restrict__ acc, double *__restrict__ sk)
 {
+    const int64_t M = max(acc->n_samples, static_cast<int64_t>(1));
     const Inst1D d = tab[inst];
     const int N = d.n;
     const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -982,27 +987,43 @@ hipError_t launch_init1d(int prec, int n_inst, int nmax, hipStream_t s, const In
 
 hipError_t launch_fin1d(int prec, hipStream_t s, const Inst1D *tab, int inst, int n, const void *pool,
                         const double *s1, const double *s2, int64_t off, const void *xblk, const double *c,
-                        int64_t n_samples, int partial_rows, bool corr, const Fin1D &out)
+                        const InstAcc *acc, bool corr, const Fin1D &out)
 {
     const int64_t nn = static_cast<int64_t>(n) * n;
-    const int64_t M = n_samples > 0 ? n_samples : 1;
     if (prec == 0)
         hipLaunchKernelGGL(k_fin_cells<float>, dim3(1), dim3(256), 0, s, tab, inst, static_cast<const float *>(pool),
-                           s1, s2, M, out);
+                           s1, s2, acc, out);
     else
         hipLaunchKernelGGL(k_fin_cells<double>, dim3(1), dim3(256), 0, s, tab, inst,
-                           static_cast<const double *>(pool), s1, s2, M, out);
+                           static_cast<const double *>(pool), s1, s2, acc, out);
     if (corr) {
         const dim3 nb(static_cast<unsigned>((nn + 255) / 256)), nw((n + 3) / 4);
         if (prec == 0)
-            hipLaunchKernelGGL(k_fin_m2<float>, nb, dim3(256), 0, s, static_cast<const float *>(xblk), partial_rows, c,
-                               s1 + off, n, M, out.m2, out.cov);
+            hipLaunchKernelGGL(k_fin_m2<float>, nb, dim3(256), 0, s, static_cast<const float *>(xblk), c, s1 + off, n,
+                               acc, out.m2, out.cov);
         else
-            hipLaunchKernelGGL(k_fin_m2<double>, nb, dim3(256), 0, s, static_cast<const double *>(xblk), partial_rows,
-                               c, s1 + off, n, M, out.m2, out.cov);
+            hipLaunchKernelGGL(k_fin_m2<double>, nb, dim3(256), 0, s, static_cast<const double *>(xblk), c, s1 + off, n,
+                               acc, out.m2, out.cov);
         hipLaunchKernelGGL(k_fin_circ, nw, dim3(256), 0, s, n, out.m2, out.circ);
-        hipLaunchKernelGGL(k_fin_sk, nw, dim3(256), 0, s, tab, inst, s1, out.circ, M, out.sk);
+        hipLaunchKernelGGL(k_fin_sk, nw, dim3(256), 0, s, tab, inst, s1, out.circ, acc, out.sk);
     }
+    return hipGetLastError();
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_widen(const T *__restrict__ f, int64_t n, double *__restrict__ out)
+{
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i < n) out[i] = static_cast<double>(f[i]);
+}
+
+hipError_t launch_widen(int prec, hipStream_t s, const void *field, int64_t n, double *out)
+{
+    const dim3 g(static_cast<unsigned>((n + 255) / 256));
+    if (prec == 0)
+        hipLaunchKernelGGL(k_widen<float>, g, dim3(256), 0, s, static_cast<const float *>(field), n, out);
+    else
+        hipLaunchKernelGGL(k_widen<double>, g, dim3(256), 0, s, static_cast<const double *>(field), n, out);
     return hipGetLastError();
 }
 

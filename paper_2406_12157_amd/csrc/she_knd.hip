@@ -137,6 +137,9 @@ __global__ void __launch_bounds__(256)
 {
     const double total = nparts > 0 ? block_sum<double>(part, 0, nparts)
                                     : block_sum<T>(field + static_cast<int64_t>(inst) * cells, 0, cells);
+    if (threadIdx.x < sizeof(InstAcc) / 8)
+        reinterpret_cast<uint64_t *>(out)[threadIdx.x] = reinterpret_cast<const uint64_t *>(acc + inst)[threadIdx.x];
+    out += kFinAcc;
     const double u0 = p.ip[inst].u0;
     if (threadIdx.x == 0) {
         const InstAcc q = acc[inst];
@@ -210,10 +213,9 @@ hipError_t launch_initnd(int prec, hipStream_t s, const ParamsND &p, int64_t cel
 // launches) and 4.2 us.
 template <typename T>
 static void finnd_t(hipStream_t s, const ParamsND &p, int inst, int64_t cells, const void *field, const InstAcc *acc,
-                    const double *sk_sums, const double *sk_modes, int nbins, double *out)
+                    const double *sk_sums, const double *sk_modes, int nbins, double *part, double *out)
 {
     const T *f = static_cast<const T *>(field);
-    double *part = out + ((3 + nbins + 1) & ~1);  // 16-byte aligned
     int nparts = 0;
     if (cells > 16384) {
         int64_t span = 8192;
@@ -227,12 +229,13 @@ static void finnd_t(hipStream_t s, const ParamsND &p, int inst, int64_t cells, c
 }
 
 hipError_t launch_finnd(int prec, hipStream_t s, const ParamsND &p, int inst, int64_t cells, const void *field,
-                        const InstAcc *acc, const double *sk_sums, const double *sk_modes, int nbins, double *out)
+                        const InstAcc *acc, const double *sk_sums, const double *sk_modes, int nbins, double *part,
+                        double *out)
 {
     if (prec == 0)
-        finnd_t<float>(s, p, inst, cells, field, acc, sk_sums, sk_modes, nbins, out);
+        finnd_t<float>(s, p, inst, cells, field, acc, sk_sums, sk_modes, nbins, part, out);
     else
-        finnd_t<double>(s, p, inst, cells, field, acc, sk_sums, sk_modes, nbins, out);
+        finnd_t<double>(s, p, inst, cells, field, acc, sk_sums, sk_modes, nbins, part, out);
     return hipGetLastError();
 }
 
