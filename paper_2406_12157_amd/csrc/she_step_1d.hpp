@@ -483,18 +483,24 @@ __device__ __forceinline__ void wait_flags(const int *flag, int a, int b, int se
     }
 }
 
-// All nw waves of the instance meet (LDS and global accesses of each before it
-// are seen by all after it).
-__device__ __forceinline__ void inst_sync(int *flag, int lw, int nw, int seq)
+// Wait until the flags of all nw waves of the instance reach seq.
+__device__ __forceinline__ void wait_all(const int *flag, int nw, int seq)
 {
-    if (nw == 1) return;
     const int lane = threadIdx.x & 63;
-    if (lane == 0) __hip_atomic_store(flag + lw, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     for (;;) {
         const int v = __hip_atomic_load(flag + min(lane, nw - 1), __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (__all(v >= seq)) break;
         __builtin_amdgcn_s_sleep(1);
     }
+}
+
+// All nw waves of the instance meet (LDS and global accesses of each before it
+// are seen by all after it).
+__device__ __forceinline__ void inst_sync(int *flag, int lw, int nw, int seq)
+{
+    if (nw == 1) return;
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(flag + lw, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    wait_all(flag, nw, seq);
 }
 
 // First unit (of CPL cells) of wave lw's own: nf faces in blocks of four over nw
@@ -517,7 +523,7 @@ __device__ __forceinline__ int rod_split(int nf, bool dir, int nw, int nbig, int
     return b / (CPL / 4);
 }
 
-template <typename T, int CPL, bool STATS, int MODE>
+template <typename T, int CPL, int STATS, int MODE>
 __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1D *__restrict__ tab, T *__restrict__ pool,
                                           const T *__restrict__ coef, int64_t step0, int32_t nsteps, int64_t burn_in,
                                           int32_t every, uint32_t mask, const Stats1D &st, unsigned char *lds)
@@ -550,16 +556,20 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
 #pragma unroll
     for (int l = 0; l < CPL; ++l) u[l] = l < rod.nc && lane < own1 + hr ? gU[CPL * rod.unit + l] : T(0);
 
-    constexpr bool kRegSums = CPL == 4;
+    // STATS 1: per-cell and spatial sums only, the per-cell ones in memory (64
+    // VGPRs in FP32: a batch which needs two workgroups per CU has both resident);
+    // 2: every statistic, FP32 per-cell sums in registers at 4 cells per lane
+    constexpr bool kRegSums = STATS == 2 && CPL == 4 && std::is_same<T, float>::value;
     double s1r[kRegSums ? CPL : 1], s2r[kRegSums ? CPL : 1];
     const bool moments = STATS && (mask & 1u) && st.s1 != nullptr;
-    const bool corr = STATS && (mask & 2u) && d.x_off >= 0;
-    const bool tcorr = STATS && (mask & 16u) && d.h_off >= 0;
+    const bool corr = STATS == 2 && (mask & 2u) && d.x_off >= 0;
+    const bool tcorr = STATS == 2 && (mask & 16u) && d.h_off >= 0;
     int64_t nsamp = STATS ? acc->n_samples : 0;
     double sp_mean = STATS ? acc->sp_mean : 0.0, sp_sq = STATS ? acc->sp_sq : 0.0, sp_var = STATS ? acc->sp_var : 0.0;
     // reference profile of the deviations: u0, or the linear wall profile
     const double ref0 = dir ? d.uL : d.u0, ref_slope = dir ? (d.uR - d.uL) / N : 0.0;
-    if constexpr (STATS && kRegSums) {
+    const double inv_n = 1.0 / N;
+    if constexpr (kRegSums) {
 #pragma unroll
         for (int l = 0; l < CPL; ++l) {
             const bool in = moments && rod.own && l < rod.nc;
@@ -603,6 +613,129 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
             for (int l = 0; l < CPL; ++l) u[l] = src[l];
         }
     };
+    // A sample is taken in two parts.  begin: the wave's sums over the sampled
+    // state, published to the instance's other waves, and a copy of the state.
+    // finish, at the next sample or the launch's end: the sums over the instance
+    // and the statistics.  By then the other waves have published theirs long
+    // ago: N = 3967 x 256 FE FP32 with a sample every ten steps takes 1.16 us/step
+    // (0.93 without samples), 1.79 when all 16 waves met at the sample itself.
+    T up[CPL];
+    bool pend = false;
+    double pa = 0.0, pb = 0.0;
+    int pbad = 0;
+    auto begin = [&]() __attribute__((always_inline)) {
+        double a = 0.0, b = 0.0;
+        int bad = 0;
+#pragma unroll
+        for (int l = 0; l < CPL; ++l) {
+            up[l] = u[l];
+            if (rod.own && l < rod.nc) {
+                if (!isfinite(u[l])) bad = 1;
+                const double dl = static_cast<double>(u[l]) - fma(ref_slope, CPL * rod.unit + l + 0.5, ref0);
+                a += dl;
+                b += dl * dl;
+            }
+        }
+        pa = wave_total(a);
+        pb = wave_total(b);
+        pbad = __any(bad) ? 1 : 0;
+        pend = true;
+        if (nw > 1) {
+            // the two sets of slots alternate: a wave writes a set again only
+            // after every wave has published the next sample, and so read this one
+            double *rd = red + (mseq & 1) * 48;
+            ++mseq;
+            if (lane == 0) {
+                rd[lw] = pa;
+                rd[16 + lw] = pb;
+                rd[32 + lw] = static_cast<double>(pbad);
+                __hip_atomic_store(mflag + lw, mseq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+    };
+    // returns whether the instance froze
+    auto finish = [&]() __attribute__((always_inline)) {
+        pend = false;
+        if (nw > 1) {
+            wait_all(mflag, nw, mseq);
+            const double *rd = red + ((mseq - 1) & 1) * 48;
+            pbad = __any(rd[32 + min(lane, nw - 1)] != 0.0) ? 1 : 0;
+            if (lw == 0) {  // in the order of the waves
+                pa = wave_total(lane < nw ? rd[lane] : 0.0);
+                pb = wave_total(lane < nw ? rd[16 + lane] : 0.0);
+            }
+        }
+        const int row = static_cast<int>(nsamp % kCorrBlock);
+        T *X = corr ? static_cast<T *>(st.xblk) + d.x_off : nullptr;
+        const int64_t i0 = CPL * rod.unit;
+        const int c = rod.own ? rod.nc : 0;  // the unit's cells of this wave's own
+        if (pbad) {
+            // a non-finite sample: keep the statistics as they were before it
+            // and freeze the state
+#pragma unroll
+            for (int l = 0; l < CPL; ++l)
+                if (l < c) {
+                    gU[i0 + l] = up[l];
+                    if constexpr (kRegSums) {
+                        if (moments) {
+                            st.s1[d.off + i0 + l] = s1r[l];
+                            st.s2[d.off + i0 + l] = s2r[l];
+                        }
+                    }
+                }
+            if (lw == 0 && lane == 0) {
+                acc->nonfinite = 1;
+                acc->n_samples = nsamp;
+                acc->sp_mean = sp_mean;
+                acc->sp_sq = sp_sq;
+                acc->sp_var = sp_var;
+            }
+            return true;
+        }
+        const double a = pa * inv_n, b = pb * inv_n;
+        sp_mean += a;
+        sp_sq += b;
+        sp_var += b - a * a;
+        T *H = tcorr ? static_cast<T *>(st.hist) + d.h_off + (nsamp % st.hist_rows) * N : nullptr;
+#pragma unroll
+        for (int h = 0; h < CPL; h += 4) {
+            // per-cell sums in memory: four cells' loads ahead of their stores
+            double m1[4], m2[4];
+            if (!kRegSums && moments) {
+#pragma unroll
+                for (int l = 0; l < 4; ++l) {
+                    m1[l] = h + l < c ? st.s1[d.off + i0 + h + l] : 0.0;
+                    m2[l] = h + l < c ? st.s2[d.off + i0 + h + l] : 0.0;
+                }
+            }
+#pragma unroll
+            for (int l = 0; l < 4; ++l) {
+                const int q = h + l;
+                const double dl = static_cast<double>(up[q]) - fma(ref_slope, CPL * rod.unit + q + 0.5, ref0);
+                if constexpr (kRegSums) {
+                    s1r[q] += dl;
+                    s2r[q] += dl * dl;
+                }
+                if (q < c) {
+                    if (!kRegSums && moments) {
+                        st.s1[d.off + i0 + q] = m1[l] + dl;
+                        st.s2[d.off + i0 + q] = m2[l] + dl * dl;
+                    }
+                    if (corr) X[(int64_t)row * N + i0 + q] = static_cast<T>(dl);
+                    if (tcorr) H[i0 + q] = static_cast<T>(dl);
+                }
+            }
+            if (!kRegSums) __builtin_amdgcn_sched_barrier(0);
+        }
+        ++nsamp;
+        if (corr && row == kCorrBlock - 1) {
+            __threadfence_block();
+            inst_sync(mflag, lw, nw, ++mseq);
+            xtx_block<T>(X, st.c + d.c_off, N, lw, nw);
+            inst_sync(mflag, lw, nw, ++mseq);
+        }
+        return false;
+    };
     for (int k = 0; k < nsteps;) {
         // the steps up to the next sample (or the end of the launch)
         const int k_end = min(nsteps, k_next);
@@ -643,108 +776,18 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
 
         if (STATS && k == k_next) {
             k_next += every;
-            double a = 0.0, b = 0.0;
-            int bad = 0;
-            const int row = static_cast<int>(nsamp % kCorrBlock);
-            T *X = corr ? static_cast<T *>(st.xblk) + d.x_off : nullptr;
-            T *Hrow = tcorr ? static_cast<T *>(st.hist) + d.h_off + (nsamp % st.hist_rows) * N : nullptr;
-            double del[CPL];
-#pragma unroll
-            for (int l = 0; l < CPL; ++l) {
-                const int i = CPL * rod.unit + l;
-                del[l] = 0.0;
-                if (rod.own && l < rod.nc) {
-                    const T v = u[l];
-                    if (!isfinite(v)) bad = 1;
-                    const double dl = static_cast<double>(v) - fma(ref_slope, i + 0.5, ref0);
-                    del[l] = dl;
-                    a += dl;
-                    b += dl * dl;
-                    if (corr) X[(int64_t)row * N + i] = static_cast<T>(dl);
-                    if (tcorr) Hrow[i] = static_cast<T>(dl);
-                }
-            }
-            // sums over the instance (fixed order): DPP within each wave, then
-            // (several waves) the wave sums through LDS, added by every wave in
-            // the same order; the two sets of slots alternate
-            a = wave_total(a);
-            b = wave_total(b);
-            bad = __any(bad) ? 1 : 0;
-            if (nw > 1) {
-                double *rd = red + (mseq & 1) * 48;
-                if (lane == 0) {
-                    rd[lw] = a;
-                    rd[16 + lw] = b;
-                    rd[32 + lw] = static_cast<double>(bad);
-                }
-                inst_sync(mflag, lw, nw, ++mseq);
-                a = b = 0.0;
-                bad = 0;
-                for (int w = 0; w < nw; ++w) {
-                    a += rd[w];
-                    b += rd[16 + w];
-                    bad |= rd[32 + w] != 0.0;
-                }
-            }
-            if (bad) {
-                // a non-finite sample: keep the statistics as they were
-                // before it and freeze the state
-#pragma unroll
-                for (int l = 0; l < CPL; ++l)
-                    if (rod.own && l < rod.nc) {
-                        gU[CPL * rod.unit + l] = u[l];
-                        if constexpr (kRegSums) {
-                            if (moments) {
-                                st.s1[d.off + CPL * rod.unit + l] = s1r[l];
-                                st.s2[d.off + CPL * rod.unit + l] = s2r[l];
-                            }
-                        }
-                    }
-                if (lw == 0 && lane == 0) {
-                    acc->nonfinite = 1;
-                    acc->n_samples = nsamp;
-                    acc->sp_mean = sp_mean;
-                    acc->sp_sq = sp_sq;
-                    acc->sp_var = sp_var;
-                }
-                return;
-            }
-            a /= N;
-            b /= N;
-            sp_mean += a;
-            sp_sq += b;
-            sp_var += b - a * a;
-            if constexpr (kRegSums) {
-#pragma unroll
-                for (int l = 0; l < CPL; ++l) {
-                    s1r[l] += del[l];
-                    s2r[l] += del[l] * del[l];
-                }
-            } else if (moments) {
-#pragma unroll
-                for (int l = 0; l < CPL; ++l)
-                    if (rod.own && l < rod.nc) {
-                        const int64_t i = d.off + CPL * rod.unit + l;
-                        st.s1[i] += del[l];
-                        st.s2[i] += del[l] * del[l];
-                    }
-            }
-            ++nsamp;
-            if (corr && row == kCorrBlock - 1) {
-                __threadfence_block();
-                inst_sync(mflag, lw, nw, ++mseq);
-                xtx_block<T>(X, st.c + d.c_off, N, lw, nw);
-                inst_sync(mflag, lw, nw, ++mseq);
-            }
+            if (pend && finish()) return;
+            begin();
         }
     }
+    if (STATS && pend && finish()) return;
 
 #pragma unroll
     for (int l = 0; l < CPL; ++l)
         if (rod.own && l < rod.nc) {
             const int64_t i = CPL * rod.unit + l;
             gU[i] = u[l];
-            if constexpr (STATS && kRegSums) {
+            if constexpr (kRegSums) {
                 if (moments) {
                     st.s1[d.off + i] = s1r[l];
                     st.s2[d.off + i] = s2r[l];
@@ -764,15 +807,16 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
 }
 
 // CMAX: the largest cells per lane of the batch's waves: 4 alone, 4 and 8
-// side by side, or 16 alone.  The plain FP32 kernels hold 32 and 47 VGPRs; they
-// are kept to eight waves per SIMD, two workgroups of 1024 threads on a CU.
-template <typename T, int CMAX, bool STATS, int MODE>
+// side by side, or 16 alone.  The FP32 kernels of one equation without the
+// covariance are kept to eight waves per SIMD (64 VGPRs), two workgroups of 1024
+// threads on a CU.
+template <typename T, int CMAX, int STATS, int MODE>
 constexpr int rods_occupancy()
 {
-    return std::is_same<T, float>::value && !STATS && MODE >= 3 && CMAX <= 8 ? 8 : 4;
+    return std::is_same<T, float>::value && STATS < 2 && MODE >= 3 && CMAX <= 8 ? 8 : 4;
 }
 
-template <typename T, int CMAX, bool STATS, int MODE>
+template <typename T, int CMAX, int STATS, int MODE>
 __global__ void __launch_bounds__(1024, (rods_occupancy<T, CMAX, STATS, MODE>()))
     k_rods(const Inst1D *__restrict__ tab, const Seg1D *__restrict__ segs, T *__restrict__ pool,
            const T *__restrict__ coef, int64_t step0, int32_t nsteps, int64_t burn_in, int32_t every, uint32_t mask,
@@ -1169,7 +1213,7 @@ __global__ void __launch_bounds__(512, CPL == 8 ? 2 : 4)
 
 // ------------------------------------------------------------------ typed launchers
 
-template <typename T, bool STATS, int MODE>
+template <typename T, int STATS, int MODE>
 static hipError_t rods_m(const Launch1D &a)
 {
 #define SHE_RODS(C)                                                                                              \
@@ -1219,7 +1263,15 @@ template <typename T, int MODE, bool AHEAD>
 hipError_t rods_t(const Launch1D &a)
 {
     if constexpr (AHEAD) return a.stats ? ahead_m<T, true, MODE>(a) : ahead_m<T, false, MODE>(a);
-    else return a.stats ? rods_m<T, true, MODE>(a) : rods_m<T, false, MODE>(a);
+    else if (!a.stats) return rods_m<T, 0, MODE>(a);
+    // Per-cell sums in registers pay while the whole batch is resident at the four
+    // waves per SIMD they leave (256 CUs of 1024 threads): N = 3967 x 256 FE FP32
+    // with a sample every ten steps 1.17 us/step, 1.26 with the sums in memory; but
+    // 4000 x 300 PC 2.88 in two rounds against 2.65.  FP64 spills them either way
+    // (3967 x 256 PC 3.28 against 2.94) and always takes the memory form.
+    else if (a.mask & 0x12u) return rods_m<T, 2, MODE>(a);
+    else if (std::is_same<T, float>::value && (int64_t)a.n_blocks * a.block <= 256 * 1024) return rods_m<T, 2, MODE>(a);
+    else return rods_m<T, 1, MODE>(a);
 }
 
 }  // namespace she

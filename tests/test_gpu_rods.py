@@ -94,6 +94,29 @@ def test_samples_do_not_depend_on_the_launches(she, n):
                 np.testing.assert_array_equal(x[key], y[key])
 
 
+def test_moments_in_registers_and_in_memory(she):
+    """A batch that fills more than one workgroup per CU keeps its per-cell sums
+    in memory, a small one in registers: the same FP64 sums of the same values
+    in the same order, samples up to the last step of a call."""
+    insts = [W.instance((n,), bc=bc, scheme=scheme, r=0.1, eps=1e-2, u0=1.0, u_left=1.0 + 0.1 * bc,
+                        u_right=1.0 - 0.1 * bc, init_sd=0.1, seed=3, realisation=q)
+             for q, (n, bc, scheme) in enumerate([(3967, 1, 0), (3967, 0, 1), (257, 1, 1), (4100, 0, 0)] * 129)]
+    kw = dict(precision=0, sample_every=3, burn_in=0, stats=she.STAT_MOMENTS | she.STAT_SPATIAL)
+    with she.Handle([gpu_instance(she, i) for i in insts], **kw) as a, \
+            she.Handle([gpu_instance(she, i) for i in insts[:4]], **kw) as b:
+        for h in (a, b):
+            for k in (1, 2, 27, 33):
+                h.run(k)
+        for q in range(4):
+            np.testing.assert_array_equal(a.read_field(q), b.read_field(q))
+            x, y = a.stats(q), b.stats(q)
+            assert x["n_samples"] == y["n_samples"] == 21
+            for key in ("mean", "var"):
+                np.testing.assert_array_equal(x[key], y[key])
+            # the order over cells follows the work split: 2 x 4100 x 2^-53, doubled
+            assert abs(x["spatial_var"] / y["spatial_var"] - 1) <= 2e-12
+
+
 # one wave per rod up to 512 cells (1, 2, 4, 8 cells per lane, full and not);
 # 513: the kernel of longer implicit rods.  r = 0.01: two levels of the
 # reduction matter, r = 300: all of them
