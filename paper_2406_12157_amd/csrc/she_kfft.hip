@@ -25,7 +25,7 @@
 //    lo(kx, b) the first |ky| in shell b: (2b-1)^2 <= 4(kx^2 + ky^2), exact in
 //    integers (a table built once per handle).  Only shells
 //    kx .. round(sqrt(kx^2 + (Ny/2)^2)) meet column kx.  The waves' shell sums
-//    are added in a fixed order into one partial per block.  The first block
+//    are added in a fixed order into one partial per block.  The last block
 //    of each instance also does the sample's spatial reduction (one wave, the
 //    same fixed-order sum as k_reduce_parts); k_bins_reduce, which follows,
 //    reads the sample counts it updates.
@@ -78,7 +78,7 @@ constexpr int row_waves()
         if (!sample_) return; /* a non-sample step of a captured graph */                           \
     } while (0)
 
-// grid: (ceil(ny/2 / (W S)), n_inst); block 64 W; LDS: pass twiddles + W regions.
+// grid: (ceil(ny/2 / (W S)), n_inst); block 64 W (W a power of two); LDS: pass twiddles + W regions.
 template <typename T, int LGX>
 __global__ void __launch_bounds__(512)
     k_sk_rows(StepArg sarg, const T *__restrict__ field, int ny, const InstND *__restrict__ ip,
@@ -87,7 +87,8 @@ __global__ void __launch_bounds__(512)
 {
     SHE_SAMPLE_GATE();
     using F = WaveFft<LGX>;
-    constexpr int n = F::n, P = F::P, S = F::S, W = row_waves<T, LGX>();
+    constexpr int n = F::n, P = F::P, S = F::S;
+    const int W = blockDim.x >> 6;
     constexpr int LR = PassRadix<LGX>::LR, R = 1 << LR;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cplx<T> *tw = reinterpret_cast<cplx<T> *>(smem_raw);
@@ -120,10 +121,11 @@ __global__ void __launch_bounds__(512)
     __syncthreads();
     // column-tiled store: the block's rows of one tile are one contiguous run
     constexpr int nh = n / 2 + 1;
-    const int nrow = 2 * npairs, tcw = 1 << ltc;
+    // (2 npairs rows of 2^ltc columns: W S and ny / 2 are powers of two)
+    const int tcw = 1 << ltc, lt = 31 - __builtin_clz(npairs) + 1 + ltc;
     constexpr int lS = 31 - __builtin_clz(S);
-    for (int e = threadIdx.x; e < nkb * nrow * tcw; e += blockDim.x) {
-        const int t = e / (nrow * tcw), rest = e - t * (nrow * tcw);
+    for (int e = threadIdx.x; e < nkb << lt; e += blockDim.x) {
+        const int t = e >> lt, rest = e & ((1 << lt) - 1);
         const int rr = rest >> ltc, k = (t << ltc) + (rest & (tcw - 1));
         if (k >= nh) continue;
         const int pair = rr >> 1;
@@ -136,27 +138,27 @@ __global__ void __launch_bounds__(512)
     }
 }
 
-// LDS bytes per column group of the column transform: its transform region
-// and the FP64 prefix sums of one column (ppad layout).  A group of one
-// column (S = 1) holds the prefix sums in its transform region once the
-// transform has left it, so they need no room of their own.
-constexpr int col_region(int es, int lg)
-{
-    return es * wave_lds(lg) + (wave_seqs(lg) == 1 ? 0 : 8 * (((1 << lg) / 2 + 1) * 5 / 4 + 1));
-}
-
 // Index of |ky| = m in a column's prefix sums: one pad entry per four, so the
 // lanes' runs of four consecutive m fall in distinct banks.
-__device__ __forceinline__ int ppad(int m)
+__host__ __device__ constexpr int ppad(int m)
 {
     return m + (m >> 2);
+}
+
+// LDS bytes per column group of the column transform: its transform region.
+// The FP64 prefix sums of its columns (ppad layout) take the region's place
+// once the transform has left it.
+constexpr int col_region(int es, int lg)
+{
+    return es * wave_lds(lg);
 }
 
 // Shape of the tiled column transform: a tile of TC = CW CPW S columns by Ny
 // rows holds up to 32 KB of points, at most eight column groups (of S
 // columns); a block has CW <= 4 waves and each wave transforms CPW groups of
 // the tile in turn.  Wide tiles keep the row runs of the column-tiled half
-// spectrum at 64 bytes and more; small blocks keep the barriers cheap.
+// spectrum at 64 bytes and more; small blocks keep the barriers cheap.  A batch
+// of few tiles, which leaves SIMDs idle, takes a wave per group instead.
 template <typename T, int LGY>
 constexpr int colt_groups()
 {
@@ -264,6 +266,52 @@ __device__ __forceinline__ void col_power_prefix(const cplx<T> (&v)[WaveFft<LG>:
     if (lane == 63) pre[ppad(hy)] = excl + loc[Q];
 }
 
+// The same for the S columns of a group, transformed into the wave's region
+// `buf`, all at once: lane c L + q (L = 64 / S) takes the Q = P/2 = n/(2 L)
+// consecutive m from Q q on of column c (the column's last lane m = n/2 too) and
+// the L lane totals of a column are scanned together.  The prefix sums of column
+// c, from pre + c col_pre(LG) on, take the transform's place.
+constexpr int col_pre(int lg)
+{
+    return ppad((1 << lg) / 2) + 1;
+}
+
+template <typename T, int LG>
+__device__ __forceinline__ void cols_power_prefix(const cplx<T> *buf, double *pre, int lane)
+{
+    using F = WaveFft<LG>;
+    constexpr int n = F::n, hy = n / 2, S = F::S, L = 64 / S, Q = F::P / 2;
+    static_assert(S > 1 && L * Q == hy, "the lanes of a column hold half of it");
+    static_assert(S * col_pre(LG) * 8 <= col_region(sizeof(cplx<T>), LG), "the prefix sums fit the region");
+    const int q = lane & (L - 1), c = lane / L, base = c << LG;
+    double loc[Q + 1];
+    double run = 0.0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        const int m = Q * q + i;
+        const cplx<T> a = buf[pidx(base + m)], b = buf[pidx(base + ((n - m) & (n - 1)))];
+        const T ea = a.re * a.re + a.im * a.im, eb = m ? b.re * b.re + b.im * b.im : T(0);
+        run += static_cast<double>(ea) + static_cast<double>(eb);
+        loc[i] = run;
+    }
+    const cplx<T> z = buf[pidx(base + hy)];
+    loc[Q] = run + static_cast<double>(z.re * z.re + z.im * z.im);
+    double inc = run;
+    // (each move before its select: within a branch it would read idle lanes)
+    auto add = [&](double moved, int d) __attribute__((always_inline)) { inc += (q & 15) >= d ? moved : 0.0; };
+    if constexpr (L > 1) add(dpp_move<0x111, 0xf>(inc), 1);
+    if constexpr (L > 2) add(dpp_move<0x112, 0xf>(inc), 2);
+    if constexpr (L > 4) add(dpp_move<0x114, 0xf>(inc), 4);
+    if constexpr (L > 8) add(dpp_move<0x118, 0xf>(inc), 8);
+    if constexpr (L > 16) inc += dpp_move<0x142, 0xa>(inc);  // lane 15 of a row to the next, rows 1 and 3
+    const double excl = inc - run;
+    wave_sync();
+    double *pc = pre + c * col_pre(LG);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) pc[ppad(Q * q + i)] = excl + loc[i];
+    if (q == L - 1) pc[ppad(hy)] = excl + loc[Q];
+}
+
 // Adds column kx's power to the shell sums: lane b of group j takes shell
 // b = lane + 64 j, the range [first(b), first(b + 1)) of |ky| (from the shell
 // table, col = its row for kx), as pre[first(b + 1) - 1] - pre[first(b) - 1],
@@ -273,19 +321,30 @@ __device__ __forceinline__ void col_power_prefix(const cplx<T> (&v)[WaveFft<LG>:
 // b - 1's, moved one lane up; lane 0 takes those of lane 63 of the previous
 // group, and 0 for the first group met (its shells lie below kx, first = 0).
 // Only shells kx .. round(sqrt(kx^2 + hy^2)) (bound by excess) meet the column.
-template <int NBJ>
-__device__ __forceinline__ void bin_column(double (&acc)[NBJ], const double *pre, const uint16_t *__restrict__ col,
-                                           int kx, int nx, int nbins, int nbj, int hy, int lane)
+// The table's entries are loaded by bin_firsts, ahead of the column's turn.
+__device__ __forceinline__ int last_group(int kx, int hy)
 {
-    const double w = (kx == 0 || 2 * kx == nx) ? 0.25 : 0.5;
-    const int jlo = kx >> 6;
-    const int jhi = static_cast<int>(__builtin_amdgcn_sqrtf(static_cast<float>(kx * kx + hy * hy)) + 1.5f) >> 6;
-    int m1s[NBJ];
+    return static_cast<int>(__builtin_amdgcn_sqrtf(static_cast<float>(kx * kx + hy * hy)) + 1.5f) >> 6;
+}
+
+template <int NBJ>
+__device__ __forceinline__ void bin_firsts(int (&m1s)[NBJ], const uint16_t *__restrict__ col, int kx, int nbins, int nbj,
+                                           int hy, int lane)
+{
+    const int jlo = kx >> 6, jhi = last_group(kx, hy);
 #pragma unroll
     for (int j = 0; j < NBJ; ++j) {
         const int b = lane + 64 * j;
         m1s[j] = (j >= jlo && j <= jhi && j < nbj && b < nbins) ? static_cast<int>(col[b + 1]) : hy + 1;
     }
+}
+
+template <int NBJ>
+__device__ __forceinline__ void bin_column(double (&acc)[NBJ], const double *pre, const int (&m1s)[NBJ], int kx, int nx,
+                                           int nbins, int nbj, int hy, int lane)
+{
+    const double w = (kx == 0 || 2 * kx == nx) ? 0.25 : 0.5;
+    const int jlo = kx >> 6, jhi = last_group(kx, hy);
     int carry = 0, clo = 0, chi = 0;
 #pragma unroll
     for (int j = 0; j < NBJ; ++j) {
@@ -312,27 +371,30 @@ __device__ __forceinline__ void bin_column(double (&acc)[NBJ], const double *pre
 // contiguous block of the column-tiled half spectrum) through registers into
 // the LDS regions of its NG column groups (the transpose), and wave w
 // transforms groups w CPW .. w CPW + CPW - 1 in turn.  LDS: pass twiddles,
-// then per group `rs` bytes: its columns' transform region, the FP64 prefix
-// sums of one column (within the transform region when S = 1), and (after
-// the loop, the first CW) the waves' shell sums.
-// Compiled for four waves per SIMD (128 VGPRs) where the FP32 transform fits
-// without spilling, else two.
-template <typename T, int LGY, int NBJ>
-__global__ void __launch_bounds__(256, (sizeof(T) == 4 && LGY <= 9) ? 4 : 2)
+// then per group `rs` bytes: its columns' transform region, then their FP64
+// prefix sums, and (after the loop, the first CW) the waves' shell sums.
+// On small grids the launch is one chain of latencies; the S columns of a group
+// are summed at once and the shell table's loads issued before the transform
+// (column by column, each with its own loads: 11.3 us at 128^2 x 1; now 7.4).
+template <typename T, int LGY, int NBJ, int CW>
+constexpr int colt_waves_per_simd()
+{
+    // four (128 VGPRs) or three where the FP32 transform fits without spilling
+    if (CW > 4 || sizeof(T) == 8 || LGY > 9) return 2;
+    return LGY == 8 || (LGY == 7 && NBJ > 6) ? 3 : 4;
+}
+
+template <typename T, int LGY, int NBJ, int CW>
+__global__ void __launch_bounds__(64 * CW, (colt_waves_per_simd<T, LGY, NBJ, CW>()))
     k_sk_colt(StepArg sarg, const cplx<T> *__restrict__ half, int nx, int nkb, int iters, int rs, int nbins,
               const cplx<T> *__restrict__ twy, const uint16_t *__restrict__ shells, double *__restrict__ part,
               SpatialParts sp)
 {
     SHE_SAMPLE_GATE();
-    // the sample's spatial reduction of this instance, when it rides along
-    // (one wave of the instance's first block; the shell reduction that
-    // follows reads what it wrote)
-    if (sp.part && blockIdx.x == 0 && threadIdx.x < 64) reduce_spatial_wave(sp, blockIdx.y, threadIdx.x);
     using F = WaveFft<LGY>;
     constexpr int n = F::n, P = F::P, S = F::S, hy = n / 2;
     constexpr int LR = PassRadix<LGY>::LR, R = 1 << LR;
-    constexpr int CW = colt_waves<T, LGY>(), NG = colt_groups<T, LGY>(), CPW = NG / CW, TC = NG * S;
-    constexpr int per = (hy + 1 + 63) >> 6;
+    constexpr int NG = colt_groups<T, LGY>(), CPW = NG / CW, TC = NG * S;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cplx<T> *tw = reinterpret_cast<cplx<T> *>(smem_raw);
     unsigned char *regions = smem_raw + sizeof(cplx<T>) * F::tw;
@@ -401,12 +463,29 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 && LGY <= 9) ? 4 : 2)
         fetch(cb);
         stash();
         __syncthreads();
+        // the sample's spatial reduction of this instance, when it rides along:
+        // the last wave of the last block, whose tile ends with column nx / 2 and
+        // so mostly leaves that wave idle (the shell reduction that follows reads
+        // what it wrote)
+        if (sp.part && it == 0 && blockIdx.x == gridDim.x - 1 && wave == CW - 1) reduce_spatial_wave(sp, inst, lane);
         for (int cg = 0; cg < CPW; ++cg) {
             const int r = wave * CPW + cg;  // the column group's region
             cplx<T> *buf = reinterpret_cast<cplx<T> *>(regions + static_cast<size_t>(r) * rs);
-            double *pre = S == 1 ? reinterpret_cast<double *>(buf) : reinterpret_cast<double *>(buf + F::lds);
+            double *pre = reinterpret_cast<double *>(buf);
             const int g = cb + S * r;
             if (g < nh) {  // wave-uniform
+                // the shell table's rows of the first columns, needed after the
+                // transform: as many as fit the registers
+                constexpr int lim = CW > 4 ? 4 : NBJ > 6 ? 1 : 2, AH = S < lim ? S : lim;
+                constexpr bool early = CW > 4 || NBJ <= 6;
+                int m1s[AH][NBJ];
+                auto firsts = [&](int (&m)[NBJ], int kx) {
+                    if (kx < nh) bin_firsts<NBJ>(m, shells + kx * (nbins + 1), kx, nbins, nbj, hy, lane);
+                };
+                if constexpr (early) {
+#pragma unroll
+                    for (int a = 0; a < AH; ++a) firsts(m1s[a], g + a);
+                }
                 cplx<T> v[P];
 #pragma unroll
                 for (int i = 0; i < P / R; ++i) {
@@ -418,43 +497,26 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 && LGY <= 9) ? 4 : 2)
                     }
                 }
                 wave_sync();
-                if constexpr (S == 1) {
-                    // the transform stays in registers: lane l holds X(l + 64 j)
-                    wave_fft<T, LGY, LGY, true>(v, buf, tw, lane);
-                    col_power_prefix<T, LGY>(v, pre, lane);
-                    wave_sync();
-                    bin_column<NBJ>(acc, pre, shells + g * (nbins + 1), g, nx, nbins, nbj, hy, lane);
-                } else {
-                    wave_fft<T, LGY, LGY>(v, buf, tw, lane);
-                    for (int c = 0; c < S && g + c < nh; ++c) {
-                        const int kx = g + c;
-                        const cplx<T> *col = buf;
-                        const int cbase = c << LGY;
-                        double loc[per];
-                        double run = 0.0;
+                // S = 1: the transform stays in registers, lane l holds X(l + 64 j)
+                wave_fft<T, LGY, LGY, S == 1>(v, buf, tw, lane);
+                if constexpr (S == 1) col_power_prefix<T, LGY>(v, pre, lane);
+                else cols_power_prefix<T, LGY>(buf, pre, lane);
+                wave_sync();
+                if constexpr (!early) {
 #pragma unroll
-                        for (int j = 0; j < per; ++j) {
-                            // power at |ky| = m: X(m), plus X(-m) for 0 < m < hy; m > hy
-                            // is padding (both reads stay inside the column, masked after)
-                            const int m = lane * per + j;
-                            const cplx<T> a = col[pidx(cbase + min(m, hy))];
-                            const cplx<T> b = col[pidx(cbase + ((n - m) & (n - 1)))];
-                            const T ea = m <= hy ? a.re * a.re + a.im * a.im : T(0);
-                            const T eb = (m != 0 && m < hy) ? b.re * b.re + b.im * b.im : T(0);
-                            run += static_cast<double>(ea) + static_cast<double>(eb);
-                            loc[j] = run;
-                        }
-                        const double excl = wave_inclusive_sum(run) - run;
+                    for (int a = 0; a < AH; ++a) firsts(m1s[a], g + a);
+                }
+                for (int c0 = 0; c0 < S && g + c0 < nh; c0 += AH) {
 #pragma unroll
-                        for (int j = 0; j < per; ++j) {
-                            const int m = lane * per + j;
-                            if (m <= hy) pre[ppad(m)] = excl + loc[j];
+                    for (int a = 0; a < AH; ++a) {
+                        const int kx = g + c0 + a;
+                        if (kx < nh) {
+                            bin_column<NBJ>(acc, pre + (c0 + a) * col_pre(LGY), m1s[a], kx, nx, nbins, nbj, hy, lane);
+                            if (c0 + AH < S) firsts(m1s[a], kx + AH);
                         }
-                        wave_sync();
-                        bin_column<NBJ>(acc, pre, shells + kx * (nbins + 1), kx, nx, nbins, nbj, hy, lane);
-                        wave_sync();
                     }
                 }
+                wave_sync();
             }
         }
         __syncthreads();  // the regions take the next tile
@@ -481,7 +543,10 @@ __global__ void __launch_bounds__(256)
     SHE_SAMPLE_GATE();
     const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (e >= static_cast<int64_t>(n_inst) * nbins) return;
-    const int inst = static_cast<int>(e / nbins), b = static_cast<int>(e - static_cast<int64_t>(inst) * nbins);
+    // (a 64-bit division costs this short kernel a fifth of its time)
+    const int inst = static_cast<int>(e >> 32 ? static_cast<uint64_t>(e) / static_cast<unsigned>(nbins)
+                                              : static_cast<uint32_t>(e) / static_cast<uint32_t>(nbins));
+    const int b = static_cast<int>(e - static_cast<int64_t>(inst) * nbins);
     const InstAcc q = acc[inst];
     if (q.nonfinite) return;
     const double *pp = part + static_cast<int64_t>(inst) * ngroups * nbins + b;
@@ -550,6 +615,16 @@ int tile_cols(int prec, int lgy)
 #undef SHE_TC
 }
 
+// A wave per column group (eight waves per block instead of four with two
+// groups each) where the blocks would give a CU two at most.  Measured with the
+// whole S(k) of a sample, us, eight waves against four: 128^2 x 1 12.7 / 16.6,
+// 256^2 x 16 17.1 / 19.8, 256^2 x 64 (576 blocks) 24.6 / 24.4, 512^2 x 64 57.3 / 55.2, 128^2 x 256 (768
+// blocks) 33.1 / 28.3, 16^2 x 4096 88 / 65.
+bool colt_wide(int groups, int n_inst)
+{
+    return static_cast<int64_t>(groups) * n_inst <= 512;
+}
+
 // Tiles per column-transform block: at least about 4096 blocks over the
 // batch (four resident per CU, so about four rounds).  Measured at
 // 512 x 512 x 256 (8448 tiles), us per sample: 1 tile per block 103.4, 2
@@ -599,11 +674,15 @@ void rows_t(hipStream_t s, const StepArg &sa, int n_inst, int ny, const InstND *
             void *half, int ltc, int nkb)
 {
     using F = WaveFft<LGX>;
-    constexpr int W = row_waves<T, LGX>();
-    const int pairs = W * F::S;
-    const dim3 grid((ny / 2 + pairs - 1) / pairs, n_inst);
+    constexpr int Wmax = row_waves<T, LGX>();
+    static_assert(sizeof(cplx<T>) * (F::tw + Wmax * F::lds) <= kLdsBudget, "row transform exceeds the LDS budget");
+    // fewer waves per block where that puts them on more CUs (128^2 alone, 16
+    // blocks of one wave: 5.9 us; two of eight: 7.3)
+    int W = Wmax;
+    auto blocks = [&](int w) { return (ny / 2 + w * F::S - 1) / (w * F::S); };
+    while (W > 1 && static_cast<int64_t>(blocks(W)) * n_inst < 256) W /= 2;
+    const dim3 grid(blocks(W), n_inst);
     const size_t smem = sizeof(cplx<T>) * (F::tw + static_cast<size_t>(W) * F::lds);
-    static_assert(sizeof(cplx<T>) * (F::tw + W * F::lds) <= kLdsBudget, "row transform exceeds the LDS budget");
     hipLaunchKernelGGL((k_sk_rows<T, LGX>), grid, dim3(64 * W), smem, s, sa, static_cast<const T *>(field), ny, ip,
                        static_cast<const cplx<T> *>(twx), static_cast<cplx<T> *>(half), ltc, nkb);
 }
@@ -615,15 +694,20 @@ bool cols_t(hipStream_t s, const StepArg &sa, int n_inst, int nx, int nkb, int n
     size_t rs = 0;
     const size_t smem = colt_lds<T, LGY>(nbins, &rs);
     if (smem > kLdsBudget) return false;
-    const dim3 grid(groups, n_inst), block(64 * colt_waves<T, LGY>());
-    if (nbins <= 64 * (kMaxBinIters / 2))
-        hipLaunchKernelGGL((k_sk_colt<T, LGY, kMaxBinIters / 2>), grid, block, smem, s, sa,
-                           static_cast<const cplx<T> *>(half), nx, nkb, iters, static_cast<int>(rs), nbins,
-                           static_cast<const cplx<T> *>(twy), shells, part, sp);
-    else
-        hipLaunchKernelGGL((k_sk_colt<T, LGY, kMaxBinIters>), grid, block, smem, s, sa,
-                           static_cast<const cplx<T> *>(half), nx, nkb, iters, static_cast<int>(rs), nbins,
-                           static_cast<const cplx<T> *>(twy), shells, part, sp);
+    const dim3 grid(groups, n_inst);
+    auto run = [&](auto kernel, int cw) {
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * cw), smem, s, sa, static_cast<const cplx<T> *>(half), nx, nkb, iters,
+                           static_cast<int>(rs), nbins, static_cast<const cplx<T> *>(twy), shells, part, sp);
+    };
+    constexpr int CW = colt_waves<T, LGY>(), NG = colt_groups<T, LGY>();
+    const bool few = nbins <= 64 * (kMaxBinIters / 2);
+    if (colt_wide(groups, n_inst)) {
+        if (few) run(k_sk_colt<T, LGY, kMaxBinIters / 2, NG>, NG);
+        else run(k_sk_colt<T, LGY, kMaxBinIters, NG>, NG);
+    } else {
+        if (few) run(k_sk_colt<T, LGY, kMaxBinIters / 2, CW>, CW);
+        else run(k_sk_colt<T, LGY, kMaxBinIters, CW>, CW);
+    }
     return true;
 }
 
