@@ -258,6 +258,29 @@ struct InstND {
 
 // Parameters of a 2D/3D batch: one grid, equation, scheme, noise mode and
 // seed; r, u0, eps, init_sd and the realisation per instance (InstND).
+// Exact quotients by a divisor fixed for the launch, n / d for any 32-bit n: one
+// high product, an add and two shifts (Granlund and Montgomery, Division by
+// invariant integers using multiplication, 1994), where the machine has no
+// integer division.
+struct FastDiv {
+    uint32_t d, mul;
+    int32_t s1, s2;
+};
+
+inline FastDiv fast_div(uint32_t d)
+{
+    int l = 0;
+    while ((1ull << l) < d) ++l;
+    return FastDiv{d, static_cast<uint32_t>((((1ull << l) - d) << 32) / d + 1), l > 1 ? 1 : l, l > 1 ? l - 1 : 0};
+}
+
+__host__ __device__ __forceinline__ int quotient(int n, const FastDiv &f)
+{
+    const uint32_t u = static_cast<uint32_t>(n);
+    const uint32_t t = static_cast<uint32_t>((static_cast<uint64_t>(f.mul) * u) >> 32);
+    return static_cast<int>((t + ((u - t) >> f.s1)) >> f.s2);
+}
+
 struct ParamsND {
     int32_t nx, ny, nz;     // nz = 1 in 2D
     int32_t dim;
@@ -267,6 +290,9 @@ struct ParamsND {
     int32_t xcd_order;      // 1: give each XCD a contiguous range of workgroups
     uint64_t seed;
     const InstND *ip;       // device, n_inst
+    // of a step launch (launch_step2d, launch_step3d): lanes per row, marches
+    // (2D) or tiles (3D) per instance, tiles along y (3D)
+    FastDiv by_lx, by_parts, by_yt;
 };
 
 // Step index and sampling decision of one 2D/3D step.  Launched directly,

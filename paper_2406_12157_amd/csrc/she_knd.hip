@@ -30,23 +30,30 @@ hipError_t launch_step2d(int prec, int cx, int eq, int scheme, int n_blocks, hip
                          const void *src, void *dst, const StepArg &sa, double *part, InstAcc *acc,
                          const SkRows *skr)
 {
-    if (prec == 0) return step2d_c<float>(cx, eq, scheme, n_blocks, s, p, src, dst, sa, part, acc, skr);
-    return step2d_c<double>(cx, eq, scheme, n_blocks, s, p, src, dst, sa, part, acc, skr);
+    ParamsND q = p;
+    q.by_lx = fast_div(p.nx / cx);
+    q.by_parts = fast_div((p.ny + p.chunk - 1) / p.chunk);
+    if (prec == 0) return step2d_c<float>(cx, eq, scheme, n_blocks, s, q, src, dst, sa, part, acc, skr);
+    return step2d_c<double>(cx, eq, scheme, n_blocks, s, q, src, dst, sa, part, acc, skr);
 }
 
 hipError_t launch_step3d(int prec, int cx, int eq, int stage, int ty, int n_blocks, size_t smem, hipStream_t s,
                          const ParamsND &p, const void *src, const void *base, void *dst, const StepArg &sa,
                          double *part, InstAcc *acc)
 {
+    ParamsND q = p;
+    q.by_lx = fast_div(p.nx / cx);
+    q.by_yt = fast_div(p.ny / ty);
+    q.by_parts = fast_div(q.by_yt.d * ((p.nz + p.chunk - 1) / p.chunk));
     if (prec == 0) {
-        if (cx == 4) return step3d_e<float, 4>(eq, stage, ty, n_blocks, smem, s, p, src, base, dst, sa, part, acc);
-        if (cx == 8) return step3d_e<float, 8>(eq, stage, ty, n_blocks, smem, s, p, src, base, dst, sa, part, acc);
-        if (cx == 16) return step3d_e<float, 16>(eq, stage, ty, n_blocks, smem, s, p, src, base, dst, sa, part, acc);
+        if (cx == 4) return step3d_e<float, 4>(eq, stage, ty, n_blocks, smem, s, q, src, base, dst, sa, part, acc);
+        if (cx == 8) return step3d_e<float, 8>(eq, stage, ty, n_blocks, smem, s, q, src, base, dst, sa, part, acc);
+        if (cx == 16) return step3d_e<float, 16>(eq, stage, ty, n_blocks, smem, s, q, src, base, dst, sa, part, acc);
     } else {
-        if (cx == 4) return step3d_e<double, 4>(eq, stage, ty, n_blocks, smem, s, p, src, base, dst, sa, part, acc);
-        if (cx == 8) return step3d_e<double, 8>(eq, stage, ty, n_blocks, smem, s, p, src, base, dst, sa, part, acc);
+        if (cx == 4) return step3d_e<double, 4>(eq, stage, ty, n_blocks, smem, s, q, src, base, dst, sa, part, acc);
+        if (cx == 8) return step3d_e<double, 8>(eq, stage, ty, n_blocks, smem, s, q, src, base, dst, sa, part, acc);
         if (cx == 16)
-            return step3d_e<double, 16>(eq, stage, ty, n_blocks, smem, s, p, src, base, dst, sa, part, acc);
+            return step3d_e<double, 16>(eq, stage, ty, n_blocks, smem, s, q, src, base, dst, sa, part, acc);
     }
     return hipErrorInvalidValue;
 }
