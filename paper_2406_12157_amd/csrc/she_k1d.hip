@@ -275,7 +275,7 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
                     }
                 }
 #pragma unroll
-                for (int l = 0; l < 4; ++l) dv[s][l] = Wc[4 * g + l] * (F[l + 1] - F[l]);
+                for (int l = 0; l < 4; ++l) dv[s][l] = cell_flux(Wc[4 * g + l], F[l + 1] - F[l]);
             }
         };
         switch (kind) {

@@ -168,6 +168,17 @@ __device__ __forceinline__ double of_lane(double v, int lane)
     return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
 }
 
+// A cell's flux divergence with its capacity factor, rounded by itself.  Left to
+// the compiler, the product contracts with the sum that takes it wherever the two
+// end up in one basic block, so that a composite rod's last bits depended on the
+// kernel and even on the wave that held the cell.
+template <typename T>
+__device__ __forceinline__ T cell_flux(T w, T d)
+{
+#pragma clang fp contract(off)
+    return w * d;
+}
+
 // c ? a : b on values: a select between array elements as lvalues would become
 // an address select and move the array to private memory.
 template <typename T>
@@ -383,7 +394,7 @@ struct Rod {
             for (int l = 1; l < CPL; ++l) F[l] = sel(lane == lg && l == m, Fr, F[l]);
         }
 #pragma unroll
-        for (int l = 0; l < CPL; ++l) dv[l] = VARC ? Wc[VARC ? l : 0] * (F[l + 1] - F[l]) : F[l + 1] - F[l];
+        for (int l = 0; l < CPL; ++l) dv[l] = VARC ? cell_flux(Wc[VARC ? l : 0], F[l + 1] - F[l]) : F[l + 1] - F[l];
     }
 
     template <int E>
