@@ -47,8 +47,9 @@ struct she_handle {
     // 1D
     Inst1D *d_tab = nullptr;
     Seg1D *d_segs = nullptr;      // per wave of the 1D launch
-    std::vector<Seg1D> segs_host;
-    int blocks1d = 0;             // workgroups of the 1D launch
+    std::vector<Seg1D> segs_host;  // of the wave kernels' launch, then of the barrier kernel's
+    int blocks1d = 0;             // workgroups of the barrier kernel's launch (0: none)
+    size_t rod_segs = 0;          // entries of the wave kernels' launch
     int mode1d = 0;               // kernel mode (see launch_step1d)
     void *d_pool = nullptr;
     std::vector<Inst1D> tab;
@@ -72,10 +73,11 @@ struct she_handle {
     std::vector<double> pcr_host;     // implicit schemes: FP64 reduction factors
     double *d_pcr = nullptr;
     size_t smem1d = 0;
-    // explicit batches: the wave kernels' shape (Launch1D)
-    bool rods = false;
-    int rod_block = 64, rod_cpl = 4;
+    // the wave kernels' shape (Launch1D; rod_blocks 0: no launch)
+    int rod_blocks = 0, rod_block = 64, rod_cpl = 4;
+    size_t rod_smem = 0;
     int32_t rod_ahead = 0, rod_zrow = 0, rod_slots = 0;
+    bool rod_mixed = false;
 
     // batch means: samples per batch (0: none) and their arrays
     int32_t batch_len = 0;
@@ -593,25 +595,23 @@ she_status validate(const she_config *cfg, she_handle *h)
 
 // ------------------------------------------------------------------ create
 
-// Instances take whole waves (as many as they have Philox blocks, up to the
+// The instances idx take whole waves (as many as they have Philox blocks, up to the
 // workgroup) and are packed first-fit, largest first, into workgroups of
 // block / 64 waves and at most 64 KB of LDS.  Returns an error text, or null.
 static constexpr int kLdsCap1D = 64 * 1024;
 static const char *const kLdsWhy1D = "1D instance too large for LDS (64 KB per workgroup)";
 
-static const char *pack_1d(const std::vector<Inst1D> &tab, int block, int32_t es, std::vector<Seg1D> &segs,
-                           int &n_blocks, size_t &smem, int cus)
+static const char *pack_1d(const std::vector<Inst1D> &tab, std::vector<int> idx, int block, int32_t es,
+                           std::vector<Seg1D> &segs, int &n_blocks, size_t &smem, int cus)
 {
     const int W = block / 64;
-    const int n_inst = static_cast<int>(tab.size());
-    std::vector<int> nw(n_inst), bytes(n_inst), idx(n_inst);
-    for (int i = 0; i < n_inst; ++i) {
+    std::vector<int> nw(tab.size()), bytes(tab.size());
+    for (int i : idx) {
         const int n = tab[i].n, nf = tab[i].bc == SHE_DIRICHLET ? n + 1 : n;
         const int nfg = (nf + 3) / 4;
         nw[i] = std::min(W, (nfg + 63) / 64);
         bytes[i] = seg_lds(n, nf, es, 2).total;
         if (bytes[i] > kLdsCap1D) return kLdsWhy1D;
-        idx[i] = i;
     }
     std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) {
         if (nw[a] != nw[b]) return nw[a] > nw[b];
@@ -676,12 +676,10 @@ static int device_cus()
     return cus;
 }
 
-// Cells per lane of a rod whose state one wave holds.
-static int rod_cells_per_lane(int n) { return n <= 64 ? 1 : (n <= 128 ? 2 : (n <= 256 ? 4 : 8)); }
-
-// Shape of a batch on the wave kernels (she_step_1d.hpp).
+// Shape of the launch of instances idx on the wave kernels (she_step_1d.hpp): all
+// of an explicit batch, those of up to kRodAlone cells of one with implicit rods.
 //
-// Instances of up to 256 cells (512 in a batch with implicit ones): one
+// Instances of up to 256 cells (kRodAlone in a batch with implicit ones): one
 // workgroup each, wave 0 advancing the state with 1, 2, 4 or 8 cells per lane and
 // the others drawing the numbers ahead.
 //
@@ -690,22 +688,26 @@ static int rod_cells_per_lane(int n) { return n <= 64 ? 1 : (n <= 128 ? 2 : (n <
 // periodic rod whose last unit is not full).  Where 16 waves would not hold the
 // instance, some of its middle waves take 8 cells per lane, and where that does
 // not either, all take 16.
-static void plan_rods(she_handle *h, int block_threads)
+static void plan_rods(she_handle *h, std::vector<int> idx, int block_threads)
 {
-    const int cus = device_cus();
+    const int cus = device_cus(), n_idx = static_cast<int>(idx.size());
     const int32_t es = static_cast<int32_t>(h->esz);
-    h->rods = true;
-    if (h->mode1d == 2 || (h->nmax <= 256 && block_threads != 64)) {
-        h->rod_cpl = rod_cells_per_lane(h->nmax);
-        int nf = 0;
-        for (const Inst1D &t : h->tab) nf = std::max(nf, t.bc == SHE_DIRICHLET ? t.n + 1 : t.n);
+    int longest = 0, nf = 0;
+    for (int i : idx) {
+        const Inst1D &t = h->tab[i];
+        longest = std::max(longest, t.n);
+        nf = std::max(nf, t.bc == SHE_DIRICHLET ? t.n + 1 : t.n);
+    }
+    if (h->mode1d == 2 || (longest <= 256 && block_threads != 64)) {
+        h->rod_cpl = rod_cells_per_lane(longest);
         h->rod_zrow = (nf + 3) & ~3;
-        int waves = block_threads > 0 ? std::min(8, block_threads / 64) : (h->prec == SHE_F32 ? 4 : 8);
-        if (block_threads == 0 && h->n_inst > 2 * cus) waves = 4;
+        // (block_threads = 64, implicit: two waves, one to draw the numbers)
+        int waves = block_threads > 0 ? std::max(2, std::min(8, block_threads / 64)) : (h->prec == SHE_F32 ? 4 : 8);
+        if (block_threads == 0 && n_idx > 2 * cus) waves = 4;
         h->rod_block = 64 * waves;
         // chunk length: as many steps as the LDS allows beside the batch's other
         // workgroups of the CU
-        const size_t cap = h->n_inst > cus ? 36 * 1024 : 60 * 1024;
+        const size_t cap = n_idx > cus ? 36 * 1024 : 60 * 1024;
         for (int K = 32;; K /= 2) {
             const int slots = h->mask ? (K + h->every - 1) / h->every : 0;
             const size_t b = 16 + static_cast<size_t>(es) * (2 * static_cast<size_t>(K) * h->rod_zrow + 64 * h->rod_cpl + 4 +
@@ -713,16 +715,21 @@ static void plan_rods(she_handle *h, int block_threads)
             if (b <= cap || K == 2) {
                 h->rod_ahead = K;
                 h->rod_slots = slots;
-                h->smem1d = b;
+                h->rod_smem = b;
                 break;
             }
         }
-        h->blocks1d = h->n_inst;
-        h->segs_host.assign(1, Seg1D{0, 0, 1, 0, h->rod_cpl, 0});
+        h->rod_blocks = n_idx;
+        h->segs_host.clear();
+        for (int i : idx) {
+            const int c = rod_cells_per_lane(h->tab[i].n);
+            h->segs_host.push_back(Seg1D{i, 0, 1, 0, c, 0});
+            h->rod_mixed = h->rod_mixed || (h->tab[i].scheme >= 2 && c != h->rod_cpl);
+        }
+        h->rod_segs = h->segs_host.size();
         return;
     }
-    const int n_inst = h->n_inst;
-    std::vector<int> nw(n_inst), nbig(n_inst, 0), idx(n_inst);
+    std::vector<int> nw(h->n_inst), nbig(h->n_inst, 0);
     auto waves_of = [&](const Inst1D &t, int c) {
         const bool dirichlet = t.bc == SHE_DIRICHLET;
         const int units = ((dirichlet ? t.n + 1 : t.n) + c - 1) / c;
@@ -731,7 +738,7 @@ static void plan_rods(she_handle *h, int block_threads)
         return ((dirichlet ? units - 2 : units) + cap - 1) / cap;
     };
     int cmax = 4, wmax = 1;
-    for (int i = 0; i < n_inst; ++i) {
+    for (int i : idx) {
         nw[i] = waves_of(h->tab[i], 4);
         if (nw[i] > 16) {
             const int blocks = ((h->tab[i].bc == SHE_DIRICHLET ? h->tab[i].n + 1 : h->tab[i].n) + 3) / 4;
@@ -743,14 +750,13 @@ static void plan_rods(she_handle *h, int block_threads)
         }
     }
     int64_t total = 0;
-    for (int i = 0; i < n_inst; ++i) {
+    for (int i : idx) {
         if (cmax == 16) {
             nw[i] = waves_of(h->tab[i], 16);
             nbig[i] = 0;
         }
         wmax = std::max(wmax, nw[i]);
         total += nw[i];
-        idx[i] = i;
     }
     int W = std::max(1, block_threads / 64);
     if (block_threads == 0) W = 4;
@@ -773,7 +779,7 @@ static void plan_rods(she_handle *h, int block_threads)
     std::vector<Bin> bins;
     const int rounds0 = static_cast<int>((total + static_cast<int64_t>(W) * cus - 1) / (static_cast<int64_t>(W) * cus));
     for (int rounds = std::max(1, rounds0);; ++rounds) {
-        const int ncu = std::min(cus, n_inst), nb = ncu * rounds;
+        const int ncu = std::min(cus, n_idx), nb = ncu * rounds;
         bins.assign(nb, Bin{});
         for (Bin &b : bins) b.seg.assign(W, Seg1D{-1, 0, 0, 0, 4, 0});
         std::vector<std::array<int64_t, 4>> simd(ncu, std::array<int64_t, 4>{});
@@ -825,8 +831,9 @@ static void plan_rods(she_handle *h, int block_threads)
     h->rod_block = 64 * W;
     h->rod_cpl = cmax;
     h->rod_ahead = 0;
-    h->blocks1d = static_cast<int>(bins.size());
-    h->smem1d = smem;
+    h->rod_blocks = static_cast<int>(bins.size());
+    h->rod_smem = smem;
+    h->rod_segs = h->segs_host.size();
 }
 
 static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
@@ -846,11 +853,6 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
         const int64_t per = std::max<int64_t>(64, std::min<int64_t>(4096, (int64_t(1) << 22) / std::max<int64_t>(1, cells)));
         h->hist_rows = static_cast<int32_t>(per + h->tc_lags);
     }
-    // a batch with implicit rods of at most 512 cells has one wave solve each of
-    // them (lane_cells cells per lane; 0: the barrier kernel)
-    int longest = 0;
-    for (int i = 0; i < h->n_inst; ++i) longest = std::max(longest, h->inst[i].n[0]);
-    const int lane_cells = longest <= 512 && cfg->block_threads != 64 ? rod_cells_per_lane(longest) : 0;
     int64_t ho = 0, to = 0;
     std::map<std::vector<double>, std::pair<int64_t, int32_t>> pcr_shared;  // matrix rows -> factor block
     for (int i = 0; i < h->n_inst; ++i) {
@@ -935,8 +937,8 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
                     q = beta / g;
                     sc = 1.0 / (1.0 + z[0] + q * z[N - 1]);
                 }
-                if (lane_cells) {
-                    t.pcr_levels = lane_factors(lo, di, up, z, q, sc, lane_cells, h->pcr_host);
+                if (N <= kRodAlone) {
+                    t.pcr_levels = lane_factors(lo, di, up, z, q, sc, rod_cells_per_lane(N), h->pcr_host);
                 } else {
                     t.pcr_levels = pcr_factors(lo, di, up, h->pcr_host);
                     if (per) {
@@ -967,11 +969,10 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
     h->c_elems = co;
     h->hist_elems = ho;
     h->tc_elems = to;
-    // Launch shape of the barrier kernel (implicit batches; its limits hold for
-    // all): threads per workgroup and Philox blocks per thread.  Auto: the
-    // smallest shape whose workgroup holds the largest instance with at most one
-    // block per thread up to 512 threads (64 x 1, 64 x 2, 256 x 1, 512 x 1), then
-    // 512 threads with 2 or 4 blocks each.
+    // Launch shape of the barrier kernel (its limits hold for all): threads per
+    // workgroup and Philox blocks per thread.  Auto: the smallest shape whose
+    // workgroup holds the largest instance with at most one block per thread up
+    // to 512 threads (256 x 1, 512 x 1), then 512 threads with 2 or 4 blocks each.
     // instantaneous noise and one equation throughout: a kernel for that face
     // path alone (mode 3, 4 or 5)
     bool one_kind = true;
@@ -1001,17 +1002,22 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
         return fail(nullptr, SHE_EUNSUPPORTED, "1D instance too large for the resident kernel at this block size");
     h->block1d = block;
     h->maxg = maxg;
-    if (mode == 2) {
-        const char *why =
-            pack_1d(h->tab, block, static_cast<int32_t>(es), h->segs_host, h->blocks1d, h->smem1d, device_cus());
-        if (why) return fail(nullptr, SHE_EUNSUPPORTED, why);
-    } else {
-        for (const Inst1D &t : h->tab)
-            if (seg_lds(t.n, t.bc == SHE_DIRICHLET ? t.n + 1 : t.n, static_cast<int32_t>(es), mode).total > kLdsCap1D)
-                return fail(nullptr, SHE_EUNSUPPORTED, kLdsWhy1D);
-        plan_rods(h, cfg->block_threads);
+    // A batch with implicit rods: those of at most kRodAlone cells are solved by one
+    // wave each, longer ones (of any scheme) run the barrier kernel.
+    std::vector<int> shorter, longer;
+    for (int i = 0; i < h->n_inst; ++i) (mode == 2 && h->tab[i].n > kRodAlone ? longer : shorter).push_back(i);
+    for (int i : shorter) {
+        const Inst1D &t = h->tab[i];
+        if (seg_lds(t.n, t.bc == SHE_DIRICHLET ? t.n + 1 : t.n, static_cast<int32_t>(es), mode).total > kLdsCap1D)
+            return fail(nullptr, SHE_EUNSUPPORTED, kLdsWhy1D);
     }
-    if (mode == 2 && lane_cells) plan_rods(h, cfg->block_threads);
+    if (!shorter.empty()) plan_rods(h, shorter, cfg->block_threads);
+    if (!longer.empty()) {
+        std::vector<Seg1D> segs;
+        const char *why = pack_1d(h->tab, longer, block, static_cast<int32_t>(es), segs, h->blocks1d, h->smem1d, device_cus());
+        if (why) return fail(nullptr, SHE_EUNSUPPORTED, why);
+        h->segs_host.insert(h->segs_host.end(), segs.begin(), segs.end());
+    }
 
     plan.add(reinterpret_cast<void **>(&h->d_tab), sizeof(Inst1D) * h->n_inst);
     plan.add(reinterpret_cast<void **>(&h->d_segs), sizeof(Seg1D) * h->segs_host.size());
@@ -1669,14 +1675,16 @@ static she_status advance(she_handle *h, int64_t nsteps, bool sampling)
                     fold = true;
                 }
             }
-            if (h->rods)
-                SHE_HIP(h, launch_rods(Launch1D{h->prec, h->mode1d, stats, h->blocks1d, h->rod_block, h->smem1d, s,
+            if (h->rod_blocks > 0) {
+                const int mode = h->mode1d == 2 && !h->varc ? 6 : h->mode1d;
+                SHE_HIP(h, launch_rods(Launch1D{h->prec, mode, stats, h->rod_blocks, h->rod_block, h->rod_smem, s,
                                                 h->d_tab, h->d_segs, h->d_pool, h->d_coef, h->d_pcr, h->steps,
                                                 static_cast<int32_t>(k), h->burn_in, h->every, h->mask, st, h->rod_cpl,
-                                                h->rod_ahead, h->rod_zrow, h->rod_slots}));
-            else
+                                                h->rod_ahead, h->rod_zrow, h->rod_slots, h->rod_mixed}));
+            }
+            if (h->blocks1d > 0)
                 SHE_HIP(h, launch_step1d(h->prec, h->block1d, h->maxg, stats, h->blocks1d, h->smem1d, s, h->d_tab,
-                                         h->d_segs, h->d_pool, h->d_coef, h->d_pcr, h->steps,
+                                         h->d_segs + h->rod_segs, h->d_pool, h->d_coef, h->d_pcr, h->steps,
                                          static_cast<int32_t>(k), h->burn_in, h->every, h->mask, st));
             const int64_t cnt = stats ? sampled_by(h->steps + k) - sampled_by(h->steps) : 0;
             if (tc && cnt > 0)

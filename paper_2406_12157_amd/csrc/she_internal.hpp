@@ -198,6 +198,11 @@ struct Seg1D {
                         // beside others with 4 (0: all alike)
 };
 
+// Rods of up to kRodAlone cells are advanced by one wave in a batch with implicit
+// ones; cells per lane of a rod whose state one wave holds.
+constexpr int kRodAlone = 512;
+__host__ __device__ constexpr int rod_cells_per_lane(int n) { return n <= 64 ? 1 : (n <= 128 ? 2 : (n <= 256 ? 4 : 8)); }
+
 // LDS bytes of one instance of an explicit batch served by nw waves: meeting
 // flags, the wave sums of a sample and the edge exchange (rod_waves).
 constexpr int rod_edge(int cpl) { return cpl > 8 ? 2 * cpl : 8; }  // two units of a wave at the ends
@@ -327,12 +332,15 @@ namespace she {
 // ---- launchers (defined next to their kernels) ----
 // One launch of an explicit 1D batch.  mode 0: uniform; 3, 4, 5: uniform with
 // instantaneous noise and of one equation; 1: some instance has material
-// coefficients (k_off >= 0 in `coef`); 2 (ahead only): some instance is implicit
-// (factors in `pcr`, lane_factors).
+// coefficients (k_off >= 0 in `coef`); 2 and 6 (ahead only): some instance is
+// implicit (factors in `pcr`, lane_factors), 2 with and 6 without material
+// coefficients.
 // ahead = 0: k_rods, segs holding n_blocks * block / 64 wave entries, cpl the
 // largest cells per lane (4, 8 or 16); ahead > 0: k_rods_ahead, one block per
-// instance with cpl (1, 2, 4, or in mode 2 also 8) cells per lane, chunks of `ahead` steps, rows of
-// zrow numbers and `slots` sampled states per chunk in LDS.
+// instance (modes 2 and 6: those named in segs, one entry per block) with cpl (1, 2,
+// 4, or in modes 2 and 6 also 8) cells per lane, or with `mixed` (modes 2 and 6) its
+// entry's cpl, at most the launch's; chunks of `ahead` steps, rows of zrow numbers and `slots`
+// sampled states per chunk in LDS.
 struct Launch1D {
     int prec;
     int mode;
@@ -353,10 +361,12 @@ struct Launch1D {
     Stats1D st;
     int cpl;
     int32_t ahead, zrow, slots;
+    bool mixed;
 };
 hipError_t launch_rods(const Launch1D &a);
-// Batches with an implicit instance: reduction factors in `pcr`; r_f, s_f, w_i
-// of every instance staged in LDS.  segs: n_blocks * block / 64 wave entries.
+// The instances above kRodAlone cells of a batch with an implicit one: reduction
+// factors in `pcr`; r_f, s_f, w_i of every instance staged in LDS.  segs: n_blocks *
+// block / 64 wave entries.
 hipError_t launch_step1d(int prec, int block, int maxg, bool stats, int n_blocks, size_t smem, hipStream_t s,
                          const Inst1D *tab, const Seg1D *segs, void *pool, const void *coef, const double *pcr,
                          int64_t step0, int32_t nsteps, int64_t burn_in, int32_t every, uint32_t mask, Stats1D st);

@@ -1,4 +1,4 @@
-// 1D batches: the step kernel of batches with implicit instances, the time
+// 1D batches: the step kernel of the long instances of batches with implicit ones, the time
 // correlation, initial state, finalisation, batch means and the verification
 // kernels.  Explicit batches step in she_step_1d.hpp, whose comment states the
 // scheme.
@@ -34,8 +34,9 @@ __device__ __forceinline__ T last_of(int m, T a0, T a1, T a2, T a3)
     return m >= 4 ? a3 : (m == 3 ? a2 : (m == 2 ? a1 : a0));
 }
 
-// Batches with an implicit instance (explicit and composite ones may be among
-// them; explicit batches run the wave kernels of she_step_1d.hpp).
+// The instances above kRodAlone cells of a batch with an implicit one (explicit and
+// composite ones may be among them; the others, and explicit batches, run the wave
+// kernels of she_step_1d.hpp).
 //
 // Thread t of an instance's waves owns Philox blocks g = t + s TS (s < MAXG,
 // TS the instance's thread count): the faces 4g..4g+3 and the cells 4g..4g+3,
@@ -911,12 +912,10 @@ static hipError_t step1d_t(bool stats, const Step1DLaunch &a)
 }
 
 // Launch shapes (threads per workgroup, Philox blocks per thread) the
-// planner chooses: 64 x {1, 2}, 256 x {1, 2}, 512 x {1, 2, 4}.
+// planner chooses: 256 x {1, 2}, 512 x {1, 2, 4}.
 template <typename T>
 static hipError_t step1d_p(int block, int maxg, bool stats, const Step1DLaunch &a)
 {
-    if (block == 64 && maxg == 1) return step1d_t<T, 64, 1>(stats, a);
-    if (block == 64 && maxg == 2) return step1d_t<T, 64, 2>(stats, a);
     if (block == 256 && maxg == 1) return step1d_t<T, 256, 1>(stats, a);
     if (block == 256 && maxg == 2) return step1d_t<T, 256, 2>(stats, a);
     if (block == 512 && maxg == 1) return step1d_t<T, 512, 1>(stats, a);
@@ -956,6 +955,12 @@ extern template hipError_t rods_t<double, 4, false>(const Launch1D &);
 extern template hipError_t rods_t<double, 4, true>(const Launch1D &);
 extern template hipError_t rods_t<double, 5, false>(const Launch1D &);
 extern template hipError_t rods_t<double, 5, true>(const Launch1D &);
+extern template hipError_t rods_t<float, 6, true>(const Launch1D &);
+extern template hipError_t rods_t<double, 6, true>(const Launch1D &);
+extern template hipError_t rods_mixed_t<float, 2>(const Launch1D &);
+extern template hipError_t rods_mixed_t<float, 6>(const Launch1D &);
+extern template hipError_t rods_mixed_t<double, 2>(const Launch1D &);
+extern template hipError_t rods_mixed_t<double, 6>(const Launch1D &);
 
 template <typename T>
 static hipError_t rods_p(const Launch1D &a)
@@ -964,10 +969,11 @@ static hipError_t rods_p(const Launch1D &a)
     switch (a.mode) {
     case 0: return ahead ? rods_t<T, 0, true>(a) : rods_t<T, 0, false>(a);
     case 1: return ahead ? rods_t<T, 1, true>(a) : rods_t<T, 1, false>(a);
-    case 2: return ahead ? rods_t<T, 2, true>(a) : hipErrorInvalidValue;
+    case 2: return !ahead ? hipErrorInvalidValue : (a.mixed ? rods_mixed_t<T, 2>(a) : rods_t<T, 2, true>(a));
     case 3: return ahead ? rods_t<T, 3, true>(a) : rods_t<T, 3, false>(a);
     case 4: return ahead ? rods_t<T, 4, true>(a) : rods_t<T, 4, false>(a);
     case 5: return ahead ? rods_t<T, 5, true>(a) : rods_t<T, 5, false>(a);
+    case 6: return !ahead ? hipErrorInvalidValue : (a.mixed ? rods_mixed_t<T, 6>(a) : rods_t<T, 6, true>(a));
     default: return hipErrorInvalidValue;
     }
 }

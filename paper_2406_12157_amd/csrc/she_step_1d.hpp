@@ -209,15 +209,21 @@ struct NoSolve {
     __device__ __forceinline__ void operator()(double (&)[C]) const {}
 };
 
+// Modes of a batch.  0: any uniform rods (the face kind is looked up in each
+// stage); 3, 4, 5: every rod uniform, with instantaneous noise and of one
+// equation, heat, Dean-Kawasaki or Burgers (one face path: fewer registers, no
+// branches); 1: material coefficients; 2 and 6: implicit rods among them, 2 with
+// and 6 without material coefficients (which take 6 registers per cell in FP64).
+// A rod has the same bits in every mode that holds it.
+constexpr bool material(int mode) { return mode == 1 || mode == 2; }
+constexpr bool implicit(int mode) { return mode == 2 || mode == 6; }
+constexpr bool one_face(int mode) { return mode >= 3 && mode <= 5; }
+
 // What one wave knows of its instance: the uniform parameters, the unit of
-// each lane and where the ends of the rod lie.  MODE 0: any uniform rod (the
-// face kind is looked up in each stage); 3, 4, 5: every rod uniform, with
-// instantaneous noise and of one equation, heat, Dean-Kawasaki or Burgers (one
-// face path: fewer registers, no branches); 1: material coefficients; 2: as 1,
-// with implicit rods among them.
+// each lane and where the ends of the rod lie.
 template <typename T, int CPL, int MODE>
 struct Rod {
-    static constexpr bool VARC = MODE == 1 || MODE == 2;
+    static constexpr bool VARC = material(MODE), IMPL = implicit(MODE);
     int N;
     bool dir;
     int eq, noise, kind;
@@ -232,7 +238,7 @@ struct Rod {
     bool left_wall;  // Dirichlet and lane 0 holds cell 0
     int lg, m;       // lane of the unit of the last cell (-1: not here), its cells
     bool partial;    // that unit is here and not full
-    T ex;            // MODE 2: weight 1 - theta of the state-dependent deterministic flux
+    T ex, rex;       // implicit: weight 1 - theta of the state-dependent deterministic flux; r of that
     T Rf[VARC ? CPL : 1], Sf[VARC ? CPL : 1], Wc[VARC ? CPL : 1];
 
     // Lane l holds unit first + l (wrapped on a periodic rod); lanes
@@ -273,7 +279,8 @@ struct Rod {
         }
         partial = lg >= 0 && m < CPL;
         T sw = static_cast<T>(d.sigma * 1.41421356237309504880), swR = sw, rl = r, rr = r;
-        ex = static_cast<T>(MODE == 2 && d.scheme >= 2 ? 1.0 - d.theta : 1.0);
+        ex = static_cast<T>(IMPL && d.scheme >= 2 ? 1.0 - d.theta : 1.0);
+        rex = r * ex;
         if constexpr (VARC) {
             const int nf = dir ? N + 1 : N;
             const T *k = d.k_off >= 0 ? coef + d.k_off : nullptr;
@@ -303,7 +310,7 @@ struct Rod {
     __device__ __forceinline__ int ends() const
     {
         if (!left_wall && lg < 0) return kInterior;
-        if (MODE < 3) return kAny;  // the mixed modes compile two loops only
+        if (!one_face(MODE)) return kAny;  // the mixed modes compile two loops only
         if (dir) return partial ? kAny : kWalls;
         return wrap1 && !partial ? kRing : (wrap1 || partial ? kAny : kInterior);
     }
@@ -311,7 +318,7 @@ struct Rod {
     template <int K>
     __device__ __forceinline__ T face(T lo, T hi, T z, int l, uint32_t &clamps) const
     {
-        const T rf = VARC ? Rf[VARC ? l : 0] : r;
+        const T rf = VARC ? Rf[VARC ? l : 0] : (IMPL ? rex : r);
         const T sf = VARC ? Sf[VARC ? l : 0] : sg;
         const T df = hi - lo;
         if constexpr (K == 0) {
@@ -363,14 +370,14 @@ struct Rod {
         T F[CPL + 1];
         // walls: F_0 = 2 r (U_0 - U_L) + sqrt 2 sigma A(U_L) N_0, mirrored at face N
         const bool wall0 = WALLS && left_wall && lane == 0;
-        if constexpr (WALLS && K == 0 && !VARC) {
+        if constexpr (WALLS && K == 0 && !VARC && !IMPL) {
             // the left wall is a face like any other but for its factors
             const T w = sel(wall0, ampL, hs * (left + V[0]));
             F[0] = fma(w, z[0], r0 * (V[0] - left));
         } else {
             F[0] = face<K>(left, V[0], z[0], 0, clamps);
             if (WALLS && left_wall) {
-                T w = rwL * ((MODE == 2 ? ex * V[0] : V[0]) - uL);
+                T w = rwL * ((IMPL ? ex * V[0] : V[0]) - uL);
                 if constexpr (K != 0 && K != 2) w = fma(-nu * uL, T(1) - uL, w);
                 w = fma(ampL, z[0], w);
                 F[0] = sel(wall0, w, F[0]);
@@ -380,7 +387,7 @@ struct Rod {
         for (int l = 1; l < CPL; ++l) F[l] = face<K>(V[l - 1], V[l], z[l], l, clamps);
         T Fr = F[0];
         if (E == kWalls || (E == kAny && dir)) {
-            T w = rwR * (uR - (MODE == 2 ? ex * lastv : lastv));
+            T w = rwR * (uR - (IMPL ? ex * lastv : lastv));
             if constexpr (K != 0 && K != 2) w = fma(-nu * uR, T(1) - uR, w);
             w = fma(ampR, zN, w);
             Fr = sel(lane == lg, w, from_right(w, F[0]));
@@ -401,7 +408,7 @@ struct Rod {
     __device__ __forceinline__ void stage(const T (&V)[CPL], const T (&z)[CPL], T zN, T (&dv)[CPL],
                                           uint32_t &clamps) const
     {
-        if constexpr (MODE >= 3) {
+        if constexpr (one_face(MODE)) {
             stage_k<E, MODE == 3 ? 0 : MODE - 2>(V, z, zN, dv, clamps);
         } else {
             switch (kind) {
@@ -446,15 +453,15 @@ struct Rod {
     {
         auto g = [&](auto e) __attribute__((always_inline)) {
             if (scheme == 0) f(e, std::integral_constant<int, 0>{});
-            else if (MODE != 2 || scheme == 1) f(e, std::integral_constant<int, 1>{});
-            else if constexpr (MODE == 2) f(e, std::integral_constant<int, 2>{});
+            else if (!IMPL || scheme == 1) f(e, std::integral_constant<int, 1>{});
+            else if constexpr (IMPL) f(e, std::integral_constant<int, 2>{});
         };
         const int e = ends();
         if (e == kInterior) {
             g(std::integral_constant<int, kInterior>{});
             return;
         }
-        if constexpr (MODE >= 3) {
+        if constexpr (one_face(MODE)) {
             if (e == kWalls) {
                 g(std::integral_constant<int, kWalls>{});
                 return;
@@ -763,7 +770,7 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
                 --left;
                 const uint64_t n = static_cast<uint64_t>(step0 + k);
                 T z[CPL];
-                if (MODE >= 3 || rod.noise != 2) {
+                if (one_face(MODE) || rod.noise != 2) {
 #pragma unroll
                     for (int s = 0; s < S; ++s) {
                         const Normals4<T> nz = block_normals<T, true>(static_cast<uint32_t>(S * rod.unit + s),
@@ -824,7 +831,7 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
 template <typename T, int CMAX, int STATS, int MODE>
 constexpr int rods_occupancy()
 {
-    return std::is_same<T, float>::value && STATS < 2 && MODE >= 3 && CMAX <= 8 ? 8 : 4;
+    return std::is_same<T, float>::value && STATS < 2 && one_face(MODE) && CMAX <= 8 ? 8 : 4;
 }
 
 template <typename T, int CMAX, int STATS, int MODE>
@@ -964,15 +971,13 @@ struct LaneSolve {
 // workgroups per CU on, VALU issue.  Four waves in FP32 draw faster than wave 0
 // steps; FP64 numbers take about four times as long, so it has eight.
 template <typename T, int CPL, bool STATS, int MODE>
-__global__ void __launch_bounds__(512, CPL == 8 ? 2 : 4)
-    k_rods_ahead(const Inst1D *__restrict__ tab, T *__restrict__ pool, const T *__restrict__ coef,
-                 const double *__restrict__ pcr, int64_t step0,
-                 int32_t nsteps, int64_t burn_in, int32_t every, uint32_t mask, Stats1D st, int32_t K, int32_t zrow,
-                 int32_t slots)
+__device__ __forceinline__ void rod_ahead(int inst, const Inst1D *__restrict__ tab, T *__restrict__ pool,
+                                          const T *__restrict__ coef, const double *__restrict__ pcr, int64_t step0,
+                                          int32_t nsteps, int64_t burn_in, int32_t every, uint32_t mask,
+                                          const Stats1D &st, int32_t K, int32_t zrow, int32_t slots,
+                                          unsigned char *smem_raw)
 {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
     const int W = blockDim.x >> 6, lane = threadIdx.x & 63;
-    const int inst = blockIdx.x;
     // Wave 0 advances the state.  The hardware starts successive workgroups of a
     // CU on successive SIMDs, so these waves do not share one (measured).
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -997,7 +1002,7 @@ __global__ void __launch_bounds__(512, CPL == 8 ? 2 : 4)
             const int kk = static_cast<int>((static_cast<uint32_t>(q) * magic) >> 20), g = q - kk * nfg;
             const uint64_t n = static_cast<uint64_t>(step0 + k0 + kk);
             Normals4<T> nz{};
-            if (MODE >= 3 || d.noise != 2)
+            if (one_face(MODE) || d.noise != 2)
                 nz = block_normals<T>(static_cast<uint32_t>(g), static_cast<uint32_t>(n), ctr_word2(n, 0u),
                                       d.realisation, key);
             T *p = buf + kk * zrow + 4 * g;
@@ -1074,8 +1079,8 @@ __global__ void __launch_bounds__(512, CPL == 8 ? 2 : 4)
         Rod<T, CPL, MODE> rod;
         const int units = (N + CPL - 1) / CPL;
         rod.init(d, coef, 0, 0, units, units - 1, true);
-        typename std::conditional<MODE == 2, LaneSolve<CPL>, NoSolve>::type solve;
-        if constexpr (MODE == 2) {
+        typename std::conditional<implicit(MODE), LaneSolve<CPL>, NoSolve>::type solve;
+        if constexpr (implicit(MODE)) {
             if (d.scheme >= 2) solve.load(pcr + d.p_off, d.pcr_levels, !dir, rod.lg, rod.m);
         }
         uint32_t clamps = 0;
@@ -1222,6 +1227,58 @@ __global__ void __launch_bounds__(512, CPL == 8 ? 2 : 4)
     (void)chunks([&](int c, const Chunk &, const Chunk &nx) { draw_next(c, nx); });
 }
 
+template <typename T, int CPL, bool STATS, int MODE>
+__global__ void __launch_bounds__(512, CPL == 8 ? 2 : 4)
+    k_rods_ahead(const Inst1D *__restrict__ tab, const Seg1D *__restrict__ segs, T *__restrict__ pool,
+                 const T *__restrict__ coef, const double *__restrict__ pcr, int64_t step0, int32_t nsteps,
+                 int64_t burn_in, int32_t every, uint32_t mask, Stats1D st, int32_t K, int32_t zrow, int32_t slots)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int inst = implicit(MODE) ? segs[blockIdx.x].inst : static_cast<int>(blockIdx.x);
+    rod_ahead<T, CPL, STATS, MODE>(inst, tab, pool, coef, pcr, step0, nsteps, burn_in, every, mask, st, K, zrow, slots,
+                                   smem_raw);
+}
+
+// The same where the implicit rods of a batch ask for different counts of cells
+// per lane, CMAX the largest: each rod takes that of its own length.  The order of
+// its elimination, and so its last bits, follows from that split, and taken from
+// the longest rod it would make a rod's field depend on the others.  (Explicit rods
+// have the same bits with any split.)  Us per step with CMAX's split for every
+// rod / with their own, Crank-Nicolson at r = 2: 700 rods of 3 to 256 cells FP32
+// 0.96 / 0.90, FP64 2.96 / 2.07; of 3 to 512 cells 1.92 / 1.66 and 4.55 / 3.07.  A
+// kernel with one split holds its factors in fewer registers (1024 rods of 256 cells
+// with statistics, FP64: 3.4, 4.3 with this one) and serves the batches it can.
+template <typename T, int CMAX, bool STATS, int MODE>
+__global__ void __launch_bounds__(512, CMAX == 8 ? 2 : 4)
+    k_rods_mixed(const Inst1D *__restrict__ tab, const Seg1D *__restrict__ segs, T *__restrict__ pool,
+                 const T *__restrict__ coef, const double *__restrict__ pcr, int64_t step0, int32_t nsteps,
+                 int64_t burn_in, int32_t every, uint32_t mask, Stats1D st, int32_t K, int32_t zrow, int32_t slots)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const Seg1D seg = segs[blockIdx.x];
+    auto run = [&](auto cpl) __attribute__((always_inline)) {
+        rod_ahead<T, decltype(cpl)::value, STATS, MODE>(seg.inst, tab, pool, coef, pcr, step0, nsteps, burn_in, every, mask,
+                                                        st, K, zrow, slots, smem_raw);
+    };
+    if (seg.cpl == 1) {
+        run(std::integral_constant<int, 1>{});
+        return;
+    }
+    if constexpr (CMAX > 2) {
+        if (seg.cpl == 2) {
+            run(std::integral_constant<int, 2>{});
+            return;
+        }
+    }
+    if constexpr (CMAX > 4) {
+        if (seg.cpl == 4) {
+            run(std::integral_constant<int, 4>{});
+            return;
+        }
+    }
+    run(std::integral_constant<int, CMAX>{});
+}
+
 // ------------------------------------------------------------------ typed launchers
 
 template <typename T, int STATS, int MODE>
@@ -1246,19 +1303,33 @@ static hipError_t rods_m(const Launch1D &a)
     return hipGetLastError();
 }
 
+#define SHE_AHEAD_K(KERNEL)                                                                                  \
+    hipLaunchKernelGGL(KERNEL, dim3(a.n_blocks), dim3(a.block), a.smem, a.s, a.tab, a.segs,                  \
+                       static_cast<T *>(a.pool), static_cast<const T *>(a.coef), a.pcr, a.step0, a.nsteps,   \
+                       a.burn_in, a.every, a.mask, a.st, a.ahead, a.zrow, a.slots)
+
+template <typename T, bool STATS, int MODE>
+static hipError_t mixed_m(const Launch1D &a)
+{
+    switch (a.cpl) {
+    case 2: SHE_AHEAD_K((k_rods_mixed<T, 2, STATS, MODE>)); break;
+    case 4: SHE_AHEAD_K((k_rods_mixed<T, 4, STATS, MODE>)); break;
+    case 8: SHE_AHEAD_K((k_rods_mixed<T, 8, STATS, MODE>)); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 template <typename T, bool STATS, int MODE>
 static hipError_t ahead_m(const Launch1D &a)
 {
-#define SHE_AHEAD(C)                                                                                          \
-    hipLaunchKernelGGL((k_rods_ahead<T, C, STATS, MODE>), dim3(a.n_blocks), dim3(a.block), a.smem, a.s, a.tab, \
-                       static_cast<T *>(a.pool), static_cast<const T *>(a.coef), a.pcr, a.step0, a.nsteps,     \
-                       a.burn_in, a.every, a.mask, a.st, a.ahead, a.zrow, a.slots)
+#define SHE_AHEAD(C) SHE_AHEAD_K((k_rods_ahead<T, C, STATS, MODE>))
     switch (a.cpl) {
     case 1: SHE_AHEAD(1); break;
     case 2: SHE_AHEAD(2); break;
     case 4: SHE_AHEAD(4); break;
     case 8:
-        if constexpr (MODE == 2) {
+        if constexpr (implicit(MODE)) {
             SHE_AHEAD(8);
             break;
         }
@@ -1267,6 +1338,12 @@ static hipError_t ahead_m(const Launch1D &a)
     }
 #undef SHE_AHEAD
     return hipGetLastError();
+}
+
+template <typename T, int MODE>
+hipError_t rods_mixed_t(const Launch1D &a)
+{
+    return a.stats ? mixed_m<T, true, MODE>(a) : mixed_m<T, false, MODE>(a);
 }
 
 // One unit per state type, mode and kernel (they compile in parallel).

@@ -39,3 +39,26 @@ def test_composite_rod(she, n, bc, scheme, precision):
         np.testing.assert_array_equal(field(she, [other, rod], precision), want)
     if n <= 512:
         np.testing.assert_array_equal(field(she, [rod], precision, block_threads=64), want)
+
+
+# one wave with 1, 2, 4, 8 cells per lane (full and not), and one barrier per
+# level above 512 cells; each alone, beside rods of every other kind, and with the
+# smallest workgroups; with a composite rod among them every rod's coefficients come
+# from a table.  FP64 shows the order of the elimination in the last bits.
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("scheme", [2, 3])
+@pytest.mark.parametrize("bc", [0, 1])
+@pytest.mark.parametrize("n", [60, 64, 65, 128, 200, 257, 511, 600])
+def test_implicit_rod(she, n, bc, scheme, precision):
+    gap = 0.1 * bc
+    rod = she.Instance(n=(n,), bc=bc, scheme=scheme, r=2.0, eps=1e-3, u_left=1.0 + gap, u_right=1.0 - gap, init_sd=0.1,
+                       seed=5)
+    others = [she.Instance(n=(m,), bc=1, scheme=s, r=r, eps=1e-3, u_left=1.1, u_right=0.9)
+              for m, s, r in ((40, she.BE, 50.0), (100, she.HEUN, 0.1), (300, she.CN, 1.0), (700, she.BE, 5.0))]
+    others.append(she.Instance(n=(50,), r=0.1, cond=np.linspace(0.5, 1.5, 50)))
+    want = field(she, [rod], precision)
+    for some in (others[:1], others[:2], others[:3], others[:4], others[4:], others):
+        np.testing.assert_array_equal(field(she, some + [rod], precision), want)
+    np.testing.assert_array_equal(field(she, [rod], precision, block_threads=512), want)
+    if n <= 512:
+        np.testing.assert_array_equal(field(she, [rod], precision, block_threads=64), want)
