@@ -78,6 +78,7 @@ struct she_handle {
     size_t rod_smem = 0;
     int32_t rod_ahead = 0, rod_zrow = 0, rod_slots = 0;
     bool rod_mixed = false;
+    SampleRing ring{};            // k_rods with statistics: sampled states of a launch
 
     // batch means: samples per batch (0: none) and their arrays
     int32_t batch_len = 0;
@@ -683,7 +684,7 @@ static int device_cus()
 // workgroup each, wave 0 advancing the state with 1, 2, 4 or 8 cells per lane and
 // the others drawing the numbers ahead.
 //
-// Longer ones (or block_threads = 64): whole waves with 4 cells per lane, 62
+// Longer ones: whole waves with 4 cells per lane, 62
 // units beside the two halo lanes (one more at a Dirichlet wall; one less on a
 // periodic rod whose last unit is not full).  Where 16 waves would not hold the
 // instance, some of its middle waves take 8 cells per lane, and where that does
@@ -698,10 +699,10 @@ static void plan_rods(she_handle *h, std::vector<int> idx, int block_threads)
         longest = std::max(longest, t.n);
         nf = std::max(nf, t.bc == SHE_DIRICHLET ? t.n + 1 : t.n);
     }
-    if (h->mode1d == 2 || (longest <= 256 && block_threads != 64)) {
+    if (h->mode1d == 2 || longest <= 256) {
         h->rod_cpl = rod_cells_per_lane(longest);
         h->rod_zrow = (nf + 3) & ~3;
-        // (block_threads = 64, implicit: two waves, one to draw the numbers)
+        // (block_threads = 64: two waves, one to draw the numbers)
         int waves = block_threads > 0 ? std::max(2, std::min(8, block_threads / 64)) : (h->prec == SHE_F32 ? 4 : 8);
         if (block_threads == 0 && n_idx > 2 * cus) waves = 4;
         h->rod_block = 64 * waves;
@@ -1019,6 +1020,13 @@ static she_status plan_1d(she_handle *h, const she_config *cfg, Plan &plan)
         h->segs_host.insert(h->segs_host.end(), segs.begin(), segs.end());
     }
 
+    if (h->mask && h->rod_blocks > 0 && h->rod_ahead == 0) {
+        // Up to 256 samples per launch (an X block), fewer where their states would
+        // take more than 128 MB, but no fewer than eight.
+        const int64_t row = static_cast<int64_t>(es) * ring_first(off, h->n_inst);
+        h->ring.cap = static_cast<int32_t>(std::max<int64_t>(8, std::min<int64_t>(kCorrBlock, (int64_t(128) << 20) / row)));
+        plan.add(&h->ring.rows, static_cast<size_t>(row) * h->ring.cap);
+    }
     plan.add(reinterpret_cast<void **>(&h->d_tab), sizeof(Inst1D) * h->n_inst);
     plan.add(reinterpret_cast<void **>(&h->d_segs), sizeof(Seg1D) * h->segs_host.size());
     plan.add(&h->d_pool, es * off);
@@ -1675,18 +1683,30 @@ static she_status advance(she_handle *h, int64_t nsteps, bool sampling)
                     fold = true;
                 }
             }
+            SampleRing ring = h->ring;
+            if (stats && ring.rows && std::max(h->steps, h->burn_in) - h->steps < k) {
+                // a launch ends at the sample that fills the ring or an X block
+                int64_t most = ring.cap;
+                if (h->mask & SHE_STAT_CORR) most = std::min<int64_t>(most, kCorrBlock - h->samples % kCorrBlock);
+                const int64_t t_end = h->every * (std::max(h->steps, h->burn_in) / h->every + most);
+                if (t_end - h->steps <= k) {
+                    fold = fold && t_end - h->steps == k;
+                    k = t_end - h->steps;
+                }
+            }
+            const int64_t cnt = stats ? sampled_by(h->steps + k) - sampled_by(h->steps) : 0;
+            ring.count = static_cast<int32_t>(cnt);
             if (h->rod_blocks > 0) {
                 const int mode = h->mode1d == 2 && !h->varc ? 6 : h->mode1d;
                 SHE_HIP(h, launch_rods(Launch1D{h->prec, mode, stats, h->rod_blocks, h->rod_block, h->rod_smem, s,
                                                 h->d_tab, h->d_segs, h->d_pool, h->d_coef, h->d_pcr, h->steps,
                                                 static_cast<int32_t>(k), h->burn_in, h->every, h->mask, st, h->rod_cpl,
-                                                h->rod_ahead, h->rod_zrow, h->rod_slots, h->rod_mixed}));
+                                                h->rod_ahead, h->rod_zrow, h->rod_slots, h->rod_mixed, ring}));
             }
             if (h->blocks1d > 0)
                 SHE_HIP(h, launch_step1d(h->prec, h->block1d, h->maxg, stats, h->blocks1d, h->smem1d, s, h->d_tab,
                                          h->d_segs + h->rod_segs, h->d_pool, h->d_coef, h->d_pcr, h->steps,
                                          static_cast<int32_t>(k), h->burn_in, h->every, h->mask, st));
-            const int64_t cnt = stats ? sampled_by(h->steps + k) - sampled_by(h->steps) : 0;
             if (tc && cnt > 0)
                 SHE_HIP(h, launch_tcorr1d(h->prec, h->n_inst, h->nmax, h->tc_lags, s, h->d_tab, h->d_hist,
                                           h->hist_rows, h->samples, cnt, h->d_tc, h->d_acc));

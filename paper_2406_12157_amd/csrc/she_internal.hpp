@@ -203,12 +203,13 @@ struct Seg1D {
 constexpr int kRodAlone = 512;
 __host__ __device__ constexpr int rod_cells_per_lane(int n) { return n <= 64 ? 1 : (n <= 128 ? 2 : (n <= 256 ? 4 : 8)); }
 
-// LDS bytes of one instance of an explicit batch served by nw waves: meeting
-// flags, the wave sums of a sample and the edge exchange (rod_waves).
+// LDS bytes of one instance of an explicit batch served by nw waves: flags, the
+// wave sums of a batch of samples and the edge exchange (rod_waves).
+constexpr int kRodFlags = 144;
 constexpr int rod_edge(int cpl) { return cpl > 8 ? 2 * cpl : 8; }  // two units of a wave at the ends
 inline int32_t rod_lds(int32_t nw, int32_t cpl, int32_t es)
 {
-    return nw == 1 ? 128 : 128 + 2 * 3 * 16 * 8 + 2 * nw * 2 * rod_edge(cpl) * es;
+    return nw == 1 ? kRodFlags : kRodFlags + 2 * nw * 16 * 8 + 2 * nw * 2 * rod_edge(cpl) * es;
 }
 
 // LDS region of one 1D instance (byte offsets, 16-byte aligned parts):
@@ -330,6 +331,18 @@ __device__ __forceinline__ void resolve_step(const StepArg &a, int64_t &step, in
 namespace she {
 
 // ---- launchers (defined next to their kernels) ----
+// Sampled states of one launch of k_rods: per instance cap rows (state type) of
+// ring_row cells, side by side, from ring_first cap on; row j holds the cells after
+// the launch's sample j.  Rows start at multiples of four cells.  count: samples of
+// this launch, at most cap.
+__host__ __device__ constexpr int ring_row(int n) { return (n + 3) & ~3; }
+// (a multiple of four, at least ring_row of an instance beyond its predecessor's)
+__host__ __device__ constexpr int64_t ring_first(int64_t off, int inst) { return (off + 3 * int64_t(inst) + 3) & ~int64_t(3); }
+struct SampleRing {
+    void *rows;
+    int32_t cap, count;
+};
+
 // One launch of an explicit 1D batch.  mode 0: uniform; 3, 4, 5: uniform with
 // instantaneous noise and of one equation; 1: some instance has material
 // coefficients (k_off >= 0 in `coef`); 2 and 6 (ahead only): some instance is
@@ -362,6 +375,7 @@ struct Launch1D {
     int cpl;
     int32_t ahead, zrow, slots;
     bool mixed;
+    SampleRing ring;  // ahead = 0 with stats
 };
 hipError_t launch_rods(const Launch1D &a);
 // The instances above kRodAlone cells of a batch with an implicit one: reduction

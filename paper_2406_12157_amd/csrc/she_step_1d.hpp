@@ -39,6 +39,7 @@
 //   up to 256 cells; us per step, against one wave that draws its own numbers:
 //   one FP32 PC rod of 128 cells 0.12 (0.93 with statistics before, 0.14 now),
 //   1024 of them 0.21 (1.02), one FP64 FE ring of 64 cells 0.10 (1.66).
+#include <climits>
 #include <type_traits>
 
 #include "she_internal.hpp"
@@ -487,6 +488,15 @@ __device__ __forceinline__ int first_sample(int64_t step0, int64_t burn_in, int3
 
 // ------------------------------------------------------------------ every wave its own numbers
 
+// CMAX: the largest cells per lane of the batch's waves: 4 alone, 4 and 8
+// side by side, or 16 alone.  FP32 kernels that fit or nearly fit 64 VGPRs are kept
+// to eight waves per SIMD, two workgroups of 1024 threads on a CU.
+template <typename T, int CMAX, int MODE>
+constexpr int rods_occupancy()
+{
+    return std::is_same<T, float>::value && (one_face(MODE) ? CMAX <= 8 : CMAX == 4) ? 8 : 4;
+}
+
 // Wait until the flags (LDS, one per wave of the instance) of waves a and b
 // reach seq.  Every wave of the instance is resident and publishes seq before
 // it waits for it, so the wait ends.
@@ -521,6 +531,179 @@ __device__ __forceinline__ void inst_sync(int *flag, int lw, int nw, int seq)
     wait_all(flag, nw, seq);
 }
 
+// Exchange step of wave_totals: lanes whose bit is set keep b and give a, the
+// others keep a and give b; the value that lane `CTRL` (a DPP move) gives is added.
+template <int CTRL>
+__device__ __forceinline__ double keep_give(bool bit, double a, double b)
+{
+    const double give = sel(bit, a, b);
+    return sel(bit, b, a) + dpp_shift<CTRL>(give, give);
+}
+
+// Sums of n = 8 or 16 values over the wave, that of x[q] in the lanes with
+// lane % n = q: the lanes of a row halve the values they hold at each exchange, then
+// the rows are added (16 values: 115 instructions; 16 scans take 288).  Every value
+// is added in the same order of lanes (mirrors first: they pair the same lanes
+// whichever of the two keeps the sum), so its bits do not depend on q.
+template <int n>
+__device__ __forceinline__ double wave_totals(const double (&x)[n])
+{
+    const int lane = threadIdx.x & 63;
+    double y[8], z[4], w[2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        if constexpr (n == 16) y[i] = keep_give<0x140>(lane & 8, x[i], x[i + 8]);               // row_mirror
+        else y[i] = x[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z[i] = keep_give<0x141>(lane & 4, y[i], y[i + 4]);              // row_half_mirror
+#pragma unroll
+    for (int i = 0; i < 2; ++i) w[i] = keep_give<0xB1>(lane & 1, z[2 * i], z[2 * i + 1]);       // quad_perm 1 0 3 2
+    double v = keep_give<0x4E>(lane & 2, w[0], w[1]);                                           // quad_perm 2 3 0 1
+    if constexpr (n == 8) v += dpp_shift<0x128>(v, v);                                          // row_ror:8
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    return v;
+}
+
+// The statistics of a launch's samples, from the sampled states that the waves of
+// an instance left in the ring, at the launch's end: by then the registers of the
+// steps are free and no wave waits for another at a sample.  Batches of kB
+// samples; a lane takes whole cells (one load and store of their sums per batch)
+// and forms its part of the kB spatial sums on the way (4 samples in the kernels of
+// 64 registers, 8 in the others: more would spill).  With the statistics
+// updated at each sample the kernels spilled up to 768 bytes per lane, and rods
+// with 8 or 16 cells per lane updated their sums at a stride of as many doubles.
+// Us per step with a sample every step (that form / now; every tenth step in
+// brackets): FP32 moments 16 x 1000 cells 2.18 / 1.71 (0.86 / 0.80), 900 x 1000
+// 6.5 / 3.4, 256 x 7800 55 / 6.9 (5.9 / 2.8); FP64 covariance 1 x 1000 6.2 / 2.3.
+// Not gained: FP64 batches whose sampled states exceed the caches, 900 x 2000 with
+// spatial sums only 13.5 / 16.7.
+// bad: LDS, the first sample with a non-finite value (INT_MAX: none); red: LDS,
+// [2][nw][16].  The multiply-adds are written out, so that a sample's share has the
+// same bits in a full batch and in the last one.
+template <typename T, int kB>
+__device__ __forceinline__ void take_samples(const Inst1D &d, int inst, int lw, int nw, uint32_t clamps, T *gU,
+                                             uint32_t mask, const Stats1D &st, const SampleRing &ring, InstAcc *acc,
+                                             int *mflag, const int *bad, double *red)
+{
+    const int count = ring.count;
+    auto count_clamps = [&]() {
+        if (clamps) atomicAdd(reinterpret_cast<unsigned long long *>(&acc->clamp_count), static_cast<unsigned long long>(clamps));
+    };
+    if (count == 0) {
+        count_clamps();
+        return;
+    }
+    const int N = d.n, lane = threadIdx.x & 63;
+    const bool dir = d.bc == 1;
+    const int64_t n0 = acc->n_samples;
+    // reference profile of the deviations: u0, or the linear wall profile
+    const double ref0 = dir ? d.uL : d.u0, ref_slope = dir ? (d.uR - d.uL) / N : 0.0;
+    const T *rows = static_cast<const T *>(ring.rows) + ring_first(d.off, inst) * ring.cap;
+    const int stride = ring_row(N);
+    int seq = 0;
+    __threadfence_block();
+    inst_sync(mflag, lw, nw, ++seq);  // the sampled states, the final state, n_samples and bad
+    // a non-finite sample: keep the statistics as they were before it and freeze
+    // the state there
+    const int good = min(count, __builtin_amdgcn_readfirstlane(*bad));
+    const bool moments = (mask & 1u) && st.s1 != nullptr;
+    const bool corr = (mask & 2u) && d.x_off >= 0;
+    const bool tcorr = (mask & 16u) && d.h_off >= 0;
+    T *X = corr ? static_cast<T *>(st.xblk) + d.x_off + n0 % kCorrBlock * N : nullptr;  // (no launch goes beyond an X block)
+    T *H = tcorr ? static_cast<T *>(st.hist) + d.h_off : nullptr;
+    double *s1 = moments ? st.s1 + d.off : nullptr, *s2 = moments ? st.s2 + d.off : nullptr;
+    double sp_mean = acc->sp_mean, sp_sq = acc->sp_sq, sp_var = acc->sp_var;
+    for (int j0 = 0; j0 < good; j0 += kB) {
+        const int nb = min(kB, good - j0);  // samples of the batch
+        double x[2 * kB];
+#pragma unroll
+        for (int q = 0; q < 2 * kB; ++q) x[q] = 0.0;
+        const T *u = rows + static_cast<int64_t>(j0) * stride;
+        T *const Xb = corr ? X + static_cast<int64_t>(j0) * N : nullptr;
+        const int h0 = tcorr ? static_cast<int>((n0 + j0) % st.hist_rows) : 0;
+        auto cells = [&](auto full) __attribute__((always_inline)) {
+            // kE cells at a time, their loads ahead of all
+            constexpr int kE = kB == 8 ? 2 : 1;
+            for (uint32_t i = 64 * lw + lane; i < static_cast<uint32_t>(N); i += 64 * nw * kE) {
+                T v[kE][kB];
+                double m1[kE], m2[kE];
+#pragma unroll
+                for (int e = 0; e < kE; ++e) {
+                    const uint32_t c = i + 64 * nw * e, k = c < static_cast<uint32_t>(N) ? c : i;
+#pragma unroll
+                    for (int q = 0; q < kB; ++q) v[e][q] = (u + (full ? q : min(q, nb - 1)) * stride)[k];
+                    m1[e] = moments ? s1[k] : 0.0;
+                    m2[e] = moments ? s2[k] : 0.0;
+                }
+#pragma unroll
+                for (int e = 0; e < kE; ++e) {
+                    const uint32_t k = i + 64 * nw * e;
+                    if (k >= static_cast<uint32_t>(N)) break;
+                    const double ref = fma(ref_slope, k + 0.5, ref0);
+#pragma unroll
+                    for (int q = 0; q < kB; ++q)
+                        if (full || q < nb) {
+                            const double dl = static_cast<double>(v[e][q]) - ref;
+                            x[q] += dl;
+                            x[kB + q] = fma(dl, dl, x[kB + q]);
+                            m1[e] += dl;
+                            m2[e] = fma(dl, dl, m2[e]);
+                            if (corr) (Xb + q * N)[k] = static_cast<T>(dl);
+                            if (tcorr) (H + static_cast<int64_t>(h0 + q - (h0 + q >= st.hist_rows ? st.hist_rows : 0)) * N)[k] = static_cast<T>(dl);
+                        }
+                    if (moments) {
+                        s1[k] = m1[e];
+                        s2[k] = m2[e];
+                    }
+                }
+            }
+        };
+        if (nb == kB) cells(std::true_type{});
+        else cells(std::false_type{});
+        double tot = wave_totals<2 * kB>(x);
+        if (nw > 1) {
+            // (the slots alternate: a wave writes a set again two meetings later)
+            double *rd = red + (seq & 1) * 2 * kB * nw;
+            if (lane < 2 * kB) rd[2 * kB * lw + lane] = tot;
+            inst_sync(mflag, lw, nw, ++seq);
+            if (lw == 0) {
+                tot = 0.0;
+                for (int w = 0; w < nw; ++w) tot += rd[2 * kB * w + (lane & (2 * kB - 1))];
+            }
+        }
+        if (lw == 0) {
+            tot /= N;
+#pragma unroll
+            for (int q = 0; q < kB; ++q)
+                if (q < nb) {
+                    const double a = of_lane(tot, q), b = of_lane(tot, kB + q);
+                    sp_mean += a;
+                    sp_sq += b;
+                    sp_var += fma(-a, a, b);
+                }
+        }
+    }
+    if (good < count) {
+        for (int i = 64 * lw + lane; i < N; i += 64 * nw) gU[i] = rows[static_cast<int64_t>(good) * stride + i];
+    } else {
+        count_clamps();
+    }
+    if (corr && good == count && n0 % kCorrBlock + count == kCorrBlock) {
+        __threadfence_block();
+        inst_sync(mflag, lw, nw, ++seq);
+        xtx_block<T>(static_cast<const T *>(st.xblk) + d.x_off, st.c + d.c_off, N, lw, nw);
+    }
+    if (lw == 0 && lane == 0) {
+        acc->sp_mean = sp_mean;
+        acc->sp_sq = sp_sq;
+        acc->sp_var = sp_var;
+        acc->n_samples = n0 + good;
+        if (good < count) acc->nonfinite = 1;
+    }
+}
+
 // First unit (of CPL cells) of wave lw's own: nf faces in blocks of four over nw
 // waves, the middle nbig of which ("big" waves, 8 cells per lane) take 124
 // blocks each; the rest is shared evenly, a Dirichlet end wave, which needs no
@@ -541,20 +724,23 @@ __device__ __forceinline__ int rod_split(int nf, bool dir, int nw, int nbig, int
     return b / (CPL / 4);
 }
 
-template <typename T, int CPL, int STATS, int MODE>
+// kB: the kernel's batch of samples (all waves of an instance must agree).
+template <typename T, int CPL, bool STATS, int MODE, int kB>
 __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1D *__restrict__ tab, T *__restrict__ pool,
                                           const T *__restrict__ coef, int64_t step0, int32_t nsteps, int64_t burn_in,
-                                          int32_t every, uint32_t mask, const Stats1D &st, unsigned char *lds)
+                                          int32_t every, uint32_t mask, const Stats1D &st, const SampleRing &ring,
+                                          unsigned char *lds)
 {
     constexpr int S = CPL / 4;  // Philox calls of a lane per step
     const Inst1D d = tab[seg.inst];
     InstAcc *acc = st.acc + seg.inst;
     const int nw = seg.nw, lw = wave - seg.w0;
-    // LDS of the instance (rod_lds): edge flags, meeting flags, sample sums, edges
+    // LDS of the instance (rod_lds): edge flags, meeting flags, first bad sample;
+    // sums of a batch of samples; edges
     constexpr int HC = rod_edge(CPL);  // edge cells a wave publishes at either end
-    int *eflag = reinterpret_cast<int *>(lds), *mflag = eflag + 16;
-    double *red = reinterpret_cast<double *>(lds + 128);       // [2][3][16]
-    T *edges = reinterpret_cast<T *>(lds + 128 + 2 * 3 * 16 * 8);  // [2][nw][first HC cells, last HC cells]
+    int *eflag = reinterpret_cast<int *>(lds), *mflag = eflag + 16, *bad = eflag + 32;
+    double *red = reinterpret_cast<double *>(lds + kRodFlags);               // [2][nw][16]
+    T *edges = reinterpret_cast<T *>(lds + kRodFlags + 2 * nw * 16 * 8);  // [2][nw][first HC cells, last HC cells]
 
     // the wave's units: [s0, s1) of its own, on lanes own0 .., halo copies beside them
     const int N = d.n;
@@ -574,35 +760,16 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
 #pragma unroll
     for (int l = 0; l < CPL; ++l) u[l] = l < rod.nc && lane < own1 + hr ? gU[CPL * rod.unit + l] : T(0);
 
-    // STATS 1: per-cell and spatial sums only, the per-cell ones in memory (64
-    // VGPRs in FP32: a batch which needs two workgroups per CU has both resident);
-    // 2: every statistic, FP32 per-cell sums in registers at 4 cells per lane
-    constexpr bool kRegSums = STATS == 2 && CPL == 4 && std::is_same<T, float>::value;
-    double s1r[kRegSums ? CPL : 1], s2r[kRegSums ? CPL : 1];
-    const bool moments = STATS && (mask & 1u) && st.s1 != nullptr;
-    const bool corr = STATS == 2 && (mask & 2u) && d.x_off >= 0;
-    const bool tcorr = STATS == 2 && (mask & 16u) && d.h_off >= 0;
-    int64_t nsamp = STATS ? acc->n_samples : 0;
-    double sp_mean = STATS ? acc->sp_mean : 0.0, sp_sq = STATS ? acc->sp_sq : 0.0, sp_var = STATS ? acc->sp_var : 0.0;
-    // reference profile of the deviations: u0, or the linear wall profile
-    const double ref0 = dir ? d.uL : d.u0, ref_slope = dir ? (d.uR - d.uL) / N : 0.0;
-    const double inv_n = 1.0 / N;
-    if constexpr (kRegSums) {
-#pragma unroll
-        for (int l = 0; l < CPL; ++l) {
-            const bool in = moments && rod.own && l < rod.nc;
-            s1r[l] = in ? st.s1[d.off + CPL * rod.unit + l] : 0.0;
-            s2r[l] = in ? st.s2[d.off + CPL * rod.unit + l] : 0.0;
-        }
-    }
-    if (lane < 32 && lw == 0) eflag[lane] = 0;
+    if (lane < 33 && lw == 0) eflag[lane] = lane < 32 ? 0 : INT_MAX;
     __syncthreads();  // flags cleared, and the halo cells read before any wave writes its own back
 
     const PhiloxKey key = make_key(d.seed);
     const bool pc = d.scheme == 1;
     constexpr int kStages = CPL == 16 ? 16 : 4;  // a halo lasts this many (all waves of an instance alike)
     int left = pc ? kStages / 2 : kStages;       // steps it still lasts
-    int seq = 0, mseq = 0;
+    int seq = 0;
+    T *row = static_cast<T *>(ring.rows) + ring_first(d.off, seg.inst) * ring.cap;  // where the next sampled state goes
+    int taken = 0;
     int k_next = STATS ? first_sample(step0, burn_in, every) : (1 << 30);
     every = min(every, 1 << 29);  // sample steps beyond the launch: no overflow
     uint32_t clamps = 0;
@@ -631,130 +798,8 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
             for (int l = 0; l < CPL; ++l) u[l] = src[l];
         }
     };
-    // A sample is taken in two parts.  begin: the wave's sums over the sampled
-    // state, published to the instance's other waves, and a copy of the state.
-    // finish, at the next sample or the launch's end: the sums over the instance
-    // and the statistics.  By then the other waves have published theirs long
-    // ago: N = 3967 x 256 FE FP32 with a sample every ten steps takes 1.16 us/step
-    // (0.93 without samples), 1.79 when all 16 waves met at the sample itself.
-    T up[CPL];
-    bool pend = false;
-    double pa = 0.0, pb = 0.0;
-    int pbad = 0;
-    auto begin = [&]() __attribute__((always_inline)) {
-        double a = 0.0, b = 0.0;
-        int bad = 0;
-#pragma unroll
-        for (int l = 0; l < CPL; ++l) {
-            up[l] = u[l];
-            if (rod.own && l < rod.nc) {
-                if (!isfinite(u[l])) bad = 1;
-                const double dl = static_cast<double>(u[l]) - fma(ref_slope, CPL * rod.unit + l + 0.5, ref0);
-                a += dl;
-                b += dl * dl;
-            }
-        }
-        pa = wave_total(a);
-        pb = wave_total(b);
-        pbad = __any(bad) ? 1 : 0;
-        pend = true;
-        if (nw > 1) {
-            // the two sets of slots alternate: a wave writes a set again only
-            // after every wave has published the next sample, and so read this one
-            double *rd = red + (mseq & 1) * 48;
-            ++mseq;
-            if (lane == 0) {
-                rd[lw] = pa;
-                rd[16 + lw] = pb;
-                rd[32 + lw] = static_cast<double>(pbad);
-                __hip_atomic_store(mflag + lw, mseq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        }
-    };
-    // returns whether the instance froze
-    auto finish = [&]() __attribute__((always_inline)) {
-        pend = false;
-        if (nw > 1) {
-            wait_all(mflag, nw, mseq);
-            const double *rd = red + ((mseq - 1) & 1) * 48;
-            pbad = __any(rd[32 + min(lane, nw - 1)] != 0.0) ? 1 : 0;
-            if (lw == 0) {  // in the order of the waves
-                pa = wave_total(lane < nw ? rd[lane] : 0.0);
-                pb = wave_total(lane < nw ? rd[16 + lane] : 0.0);
-            }
-        }
-        const int row = static_cast<int>(nsamp % kCorrBlock);
-        T *X = corr ? static_cast<T *>(st.xblk) + d.x_off : nullptr;
-        const int64_t i0 = CPL * rod.unit;
-        const int c = rod.own ? rod.nc : 0;  // the unit's cells of this wave's own
-        if (pbad) {
-            // a non-finite sample: keep the statistics as they were before it
-            // and freeze the state
-#pragma unroll
-            for (int l = 0; l < CPL; ++l)
-                if (l < c) {
-                    gU[i0 + l] = up[l];
-                    if constexpr (kRegSums) {
-                        if (moments) {
-                            st.s1[d.off + i0 + l] = s1r[l];
-                            st.s2[d.off + i0 + l] = s2r[l];
-                        }
-                    }
-                }
-            if (lw == 0 && lane == 0) {
-                acc->nonfinite = 1;
-                acc->n_samples = nsamp;
-                acc->sp_mean = sp_mean;
-                acc->sp_sq = sp_sq;
-                acc->sp_var = sp_var;
-            }
-            return true;
-        }
-        const double a = pa * inv_n, b = pb * inv_n;
-        sp_mean += a;
-        sp_sq += b;
-        sp_var += b - a * a;
-        T *H = tcorr ? static_cast<T *>(st.hist) + d.h_off + (nsamp % st.hist_rows) * N : nullptr;
-#pragma unroll
-        for (int h = 0; h < CPL; h += 4) {
-            // per-cell sums in memory: four cells' loads ahead of their stores
-            double m1[4], m2[4];
-            if (!kRegSums && moments) {
-#pragma unroll
-                for (int l = 0; l < 4; ++l) {
-                    m1[l] = h + l < c ? st.s1[d.off + i0 + h + l] : 0.0;
-                    m2[l] = h + l < c ? st.s2[d.off + i0 + h + l] : 0.0;
-                }
-            }
-#pragma unroll
-            for (int l = 0; l < 4; ++l) {
-                const int q = h + l;
-                const double dl = static_cast<double>(up[q]) - fma(ref_slope, CPL * rod.unit + q + 0.5, ref0);
-                if constexpr (kRegSums) {
-                    s1r[q] += dl;
-                    s2r[q] += dl * dl;
-                }
-                if (q < c) {
-                    if (!kRegSums && moments) {
-                        st.s1[d.off + i0 + q] = m1[l] + dl;
-                        st.s2[d.off + i0 + q] = m2[l] + dl * dl;
-                    }
-                    if (corr) X[(int64_t)row * N + i0 + q] = static_cast<T>(dl);
-                    if (tcorr) H[i0 + q] = static_cast<T>(dl);
-                }
-            }
-            if (!kRegSums) __builtin_amdgcn_sched_barrier(0);
-        }
-        ++nsamp;
-        if (corr && row == kCorrBlock - 1) {
-            __threadfence_block();
-            inst_sync(mflag, lw, nw, ++mseq);
-            xtx_block<T>(X, st.c + d.c_off, N, lw, nw);
-            inst_sync(mflag, lw, nw, ++mseq);
-        }
-        return false;
-    };
-    for (int k = 0; k < nsteps;) {
+    int k = 0;
+    while (k < nsteps) {
         // the steps up to the next sample (or the end of the launch)
         const int k_end = min(nsteps, k_next);
         rod.by_kind(d.scheme, [&](auto ec, auto sc) __attribute__((always_inline)) {
@@ -794,51 +839,34 @@ __device__ __forceinline__ void rod_waves(const Seg1D seg, int wave, const Inst1
 
         if (STATS && k == k_next) {
             k_next += every;
-            if (pend && finish()) return;
-            begin();
+            bool finite = true;
+#pragma unroll
+            for (int l = 0; l < CPL; l += 4)
+                if (rod.own && l < rod.nc) {  // (what goes beyond the last cell is in the row's pad)
+                    typedef T vec __attribute__((ext_vector_type(4)));
+                    *reinterpret_cast<vec *>(row + CPL * rod.unit + l) = vec{u[l], u[l + 1], u[l + 2], u[l + 3]};
+                }
+#pragma unroll
+            for (int l = 0; l < CPL; ++l)
+                if (rod.own && l < rod.nc) finite = finite && isfinite(u[l]);
+            if (!__all(finite) && lane == 0) atomicMin(bad, taken);
+            ++taken;
+            row += ring_row(N);
         }
     }
-    if (STATS && pend && finish()) return;
 
 #pragma unroll
     for (int l = 0; l < CPL; ++l)
-        if (rod.own && l < rod.nc) {
-            const int64_t i = CPL * rod.unit + l;
-            gU[i] = u[l];
-            if constexpr (kRegSums) {
-                if (moments) {
-                    st.s1[d.off + i] = s1r[l];
-                    st.s2[d.off + i] = s2r[l];
-                }
-            }
-        }
-    if (STATS) {
-        if (clamps) atomicAdd(reinterpret_cast<unsigned long long *>(&acc->clamp_count),
-                              static_cast<unsigned long long>(clamps));
-        if (lw == 0 && lane == 0) {
-            acc->n_samples = nsamp;
-            acc->sp_mean = sp_mean;
-            acc->sp_sq = sp_sq;
-            acc->sp_var = sp_var;
-        }
-    }
+        if (rod.own && l < rod.nc) gU[CPL * rod.unit + l] = u[l];
+    if constexpr (STATS)
+        take_samples<T, kB>(d, seg.inst, lw, nw, clamps, gU, mask, st, ring, acc, mflag, bad, red);
 }
 
-// CMAX: the largest cells per lane of the batch's waves: 4 alone, 4 and 8
-// side by side, or 16 alone.  The FP32 kernels of one equation without the
-// covariance are kept to eight waves per SIMD (64 VGPRs), two workgroups of 1024
-// threads on a CU.
-template <typename T, int CMAX, int STATS, int MODE>
-constexpr int rods_occupancy()
-{
-    return std::is_same<T, float>::value && STATS < 2 && one_face(MODE) && CMAX <= 8 ? 8 : 4;
-}
-
-template <typename T, int CMAX, int STATS, int MODE>
-__global__ void __launch_bounds__(1024, (rods_occupancy<T, CMAX, STATS, MODE>()))
+template <typename T, int CMAX, bool STATS, int MODE>
+__global__ void __launch_bounds__(1024, (rods_occupancy<T, CMAX, MODE>()))
     k_rods(const Inst1D *__restrict__ tab, const Seg1D *__restrict__ segs, T *__restrict__ pool,
            const T *__restrict__ coef, int64_t step0, int32_t nsteps, int64_t burn_in, int32_t every, uint32_t mask,
-           Stats1D st)
+           Stats1D st, SampleRing ring)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -846,14 +874,16 @@ __global__ void __launch_bounds__(1024, (rods_occupancy<T, CMAX, STATS, MODE>())
     if (seg.inst < 0) return;                   // idle wave (barriers count the waves still running)
     if (st.acc[seg.inst].nonfinite) return;     // frozen after a non-finite sample
     unsigned char *lds = smem_raw + seg.lds;
+    constexpr int kB = rods_occupancy<T, CMAX, MODE>() == 8 ? 4 : 8;
     if constexpr (CMAX == 8) {
         if (seg.cpl == 8) {
-            rod_waves<T, 8, STATS, MODE>(seg, wave, tab, pool, coef, step0, nsteps, burn_in, every, mask, st, lds);
+            rod_waves<T, 8, STATS, MODE, kB>(seg, wave, tab, pool, coef, step0, nsteps, burn_in, every, mask, st, ring,
+                                            lds);
             return;
         }
     }
-    rod_waves<T, CMAX == 16 ? 16 : 4, STATS, MODE>(seg, wave, tab, pool, coef, step0, nsteps, burn_in, every, mask, st,
-                                                   lds);
+    rod_waves<T, CMAX == 16 ? 16 : 4, STATS, MODE, kB>(seg, wave, tab, pool, coef, step0, nsteps, burn_in, every, mask, st,
+                                                   ring, lds);
 }
 
 // ------------------------------------------------------------------ implicit solve
@@ -1281,13 +1311,13 @@ __global__ void __launch_bounds__(512, CMAX == 8 ? 2 : 4)
 
 // ------------------------------------------------------------------ typed launchers
 
-template <typename T, int STATS, int MODE>
+template <typename T, bool STATS, int MODE>
 static hipError_t rods_m(const Launch1D &a)
 {
 #define SHE_RODS(C)                                                                                              \
     hipLaunchKernelGGL((k_rods<T, C, STATS, MODE>), dim3(a.n_blocks), dim3(a.block), a.smem, a.s, a.tab, a.segs, \
                        static_cast<T *>(a.pool), static_cast<const T *>(a.coef), a.step0, a.nsteps, a.burn_in,   \
-                       a.every, a.mask, a.st)
+                       a.every, a.mask, a.st, a.ring)
     switch (a.cpl) {
     case 4: SHE_RODS(4); break;
     case 8: SHE_RODS(8); break;
@@ -1346,20 +1376,12 @@ hipError_t rods_mixed_t(const Launch1D &a)
     return a.stats ? mixed_m<T, true, MODE>(a) : mixed_m<T, false, MODE>(a);
 }
 
-// One unit per state type, mode and kernel (they compile in parallel).
+// Each in a unit of its own per state type, mode and kernel (they compile in parallel).
 template <typename T, int MODE, bool AHEAD>
 hipError_t rods_t(const Launch1D &a)
 {
     if constexpr (AHEAD) return a.stats ? ahead_m<T, true, MODE>(a) : ahead_m<T, false, MODE>(a);
-    else if (!a.stats) return rods_m<T, 0, MODE>(a);
-    // Per-cell sums in registers pay while the whole batch is resident at the four
-    // waves per SIMD they leave (256 CUs of 1024 threads): N = 3967 x 256 FE FP32
-    // with a sample every ten steps 1.17 us/step, 1.26 with the sums in memory; but
-    // 4000 x 300 PC 2.88 in two rounds against 2.65.  FP64 spills them either way
-    // (3967 x 256 PC 3.28 against 2.94) and always takes the memory form.
-    else if (a.mask & 0x12u) return rods_m<T, 2, MODE>(a);
-    else if (std::is_same<T, float>::value && (int64_t)a.n_blocks * a.block <= 256 * 1024) return rods_m<T, 2, MODE>(a);
-    else return rods_m<T, 1, MODE>(a);
+    else return a.stats ? rods_m<T, true, MODE>(a) : rods_m<T, false, MODE>(a);
 }
 
 }  // namespace she

@@ -1,0 +1,179 @@
+"""Statistics of rods above 256 cells: the samples are taken from the states a launch
+leaves in memory, by waves that hold other cells than in the steps."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import gpu_instance, max_rel, oracle_desc
+from paper_2406_12157_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+TOL = {0: 1e-5, 1: 1e-12}        # states, relative
+STAT_TOL = {0: 1e-3, 1: 1e-9}    # statistics, relative
+
+
+@pytest.fixture(scope="module")
+def she():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2406_12157_amd import she as mod
+    mod.load()
+    return mod
+
+
+def rods(n, **kw):
+    return [W.instance((n,), bc=bc, scheme=scheme, r=0.1, eps=1e-2, u0=1.0, u_left=1.0 + 0.1 * bc,
+                       u_right=1.0 - 0.1 * bc, init_sd=0.1, seed=9, realisation=2 * bc + scheme, **kw)
+            for bc in (0, 1) for scheme in (0, 1)]
+
+
+# two, three and 16 waves, last unit full and not; 8 and (FP32) 16 cells per lane;
+# 290 samples: a full X block and an open one, a batch of samples that is not full
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n", [300, 505, 1000, 4100, 7801])
+def test_statistics_against_the_oracle(she, n, precision):
+    if n > 7424 and precision == 1:
+        pytest.skip("FP64 rods end at 5400 cells")
+    insts = rods(n)
+    corr = n <= 505
+    mask = she.STAT_MOMENTS | (she.STAT_CORR if corr else 0) | (she.STAT_TCORR if n == 300 else 0)
+    with she.Handle([gpu_instance(she, i) for i in insts], precision=precision, burn_in=10, sample_every=1, stats=mask,
+                    tcorr_lags=5 if n == 300 else 0) as h:
+        init = [h.read_field(q) for q in range(4)]
+        for k in (1, 128, 171):
+            h.run(k)
+        got = [h.stats(q, corr=corr, sk=corr, tcorr=n == 300) for q in range(4)]
+    for q, inst in enumerate(insts):
+        d = oracle_desc(inst, precision)
+        st = oracle.Stats(d, burn_in=10, every=1, corr=corr, sk=corr, tcorr_lags=5 if n == 300 else 0)
+        oracle.advance(d, init[q], 0, 300, st)
+        g = got[q]
+        assert g["n_samples"] == st.n_samples == 290
+        assert max_rel(g["mean"], st.mean()) < STAT_TOL[precision]
+        assert max_rel(g["var"], st.var()) < STAT_TOL[precision]
+        assert abs(g["spatial_var"] / st.spatial()[2] - 1) < STAT_TOL[precision]
+        if corr:
+            assert np.max(np.abs(g["corr"] - st.cov())) < STAT_TOL[precision] * np.max(np.abs(st.cov()))
+            assert max_rel(g["sk"], st.structure_factor()) < STAT_TOL[precision]
+        if n == 300:
+            want = st.time_corr()
+            assert np.max(np.abs(g["tcorr"] - want)) < STAT_TOL[precision] * np.max(np.abs(want))
+
+
+# coefficients of halo units and, on rings, of units across the seam
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n", [301, 502, 1000])
+def test_composite_rods_and_rings(she, n, precision):
+    rng = np.random.default_rng(n)
+    insts = rods(n, cond=list(0.5 + rng.random(n)), cap=list(0.7 + 0.6 * rng.random(n)))
+    with she.Handle([gpu_instance(she, i) for i in insts], precision=precision, sample_every=2,
+                    stats=she.STAT_MOMENTS) as h:
+        init = [h.read_field(q) for q in range(4)]
+        h.run(100)
+        fields, got = [h.read_field(q) for q in range(4)], [h.stats(q) for q in range(4)]
+    for q, inst in enumerate(insts):
+        d = oracle_desc(inst, precision)
+        st = oracle.Stats(d, burn_in=0, every=2)
+        u = init[q].copy()
+        oracle.advance(d, u, 0, 100, st)
+        assert max_rel(fields[q], u) <= TOL[precision]
+        assert max_rel(got[q]["mean"], st.mean()) < STAT_TOL[precision]
+        assert max_rel(got[q]["var"], st.var()) < STAT_TOL[precision]
+
+
+@pytest.mark.parametrize("n", [301, 505, 4100])
+def test_clamps_are_counted_once(she, n):
+    """A negative face mean is counted by the wave that owns the face, not by the
+    copies beside it (FP64: the oracle's signs)."""
+    insts = [W.instance((n,), eq=W.SPECIES, bc=bc, scheme=scheme, r=0.05, eps=1.0, u0=2.0, u_left=2.0, u_right=2.0,
+                        init_sd=1.0, realisation=4) for bc in (0, 1) for scheme in (0, 1)]
+    with she.Handle([gpu_instance(she, i) for i in insts], precision=1, sample_every=7, stats=she.STAT_MOMENTS) as h:
+        init = [h.read_field(q) for q in range(4)]
+        for k in (5, 1, 54):
+            h.run(k)
+        got = [h.stats(q)["clamp_count"] for q in range(4)]
+    for q, inst in enumerate(insts):
+        d = oracle_desc(inst, 1)
+        st = oracle.Stats(d, burn_in=60, every=1, per_cell=False)
+        oracle.advance(d, init[q], 0, 60, st)
+        assert got[q] == st.clamp_count > 0
+
+
+def test_spatial_sums_are_divided(she):
+    """A uniform deviation of 1/4 has no spatial variance: its sums over 392 cells are
+    exact and so are their quotients by 392 (1/392 is not)."""
+    inst = she.Instance(n=(392,), noise=she.NOISE_OFF)
+    with she.Handle([inst], precision=1, sample_every=1, stats=she.STAT_MOMENTS) as h:
+        h.write_field(0, np.full(392, 1.25))
+        h.run(11)
+        assert h.stats(0)["spatial_var"] == 0.0
+
+
+# the diverging rod in two or five waves beside one-wave rods in its workgroup and
+# rods of more waves elsewhere, and in one wave
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,block_threads", [(300, 0), (1000, 512), (200, 0)])
+def test_freeze(she, n, block_threads, precision):
+    bad = she.Instance(n=(n,), r=0.2, eps=100.0, init_sd=0.1, realisation=1)
+    healthy = [she.Instance(n=(500 if q % 100 == 0 else 90,), bc=q & 1, scheme=q & 1, r=0.1, eps=1e-2,
+                            init_sd=0.1, realisation=q) for q in range(700)]
+    kw = dict(precision=precision, sample_every=5, stats=she.STAT_MOMENTS, flags=she.ALLOW_UNSTABLE,
+              block_threads=block_threads)
+
+    def stats(h, q):
+        return h.stats(q, raise_nonfinite=False)
+
+    with she.Handle([bad, healthy[0]], **kw) as h:
+        h.run(20000)
+        first = stats(h, 0)
+        frozen = h.read_field(0)
+    m = first["n_samples"]
+    t = 5 * (m + 1)  # the step of the sample that is not finite
+    assert first["nonfinite"] and 10 < t <= 20000
+    with she.Handle([bad], **kw) as h:  # the state at that step, and the statistics before it
+        h.step(t)
+        np.testing.assert_array_equal(h.read_field(0), frozen)
+        assert not np.all(np.isfinite(frozen))
+    with she.Handle([bad, healthy[0]], **kw) as h:
+        h.run(t - 1)
+        before = stats(h, 0)
+        assert not before["nonfinite"]
+    with she.Handle(healthy, **kw) as h:
+        h.run(t + 40)
+        fields = [h.read_field(q) for q in (0, 1, 2, 100)]
+        want = [stats(h, q) for q in (0, 1, 2, 100)]
+    # the sample inside a launch, and as the last of one; later launches leave it
+    for calls in ((t + 40,), (t, 40), (t - 1, 1, 33, 7), (3, t + 37)):
+        with she.Handle([bad] + healthy, **kw) as h:
+            for k in calls:
+                h.run(k)
+            np.testing.assert_array_equal(h.read_field(0), frozen)
+            got = stats(h, 0)
+            assert got["nonfinite"] and got["n_samples"] == m
+            for key in ("mean", "var"):
+                np.testing.assert_array_equal(got[key], before[key])
+                np.testing.assert_array_equal(got[key], first[key])
+            np.testing.assert_array_equal([got["spatial_var"], before["spatial_var"]], 2 * [first["spatial_var"]])
+            for q, f, w in zip((1, 2, 3, 101), fields, want):
+                np.testing.assert_array_equal(h.read_field(q), f)
+                g = stats(h, q)
+                assert g["n_samples"] == w["n_samples"] == (t + 40) // 5 and not g["nonfinite"]
+                np.testing.assert_array_equal(g["var"], w["var"])
+
+
+def test_ragged_batch_with_16_cells_per_lane(she):
+    """A rod that takes 16 cells per lane gives them to every rod of its batch."""
+    sizes = [7800, 64, 65, 100, 992, 1009, 3000, 8191, 1]
+    insts = [W.instance((n,), bc=1 if n == 1 else q & 1, scheme=q & 1, r=0.1, eps=1e-2, u0=1.0, init_sd=0.1, realisation=q)
+             for q, n in enumerate(sizes)]
+    with she.Handle([gpu_instance(she, i) for i in insts], precision=0, sample_every=4, stats=she.STAT_MOMENTS) as h:
+        init = [h.read_field(q) for q in range(len(sizes))]
+        h.run(42)
+        for q, inst in enumerate(insts):
+            d = oracle_desc(inst, 0)
+            st = oracle.Stats(d, burn_in=0, every=4)
+            u = init[q].copy()
+            oracle.advance(d, u, 0, 42, st)
+            assert max_rel(h.read_field(q), u) <= TOL[0], inst["n"]
+            assert max_rel(h.stats(q)["mean"], st.mean()) < STAT_TOL[0]
