@@ -41,7 +41,9 @@
  *   - one handle must not be used from two host threads at once;
  *   - device memory is allocated at she_create and freed at she_destroy,
  *     or carved from a caller-owned device arena (she_config.arena), which the
- *     caller keeps alive until she_destroy.
+ *     caller keeps alive until she_destroy.  Without an arena a handle also
+ *     holds up to 256 KB of page-locked host memory for its results, from
+ *     she_create to she_destroy; with one the library allocates nothing.
  */
 #ifndef SHE_H
 #define SHE_H

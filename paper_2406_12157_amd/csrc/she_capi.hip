@@ -35,7 +35,13 @@ struct she_handle {
 
     // device memory
     bool own = false;
-    bool counted = false;         // Stage knows of this handle
+    // Host memory that kernels write results into (null: none): a small result then
+    // costs one launch and one wait, where a copy to pageable memory adds a staging
+    // copy and a second wait (52 us for the statistics of one rod with two such
+    // copies, 24 us for its field).  The handle's own: a call that fails between its
+    // launches and the wait leaves the buffer to no other handle.
+    double *stage = nullptr;
+    size_t stage_len = 0;         // doubles; a longer result is copied
     char *base = nullptr;
     size_t bytes = 0;
 
@@ -139,67 +145,6 @@ she_status hipfail(she_handle *h, hipError_t e, const char *what)
 {
     return fail(h, SHE_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
-
-// Host memory that kernels write results into: a small result then costs one
-// launch and one wait, where a copy to pageable memory adds a staging copy and a
-// second wait (52 us for the statistics of one rod with two such copies, 24 us
-// for its field).  At most kMost buffers are kept for the next calls of any
-// thread, and none once the last handle is gone; a call that gets none copies.
-class Stage {
-public:
-    static constexpr size_t kDoubles = 32768;
-    Stage()
-    {
-        std::lock_guard<std::mutex> lk(mu());
-        if (!spare().empty()) {
-            p_ = spare().back();
-            spare().pop_back();
-            return;
-        }
-        void *v = nullptr;
-        if (hipHostMalloc(&v, kDoubles * sizeof(double), hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
-            p_ = static_cast<double *>(v);
-        else
-            (void)hipGetLastError();
-    }
-    ~Stage()
-    {
-        if (!p_) return;
-        std::lock_guard<std::mutex> lk(mu());
-        if (handles() > 0 && spare().size() < kMost) spare().push_back(p_);
-        else (void)hipHostFree(p_);
-    }
-    Stage(const Stage &) = delete;
-    Stage &operator=(const Stage &) = delete;
-    double *get() const { return p_; }
-    static void add_handle(int k)
-    {
-        std::lock_guard<std::mutex> lk(mu());
-        handles() += k;
-        if (handles() > 0) return;
-        for (double *p : spare()) (void)hipHostFree(p);
-        spare().clear();
-    }
-
-private:
-    static constexpr size_t kMost = 4;
-    static std::mutex &mu()
-    {
-        static std::mutex m;
-        return m;
-    }
-    static std::vector<double *> &spare()
-    {
-        static std::vector<double *> v;
-        return v;
-    }
-    static int &handles()
-    {
-        static int n = 0;
-        return n;
-    }
-    double *p_ = nullptr;
-};
 
 #define SHE_HIP(h, call)                                   \
     do {                                                   \
@@ -1406,6 +1351,25 @@ extern "C" she_status she_tune(const she_config *cfg, int32_t steps, she_config 
     return SHE_OK;
 }
 
+// Doubles of a statistics result (1D: without the covariance).
+static size_t stats_doubles(const she_handle *h, size_t n)
+{
+    return kFinAcc + (h->dim == 1 ? 3 * n + 1 : 3 + static_cast<size_t>(h->nbins));
+}
+
+// Length of the handle's result buffer: the longest of the largest instance's
+// field, statistics and covariance that is not above 32768 doubles (256 KB).
+static size_t stage_doubles(const she_handle *h)
+{
+    constexpr size_t kMost = 32768;
+    const size_t n = h->dim == 1 ? static_cast<size_t>(h->nmax) : static_cast<size_t>(h->cells);
+    const size_t s = stats_doubles(h, n), c = h->c_elems > 0 ? s + n * n : 0;
+    size_t len = 0;
+    for (size_t v : {n, s, c})
+        if (v <= kMost) len = std::max(len, v);
+    return std::max<size_t>(len, 1);
+}
+
 extern "C" she_status she_create(const she_config *cfg, she_handle **out)
 {
     if (!out) return fail(nullptr, SHE_EINVAL, "out is NULL");
@@ -1453,8 +1417,17 @@ extern "C" she_status she_create(const she_config *cfg, she_handle **out)
     }
     h->bytes = plan.total;
     plan.carve(h->base);
-    h->counted = true;
-    Stage::add_handle(1);
+    if (h->own) {
+        // (with a caller arena the library allocates nothing)
+        h->stage_len = stage_doubles(h);
+        void *v = nullptr;
+        if (hipHostMalloc(&v, sizeof(double) * h->stage_len, hipHostMallocMapped) == hipSuccess) {
+            h->stage = static_cast<double *>(v);
+        } else {
+            (void)hipGetLastError();
+            h->stage_len = 0;
+        }
+    }
 
     hipStream_t s = h->stream;
     // host sources of the asynchronous copies below; they live until the
@@ -1523,7 +1496,7 @@ extern "C" void she_destroy(she_handle *h)
         if (g) (void)hipGraphExecDestroy(g);
     if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
     if (h->own && h->base) (void)hipFree(h->base);
-    if (h->counted) Stage::add_handle(-1);
+    if (h->stage) (void)hipHostFree(h->stage);
     delete h;
 }
 
@@ -1817,10 +1790,8 @@ extern "C" she_status she_stats(she_handle *h, int32_t instance, she_stats_out *
     const bool corr = d1 && h->tab[instance].x_off >= 0;
     // the covariance and S_k are formed and copied only when asked for
     const bool want = corr && (out->corr || out->sk);
-    const size_t len = kFinAcc + (d1 ? 3 * static_cast<size_t>(N) + 1 + (want ? static_cast<size_t>(nn) : 0)
-                                     : 3 + static_cast<size_t>(h->nbins));
-    const Stage stage;
-    double *const to = stage.get() && len <= Stage::kDoubles ? stage.get() : h->d_fin;
+    const size_t len = stats_doubles(h, static_cast<size_t>(N)) + (want ? static_cast<size_t>(nn) : 0);
+    double *const to = len <= h->stage_len ? h->stage : h->d_fin;
     if (d1) {
         // the scratch behind the results' place in d_fin
         double *scratch = h->d_fin + kFinAcc + 3 * static_cast<size_t>(N) + 1 + (want ? nn : 0);
@@ -1946,14 +1917,11 @@ extern "C" she_status she_read_field(she_handle *h, int32_t instance, double *ho
     if (instance < 0 || instance >= h->n_inst) return fail(h, SHE_EINVAL, "instance out of range");
     const int64_t nc = inst_cells(h, instance);
     if (n != nc) return fail(h, SHE_EINVAL, "n must equal the instance's cell count");
-    if (static_cast<size_t>(nc) <= Stage::kDoubles) {
-        const Stage stage;
-        if (stage.get()) {
-            SHE_HIP(h, launch_widen(h->prec, h->stream, inst_field(h, instance), nc, stage.get()));
-            SHE_HIP(h, hipStreamSynchronize(h->stream));
-            std::memcpy(host, stage.get(), sizeof(double) * nc);
-            return SHE_OK;
-        }
+    if (static_cast<size_t>(nc) <= h->stage_len) {
+        SHE_HIP(h, launch_widen(h->prec, h->stream, inst_field(h, instance), nc, h->stage));
+        SHE_HIP(h, hipStreamSynchronize(h->stream));
+        std::memcpy(host, h->stage, sizeof(double) * nc);
+        return SHE_OK;
     }
     std::vector<char> buf(h->esz * nc);
     SHE_HIP(h, hipMemcpyAsync(buf.data(), inst_field(h, instance), buf.size(), hipMemcpyDeviceToHost, h->stream));
