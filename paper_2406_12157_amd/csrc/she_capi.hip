@@ -1769,12 +1769,13 @@ static she_status copy_out(she_handle *h, double *dst, int64_t cap, const double
 }
 
 // Finalisation results of one 1D instance at out: accumulators, mean[N], var[N],
-// sum, S_k [N], covariance [N^2] (as much of it as the caller asked for);
-// scratch for the circulant sums [N] and second moments [N^2].
-static Fin1D fin1d_at(double *out, double *scratch, int64_t n)
+// sum, S_k [N] and, with cov, the covariance [N^2]; scratch for the circulant sums
+// [N] and second moments [N^2].
+static Fin1D fin1d_at(double *out, double *scratch, int64_t n, bool cov)
 {
     double *mean = out + kFinAcc, *sk = mean + 2 * n + 1;
-    return Fin1D{reinterpret_cast<InstAcc *>(out), mean, mean + n, mean + 2 * n, sk + n, sk, scratch + n, scratch};
+    return Fin1D{reinterpret_cast<InstAcc *>(out), mean, mean + n, mean + 2 * n, cov ? sk + n : nullptr, sk,
+                 scratch + n, scratch};
 }
 
 extern "C" she_status she_stats(she_handle *h, int32_t instance, she_stats_out *out)
@@ -1788,17 +1789,18 @@ extern "C" she_status she_stats(she_handle *h, int32_t instance, she_stats_out *
     const int N = d1 ? h->tab[instance].n : 0;
     const int64_t nn = static_cast<int64_t>(N) * N;
     const bool corr = d1 && h->tab[instance].x_off >= 0;
-    // the covariance and S_k are formed and copied only when asked for
-    const bool want = corr && (out->corr || out->sk);
-    const size_t len = stats_doubles(h, static_cast<size_t>(N)) + (want ? static_cast<size_t>(nn) : 0);
+    // S_k is formed only when it or the covariance is asked for, the covariance
+    // written out only when it is itself (S_k alone of 1024 cells moved 8 MB: 610 us, now 93)
+    const bool want = corr && (out->corr || out->sk), cov = corr && out->corr;
+    const size_t len = stats_doubles(h, static_cast<size_t>(N)) + (cov ? static_cast<size_t>(nn) : 0);
     double *const to = len <= h->stage_len ? h->stage : h->d_fin;
     if (d1) {
         // the scratch behind the results' place in d_fin
-        double *scratch = h->d_fin + kFinAcc + 3 * static_cast<size_t>(N) + 1 + (want ? nn : 0);
+        double *scratch = h->d_fin + stats_doubles(h, static_cast<size_t>(N)) + (cov ? nn : 0);
         SHE_HIP(h, launch_fin1d(h->prec, s, h->d_tab, instance, N, h->d_pool, h->d_s1, h->d_s2, h->tab[instance].off,
                                 corr ? static_cast<char *>(h->d_x) + h->esz * h->tab[instance].x_off : nullptr,
                                 corr ? h->d_c + h->tab[instance].c_off : nullptr, h->d_acc + instance, want,
-                                fin1d_at(to, scratch, N)));
+                                fin1d_at(to, scratch, N, cov)));
     } else {
         SHE_HIP(h, launch_finnd(h->prec, s, h->pnd, instance, h->cells, h->field(), h->d_acc, h->d_sksum,
                                 h->d_skmodes, h->nbins, h->d_fin + h->fin_len - kFinParts, to));

@@ -388,9 +388,9 @@ hipError_t launch_step1d(int prec, int block, int maxg, bool stats, int n_blocks
 hipError_t launch_init1d(int prec, int n_inst, int nmax, hipStream_t s, const Inst1D *tab,
                          const double *init_sd, void *pool);
 // 1D finalisation of one instance (FP64): its accumulators acc, mean[N], var[N]
-// and sum(U) always; with corr the covariance cov[N^2] and S_k sk[N] too (m2[N^2]
-// and circ[N] are device scratch; the others may be host memory the device
-// writes).  s1, s2: the batch's per-cell sums (null: not kept), the instance's at
+// and sum(U) always; with corr S_k sk[N] and the covariance cov[N^2] (null: not
+// wanted) too (m2[N^2] and circ[N] are device scratch; the others may be host memory
+// the device writes).  s1, s2: the batch's per-cell sums (null: not kept), the instance's at
 // off.
 struct Fin1D {
     InstAcc *acc;

@@ -671,7 +671,7 @@ __global__ void __launch_bounds__(256)
         acc += static_cast<double>(X[static_cast<int64_t>(b) * N + i]) * static_cast<double>(X[static_cast<int64_t>(b) * N + j]);
     const double inv = 1.0 / static_cast<double>(M), v = acc / static_cast<double>(M);
     m2[e] = v;
-    cov[e] = v - (s1[i] * inv) * (s1[j] * inv);
+    if (cov) cov[e] = v - (s1[i] * inv) * (s1[j] * inv);
 }
 
 // mean, variance per cell, sum(U) of the current field
