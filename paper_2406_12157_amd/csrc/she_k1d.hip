@@ -1052,6 +1052,12 @@ __global__ void __launch_bounds__(256)
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (i >= count) return;
     const uint64_t f = face0 + static_cast<uint64_t>(i);
+    if constexpr (std::is_same<T, double>::value) {
+        if (tag == 1) {  // as the initial state is drawn
+            out[i] = init_normals(static_cast<uint32_t>(f >> 2), real, make_key(seed), step).z[f & 3];
+            return;
+        }
+    }
     const Normals4<T> nz = block_normals<T>(static_cast<uint32_t>(f >> 2), static_cast<uint32_t>(step),
                                             ctr_word2(step, tag), real, make_key(seed));
     out[i] = static_cast<double>(nz.z[f & 3]);

@@ -255,10 +255,12 @@ __device__ __forceinline__ Normals4<T> block_normals(uint32_t block, uint32_t st
     return n;
 }
 
-// The four initial normals (tag 1) of Philox block `block`.
-__device__ __forceinline__ Normals4<double> init_normals(uint32_t block, uint32_t realisation, PhiloxKey key)
+// The four FP64 normals of tag 1 of Philox block `block`; the initial perturbation
+// takes those of step 0.
+__device__ __forceinline__ Normals4<double> init_normals(uint32_t block, uint32_t realisation, PhiloxKey key,
+                                                         uint64_t step = 0)
 {
-    const Words4 x = philox4x32_10(block, 0u, ctr_word2(0, 1u), realisation, key);
+    const Words4 x = philox4x32_10(block, static_cast<uint32_t>(step), ctr_word2(step, 1u), realisation, key);
     Normals4<double> n;
     box_muller_init(x.w[0], x.w[1], n.z[0], n.z[1]);
     box_muller_init(x.w[2], x.w[3], n.z[2], n.z[3]);

@@ -33,3 +33,11 @@ def test_fp64_normals_within_two_ulp():
         # the product's rounding 0.5; an ulp is at most 2^-52 of the value
         err = np.abs(z.astype(np.longdouble) - want)
         assert np.all(err <= np.abs(want) * (0.86 + 0.76 + 0.51) * 2.0 ** -52)
+
+
+def test_initial_normals_are_the_entry_points():
+    from paper_2406_12157_amd import she
+    n = 4096
+    inst = she.Instance(n=(n,), u0=0.0, init_sd=1.0, seed=21, realisation=5)
+    with she.Handle([inst], precision=she.F64) as h:
+        np.testing.assert_array_equal(h.read_field(0), she.debug_normals(21, 5, 1, 0, 0, n, she.F64))
