@@ -1116,17 +1116,21 @@ static she_status plan_nd(she_handle *h, const she_config *cfg, Plan &plan)
         h->ty = ty;
         // Planes per march: a chunk recomputes the z-faces below its first plane
         // (about 0.4 plane), so long chunks are cheaper once the chip is full,
-        // and a small grid needs short ones to fill it at all.  Measured, us per
-        // step with chunks of 1, 2, 4, 8: 64^3 FE (256 tile planes) 4.7, 5.6, 7.4,
-        // 11.3; four 64^3 PC (1024) 16.7, 15.9, 17.1, 23.8; 128^3 FE (2048) 11.9,
-        // 9.6, 9.7, 12.3; ten 128x32x156 DK PC (6240) 60.9, 50.1, 46.4, 49.7; four
-        // 128^3 DK (8192) 37.5, 29.0, 25.7, 24.9; 256^3 DK (16384) 60.6, 46.8,
-        // 41.9, 40.7 (12: 43.9).
+        // and a small grid needs short ones to fill it at all.  Eight from three
+        // workgroups per CU on, unless a fourth to sixth round of them would be
+        // nearly empty (without noise they are short and it costs little); below,
+        // up to four.  Measured, us per step with chunks of 1, 2, 4, 8: 64^3 FE (256
+        // tile planes) 4.5, 5.4, 7.3, 11.2; four 64^3 PC (1024) 16.1, 15.3, 17.0, 23.7;
+        // 128^3 FE (2048) 10.7, 9.3, 9.3, 12.1; ten 128x32x156 DK PC (6240, 800
+        // workgroups with 8) 53.6, 46.7, 44.0, 48.4, without noise 40.4, 37.7, 32.5,
+        // 29.5; three 128^3 PC (6144, 768) 48.0, 40.0, 38.4, 37.1; four (8192, 1024)
+        // 61.7, 50.5, 47.0, 44.8; 256^3 DK (16384) 52.0, 44.0, 41.5, 39.8.
         int chunk = cfg->rows_per_block;
         if (chunk <= 0) {
-            const int64_t planes = static_cast<int64_t>(h->n_inst) * (p.ny / ty) * p.nz;
-            chunk = static_cast<int>(std::max<int64_t>(
-                1, std::min<int64_t>(8, std::max(std::min<int64_t>(4, planes / 512), planes / 1536))));
+            const int64_t tiles = static_cast<int64_t>(h->n_inst) * (p.ny / ty), cus = device_cus();
+            const int64_t wg8 = tiles * ((p.nz + 7) / 8), rest = wg8 % cus;
+            const bool eight = wg8 >= 3 * cus && (wg8 >= 6 * cus || rest == 0 || 2 * rest >= cus || p.noise == SHE_NOISE_OFF);
+            chunk = eight ? 8 : static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(4, tiles * p.nz / 512)));
         }
         chunk = std::min(chunk, p.nz);
         p.chunk = chunk;
