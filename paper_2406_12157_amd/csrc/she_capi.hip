@@ -655,7 +655,7 @@ static void plan_rods(she_handle *h, std::vector<int> idx, int block_threads)
         // workgroups of the CU
         const size_t cap = n_idx > cus ? 36 * 1024 : 60 * 1024;
         for (int K = 32;; K /= 2) {
-            const int slots = h->mask ? (K + h->every - 1) / h->every : 0;
+            const int slots = !h->mask ? 0 : (h->every >= K ? 1 : (K + h->every - 1) / h->every);
             const size_t b = 16 + static_cast<size_t>(es) * (2 * static_cast<size_t>(K) * h->rod_zrow + 64 * h->rod_cpl + 4 +
                                                              2 * static_cast<size_t>(slots) * 64 * h->rod_cpl);
             if (b <= cap || K == 2) {

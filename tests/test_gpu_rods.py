@@ -129,3 +129,24 @@ def test_implicit_rod_sizes(she, n, precision):
     insts.append(W.instance((min(n, 40),), bc=1, scheme=W.HEUN, r=0.05, eps=1e-3, u0=1.0, u_left=1.1, u_right=0.9,
                             init_sd=0.05, seed=4, realisation=9))
     check(she, insts, precision, 25)
+
+
+def test_samples_at_the_longest_interval(she):
+    """One sample every 2^31 - 1 steps: a chunk of steps has room for it (the steps
+    before are skipped by a checkpoint with a later step count)."""
+    every = 2 ** 31 - 1
+    kw = dict(precision=1, sample_every=every, stats=she.STAT_MOMENTS)
+    inst = she.Instance(n=(100,), r=0.1, eps=1e-2, init_sd=0.1, seed=3)
+    with she.Handle([inst], **kw) as h:
+        blob = bytearray(h.get_state())
+        assert int.from_bytes(blob[16:24], "little") == 0
+        blob[16:24] = (every - 20).to_bytes(8, "little")
+        h.set_state(bytes(blob))
+        h.step(20)
+        want = h.read_field(0)
+    with she.Handle([inst], **kw) as h:
+        h.set_state(bytes(blob))
+        h.run(50)
+        st = h.stats(0)
+    assert st["steps"] == every + 30 and st["n_samples"] == 1
+    np.testing.assert_array_equal(st["mean"], 1.0 + (want - 1.0))
