@@ -35,12 +35,7 @@ struct she_handle {
 
     // device memory
     bool own = false;
-    // Host memory that kernels write results into (null: none): a small result then
-    // costs one launch and one wait, where a copy to pageable memory adds a staging
-    // copy and a second wait (52 us for the statistics of one rod with two such
-    // copies, 24 us for its field).  The handle's own: a call that fails between its
-    // launches and the wait leaves the buffer to no other handle.
-    double *stage = nullptr;
+    double *stage = nullptr;      // Stage, the handle's own from create to destroy (null: none)
     size_t stage_len = 0;         // doubles; a longer result is copied
     char *base = nullptr;
     size_t bytes = 0;
@@ -145,6 +140,54 @@ she_status hipfail(she_handle *h, hipError_t e, const char *what)
 {
     return fail(h, SHE_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
+
+// Host memory that kernels write results into: a small result then costs one
+// launch and one wait, where a copy to pageable memory adds a staging copy and a
+// second wait (52 us for the statistics of one rod with two such copies, 24 us
+// for its field).  A buffer is one handle's alone from she_create to she_destroy,
+// which waits for the stream, so that no other handle's kernels can write it, whatever
+// fails in between.  Page-locking one takes 55 us: at most kMost of destroyed
+// handles' buffers are kept for new ones, and none once the last handle is gone.
+// (Nothing here has a destructor: a handle may be destroyed at exit.)
+class Stage {
+public:
+    static constexpr size_t kDoubles = 32768;
+    static double *take()
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            ++handles_;
+            if (spares_ > 0) return spare_[--spares_];
+        }
+        void *v = nullptr;
+        if (hipHostMalloc(&v, kDoubles * sizeof(double), hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+            return static_cast<double *>(v);
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    // idle: the handle's kernels are known to have ended
+    static void give(double *p, bool idle)
+    {
+        double *out[kMost + 1];
+        int n = 0;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (--handles_ > 0 && p && idle && spares_ < kMost) spare_[spares_++] = p;
+            else if (p) out[n++] = p;
+            while (handles_ == 0 && spares_ > 0) out[n++] = spare_[--spares_];
+        }
+        while (n > 0) (void)hipHostFree(out[--n]);
+    }
+
+private:
+    static constexpr int kMost = 4;
+    static std::mutex mu_;
+    static double *spare_[kMost];
+    static int spares_, handles_;
+};
+std::mutex Stage::mu_;
+double *Stage::spare_[Stage::kMost];
+int Stage::spares_ = 0, Stage::handles_ = 0;
 
 #define SHE_HIP(h, call)                                   \
     do {                                                   \
@@ -1361,19 +1404,6 @@ static size_t stats_doubles(const she_handle *h, size_t n)
     return kFinAcc + (h->dim == 1 ? 3 * n + 1 : 3 + static_cast<size_t>(h->nbins));
 }
 
-// Length of the handle's result buffer: the longest of the largest instance's
-// field, statistics and covariance that is not above 32768 doubles (256 KB).
-static size_t stage_doubles(const she_handle *h)
-{
-    constexpr size_t kMost = 32768;
-    const size_t n = h->dim == 1 ? static_cast<size_t>(h->nmax) : static_cast<size_t>(h->cells);
-    const size_t s = stats_doubles(h, n), c = h->c_elems > 0 ? s + n * n : 0;
-    size_t len = 0;
-    for (size_t v : {n, s, c})
-        if (v <= kMost) len = std::max(len, v);
-    return std::max<size_t>(len, 1);
-}
-
 extern "C" she_status she_create(const she_config *cfg, she_handle **out)
 {
     if (!out) return fail(nullptr, SHE_EINVAL, "out is NULL");
@@ -1421,16 +1451,9 @@ extern "C" she_status she_create(const she_config *cfg, she_handle **out)
     }
     h->bytes = plan.total;
     plan.carve(h->base);
-    if (h->own) {
-        // (with a caller arena the library allocates nothing)
-        h->stage_len = stage_doubles(h);
-        void *v = nullptr;
-        if (hipHostMalloc(&v, sizeof(double) * h->stage_len, hipHostMallocMapped) == hipSuccess) {
-            h->stage = static_cast<double *>(v);
-        } else {
-            (void)hipGetLastError();
-            h->stage_len = 0;
-        }
+    if (h->own) {  // (with a caller arena the library allocates nothing)
+        h->stage = Stage::take();
+        h->stage_len = h->stage ? Stage::kDoubles : 0;
     }
 
     hipStream_t s = h->stream;
@@ -1495,12 +1518,12 @@ extern "C" she_status she_create(const she_config *cfg, she_handle **out)
 extern "C" void she_destroy(she_handle *h)
 {
     if (!h) return;
-    (void)hipStreamSynchronize(h->stream);
+    const bool idle = hipStreamSynchronize(h->stream) == hipSuccess;
     for (hipGraphExec_t &g : h->gexec)
         if (g) (void)hipGraphExecDestroy(g);
     if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
     if (h->own && h->base) (void)hipFree(h->base);
-    if (h->stage) (void)hipHostFree(h->stage);
+    if (h->own) Stage::give(h->stage, idle);
     delete h;
 }
 
