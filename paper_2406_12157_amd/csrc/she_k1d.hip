@@ -432,10 +432,6 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
                             if (!isfinite(v)) bad = 1;
                             const double dl = static_cast<double>(v) - fma(ref_slope, i + 0.5, ref0);
                             del[s][l] = dl;
-                            if (kRegSums) {
-                                s1[s][l] += dl;
-                                s2[s][l] += dl * dl;
-                            }
                             a += dl;
                             b += dl * dl;
                             if (corr) X[(int64_t)row * N + i] = static_cast<T>(dl);
@@ -471,7 +467,13 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
 #pragma unroll
                         for (int l = 0; l < 4; ++l) {
                             const int i = 4 * (t + s * TS) + l;
-                            if (i < N) gU[i] = u[s][l];
+                            if (i < N) {
+                                gU[i] = u[s][l];
+                                if (kRegSums && moments) {
+                                    st.s1[d.off + i] = s1[s][l];
+                                    st.s2[d.off + i] = s2[s][l];
+                                }
+                            }
                         }
                     if (t == 0) {
                         acc->nonfinite = 1;
@@ -487,7 +489,15 @@ __device__ __forceinline__ void step1d_body(const Inst1D *__restrict__ tab, cons
                 sp_mean += a;
                 sp_sq += b;
                 sp_var += b - a * a;
-                if (!kRegSums && moments) {
+                if (kRegSums) {
+#pragma unroll
+                    for (int s = 0; s < MAXG; ++s)
+#pragma unroll
+                        for (int l = 0; l < 4; ++l) {
+                            s1[s][l] += del[s][l];
+                            s2[s][l] += del[s][l] * del[s][l];
+                        }
+                } else if (moments) {
 #pragma unroll
                     for (int s = 0; s < MAXG; ++s)
 #pragma unroll
