@@ -181,12 +181,15 @@ typedef struct {
                                      64, 256 or 512, or 1024 for an FP32
                                      batch of FE/PC heat instances with
                                      instantaneous noise, uniform material
-                                     and stats_mask 0.  An explicit instance
-                                     of up to 256 cells has a workgroup of its
-                                     own (with 64: one wave); a longer one
-                                     takes as many whole waves as it needs,
-                                     which may be more than this; results are
-                                     identical                                 */
+                                     and stats_mask 0.  Where the longest
+                                     instance has up to 256 cells (and for
+                                     those of up to 512 in a batch with
+                                     implicit ones) each has a workgroup of
+                                     its own, of 128 to 512 threads; else an
+                                     instance takes as many whole waves as it
+                                     needs, which may be more than this.
+                                     Fields are identical, statistics to the
+                                     rounding of their sums                  */
     int32_t rows_per_block;       /* tuning: 2D/3D march length (0 auto)      */
     int32_t rows_per_group;       /* tuning: 3D rows per workgroup (0 auto)   */
     int32_t tuning_flags;         /* SHE_TUNE_* bits (0 = defaults)           */
@@ -275,8 +278,8 @@ she_status she_arena_bytes(const she_config *cfg, size_t *bytes);
  * rows_per_block x rows_per_group for 3D).  Each candidate is a trial handle
  * (she_create without cfg->arena: it allocates), warmed up and then timed
  * over `steps` steps of she_step with events on cfg->stream (steps <= 0:
- * 2000 in 1D, 20 in 2D/3D); shapes the batch rejects are skipped.  Results
- * are identical for every shape; only the time differs.  A choice is cached
+ * 2000 in 1D, 20 in 2D/3D); shapes the batch rejects are skipped.  Fields
+ * are identical for every shape, statistics to the rounding of their sums.  A choice is cached
  * for the process, keyed by precision, stats_mask, the XCD-order and
  * single-step flags and each instance's sizes, boundary, scheme, equation,
  * noise mode and material; a cached key returns

@@ -1574,7 +1574,7 @@ static hipError_t nd_enqueue(she_handle *h, hipStream_t s, const StepArg &sa, in
     if (e != hipSuccess || !may_sample) return e;
     const SpatialParts sp{h->d_part, h->d_acc, 1.0 / static_cast<double>(h->cells), two ? h->nparts2 : h->nparts,
                           h->batch_len};
-    // with S(k), the first column-transform block of each instance does the
+    // with S(k), the last column-transform block of each instance does the
     // spatial reduction (one launch fewer per sample)
     if (!(h->mask & SHE_STAT_SK))
         return launch_reduce_parts(h->n_inst, s, sa, sp.part, sp.nparts, sp.inv_cells, sp.batch_len, sp.acc);

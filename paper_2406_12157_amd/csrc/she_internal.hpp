@@ -193,9 +193,9 @@ struct Seg1D {
     int32_t w0;
     int32_t nw;
     int32_t lds;
-    int32_t cpl;        // explicit batches: cells per lane of this wave (4, 8 or 16)
-    int32_t nbig;       // explicit batches: waves of the instance with 8 cells per lane
-                        // beside others with 4 (0: all alike)
+    int32_t cpl;        // cells per lane of this wave (k_rods: 4, 8 or 16)
+    int32_t nbig;       // k_rods: waves of the instance with 8 cells per lane beside
+                        // others with 4 (0: all alike)
 };
 
 // Rods of up to kRodAlone cells are advanced by one wave in a batch with implicit
@@ -203,7 +203,7 @@ struct Seg1D {
 constexpr int kRodAlone = 512;
 __host__ __device__ constexpr int rod_cells_per_lane(int n) { return n <= 64 ? 1 : (n <= 128 ? 2 : (n <= 256 ? 4 : 8)); }
 
-// LDS bytes of one instance of an explicit batch served by nw waves: flags, the
+// LDS bytes of one instance that k_rods serves with nw waves: flags, the
 // wave sums of a batch of samples and the edge exchange (rod_waves).
 constexpr int kRodFlags = 144;
 constexpr int rod_edge(int cpl) { return cpl > 8 ? 2 * cpl : 8; }  // two units of a wave at the ends
@@ -262,8 +262,6 @@ struct InstND {
     uint32_t pad;
 };
 
-// Parameters of a 2D/3D batch: one grid, equation, scheme, noise mode and
-// seed; r, u0, eps, init_sd and the realisation per instance (InstND).
 // Exact quotients by a divisor fixed for the launch, n / d for any 32-bit n: one
 // high product, an add and two shifts (Granlund and Montgomery, Division by
 // invariant integers using multiplication, 1994), where the machine has no
@@ -287,6 +285,8 @@ __host__ __device__ __forceinline__ int quotient(int n, const FastDiv &f)
     return static_cast<int>((t + ((u - t) >> f.s1)) >> f.s2);
 }
 
+// Parameters of a 2D/3D batch: one grid, equation, scheme, noise mode and
+// seed; r, u0, eps, init_sd and the realisation per instance (InstND).
 struct ParamsND {
     int32_t nx, ny, nz;     // nz = 1 in 2D
     int32_t dim;

@@ -1,7 +1,7 @@
-// 1D batches: the step kernel of the long instances of batches with implicit ones, the time
-// correlation, initial state, finalisation, batch means and the verification
-// kernels.  Explicit batches step in she_step_1d.hpp, whose comment states the
-// scheme.
+// 1D batches: the step kernel of the long instances of batches with implicit
+// ones, the time correlation, initial state, finalisation, batch means and the
+// verification kernels.  All others step in she_step_1d.hpp, whose comment states
+// the scheme.
 //
 // Implicit schemes (backward Euler theta = 1, Crank-Nicolson theta = 1/2;
 // the implicit-scheme exercise, Sec. 6): the flux pass weights the

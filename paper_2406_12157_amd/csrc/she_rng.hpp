@@ -121,11 +121,12 @@ __device__ __forceinline__ double unit_angle_f64(uint32_t w)
 
 // FP64 Box-Muller functions for the arguments it meets, 2^23 each.  The general
 // log, sqrt and sincospi spend most of their instructions on arguments that do
-// not occur (195 vector instructions per pair; these take 82).  The
-// polynomials are minimax fits of the series named (Remez exchange in 70-digit
-// arithmetic); tails are carried where a rounding would show, so that the
-// largest error over all arguments is no larger than that of the general
-// functions.  Multiply-adds are written out and nothing else is contracted.
+// not occur (195 vector instructions per pair; these take 116, 82 where a kernel
+// keeps the constants in registers).  The polynomials are minimax fits of the
+// series named (Remez exchange in 70-digit arithmetic); tails are carried where a
+// rounding would show, so that the largest error (measured over all arguments) is
+// no larger than that of the general functions.  Multiply-adds are written out and
+// nothing else is contracted.
 
 // -2 ln(u_a), u_a = (2 (w >> 9) + 1) 2^-24.  With u_a = 2^e f, f in
 // [sqrt(1/2), sqrt(2)), and s = (f - 1) / (f + 1) (both sums exact: f has 24
@@ -136,7 +137,7 @@ __device__ __forceinline__ double neg2_log_u(uint32_t w)
     const double k = static_cast<double>((w >> 8) | 1u);  // 2^24 u_a
     const long long bits = __double_as_longlong(k);
     // exponent and significand about sqrt(1/2): high word offset so that the
-    // exponent field changes at sqrt(1/2)
+    // exponent field changes at sqrt(1/2) (the split that the BSD libm's log1p uses)
     const uint32_t h = static_cast<uint32_t>(static_cast<unsigned long long>(bits) >> 32) + (0x3FF00000u - 0x3FE6A09Eu);
     const double e = static_cast<double>(static_cast<int>(h >> 20) - (0x3FF + 24));
     const uint32_t fh = (h & 0xFFFFFu) + 0x3FE6A09Eu;

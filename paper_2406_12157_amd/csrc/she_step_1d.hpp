@@ -1,7 +1,9 @@
 #pragma once
 
-// Step kernels of explicit 1D batches and their typed launchers.  Included by
-// the translation units that instantiate them (one per state type).
+// Step kernels of 1D batches whose waves hold whole rods or shares of them, and
+// their typed launchers: explicit batches, and the rods of up to kRodAlone cells of
+// batches with implicit ones.  Included by the translation units that instantiate
+// them (one per state type, mode and kernel).
 //
 // Scheme (Garcia et al., Sec. 3): face flux F_f = r (U_f - U_{f-1}) + w sigma A N_f
 // through the low face f of cell f, update U_i += F_{i+1} - F_i (FE), or the
@@ -14,9 +16,12 @@
 // A lane holds a unit of CPL consecutive cells in registers for the whole
 // launch, and neighbouring units sit in neighbouring lanes, so a stage (the FE
 // step, or either half of a PC step) moves one cell value and one face flux
-// across by a DPP wave shift: no LDS access and no barrier.  Each face is
-// evaluated once, in the lane that owns it, so the sum is conserved bit for
-// bit.  Two kernels differ in where the numbers come from:
+// across by a DPP wave shift: no LDS access and no barrier.  A face is evaluated in
+// the lane that owns it and taken over by its neighbour, so the sum is conserved
+// bit for bit; where two waves of k_rods meet, each evaluates the face between
+// them, from the same values by the same code, whose multiply-adds are written out
+// so that every copy of it rounds alike.  Two kernels differ in where the numbers
+// come from:
 //
 // k_rods: every wave draws its own numbers, four cells per Philox call.  An
 //   instance takes whole waves of a workgroup (small instances share one).
@@ -1273,11 +1278,12 @@ __global__ void __launch_bounds__(512, CPL == 8 ? 2 : 4)
 // per lane, CMAX the largest: each rod takes that of its own length.  The order of
 // its elimination, and so its last bits, follows from that split, and taken from
 // the longest rod it would make a rod's field depend on the others.  (Explicit rods
-// have the same bits with any split.)  Us per step with CMAX's split for every
-// rod / with their own, Crank-Nicolson at r = 2: 700 rods of 3 to 256 cells FP32
-// 0.96 / 0.90, FP64 2.96 / 2.07; of 3 to 512 cells 1.92 / 1.66 and 4.55 / 3.07.  A
-// kernel with one split holds its factors in fewer registers (1024 rods of 256 cells
-// with statistics, FP64: 3.4, 4.3 with this one) and serves the batches it can.
+// have the same bits with any split.)  Us per step, CMAX's split for every rod
+// with material coefficients in registers / each its own without, Crank-Nicolson at
+// r = 2: 700 rods of 3 to 256 cells FP32 0.96 / 0.88, FP64 2.96 / 1.51; of 3 to 512
+// cells 1.92 / 1.65 and 4.5 / 2.2.  A kernel with one split holds its factors in
+// fewer registers (1024 rods of 256 cells with statistics, FP64, material
+// coefficients: 3.4, 4.3 with this one) and serves the batches it can.
 template <typename T, int CMAX, bool STATS, int MODE>
 __global__ void __launch_bounds__(512, CMAX == 8 ? 2 : 4)
     k_rods_mixed(const Inst1D *__restrict__ tab, const Seg1D *__restrict__ segs, T *__restrict__ pool,
