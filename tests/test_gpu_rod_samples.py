@@ -177,3 +177,27 @@ def test_ragged_batch_with_16_cells_per_lane(she):
             oracle.advance(d, u, 0, 42, st)
             assert max_rel(h.read_field(q), u) <= TOL[0], inst["n"]
             assert max_rel(h.stats(q)["mean"], st.mean()) < STAT_TOL[0]
+
+
+# batches shorter and longer than a launch's 256 samples
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("length", [37, 300])
+def test_batch_means(she, length, precision):
+    insts = rods(301)[:2] + rods(520)[2:]
+    with she.Handle([gpu_instance(she, i) for i in insts], precision=precision, burn_in=3, sample_every=1,
+                    stats=she.STAT_MOMENTS, batch_samples=length) as h:
+        init = [h.read_field(q) for q in range(4)]
+        for k in (200, 1, 499):
+            h.run(k)
+        got = [h.stats(q, se=True) for q in range(4)]
+    for q, inst in enumerate(insts):
+        d = oracle_desc(inst, precision)
+        st = oracle.Stats(d, burn_in=3, every=1, batch=length)
+        oracle.advance(d, init[q], 0, 700, st)
+        g, se = got[q], st.se()
+        assert g["n_samples"] == 697 and g["n_batches"] == st.n_batches == 697 // length
+        # on the scale of the largest: with two batches a cell's is half the difference
+        # of two means, which may be as small as it likes
+        for key in ("mean", "var"):
+            assert np.max(np.abs(g[key + "_se"] - se[key])) < STAT_TOL[precision] * np.max(se[key])
+        assert abs(g["spatial_var_se"] / se["spatial_var"] - 1) < STAT_TOL[precision]
