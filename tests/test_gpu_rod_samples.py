@@ -82,6 +82,26 @@ def test_composite_rods_and_rings(she, n, precision):
         assert max_rel(got[q]["var"], st.var()) < STAT_TOL[precision]
 
 
+# the kernels that look the face kind up, with 4, 8 and (FP32) 16 cells per lane
+@pytest.mark.parametrize("n,precision", [(505, 0), (505, 1), (4100, 0), (4100, 1), (7801, 0)])
+def test_mixed_face_kinds(she, n, precision):
+    insts = rods(n)[:2] + rods(n, noise=1)[2:]
+    with she.Handle([gpu_instance(she, i) for i in insts], precision=precision, sample_every=3,
+                    stats=she.STAT_MOMENTS) as h:
+        init = [h.read_field(q) for q in range(4)]
+        h.run(70)
+        fields, got = [h.read_field(q) for q in range(4)], [h.stats(q) for q in range(4)]
+    for q, inst in enumerate(insts):
+        d = oracle_desc(inst, precision)
+        st = oracle.Stats(d, burn_in=0, every=3)
+        u = init[q].copy()
+        oracle.advance(d, u, 0, 70, st)
+        assert max_rel(fields[q], u) <= TOL[precision]
+        assert got[q]["n_samples"] == 23
+        assert max_rel(got[q]["mean"], st.mean()) < STAT_TOL[precision]
+        assert max_rel(got[q]["var"], st.var()) < STAT_TOL[precision]
+
+
 @pytest.mark.parametrize("n", [301, 505, 4100])
 def test_clamps_are_counted_once(she, n):
     """A negative face mean is counted by the wave that owns the face, not by the
